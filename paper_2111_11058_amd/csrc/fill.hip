@@ -2,18 +2,20 @@
 // [T_i]_mn and the block matrix Z).
 //
 // Regular pairs: one lane per (test triangle P, source triangle Q) pair,
-// 7 x 7 point pairs, both media.  Per pair the kernel accumulates, with
-// coordinates taken relative to each triangle's own centroid (r~ = r - c_P,
-// r~' = r' - c_Q, d = c_P - c_Q, so r - r' = r~ + d - r~'):
-//   T part (per medium): I0 = S G, Ir = S G r~, Irq = S G r~', Irr = S G r~.r~'
-//   K part (media summed, g = g1 + g2): S0 = S g r~.(X x r~'),
-//     SA = S g X x r~', SB = S g r~ x X, SC = S g X        (X = r - r')
-// with S the weighted double sum, and forms the 3 x 3 local blocks
-//   T_i[a,b] = c_a c_b ( (j k_i / 4) (Irr - q~_b.Ir - p~_a.Irq + p~_a.q~_b I0)
-//                        - (j / k_i) I0 )
-//   K[a,b]   = -(c_a c_b / 4) ( S0 - p~_a.SA - q~_b.SB + p~_a.(SC x q~_b) )
-// (c_a = s_a l_a, p_a / q_b the free vertices).  Every term is of the size
-// of the result, so no cancellation grows with the distance of the pair.
+// 7 x 7 point pairs, both media.  Coordinates are taken relative to each
+// triangle's own centroid, d = c_P - c_Q.  Every point of the 7-point rule
+// lies on a median, r~_k = tau_k v_i(k) (v_i the vertex, tau = 0, tau_a or
+// tau_b; likewise r~'_l = tau_l w_j(l)), and v_2 = -v_0 - v_1, so with the
+// sums H[.] over point pairs weighted by tau in place of vectors every
+// moment of the entries
+//   T_i[a,b] = c_a c_b ( (j k_i / 4) S G (r~ - p_a).(r~' - q_b) - (j / k_i) S G )
+//   K[a,b]   = -(c_a c_b / 4) S g (r~ - p_a).(X x (r~' - q_b)),  X = r - r'
+// (S the weighted double sum, g = g1 + g2, c_a = s_a l_a, p_a = v_a and
+// q_b = w_b the free vertices) is a scalar sum times one of
+//   G_ij = v_i.w_j,  D_ij = d.(v_i x w_j),  n_j = N_P.w_j,  m_i = N_Q.v_i
+// (N_P = v_0 x v_1, N_Q = w_0 x w_1); regular_pair spells them out.  Every
+// term is of the size of the result, so no cancellation grows with the
+// distance of the pair.
 //
 // Near pairs: FP64, 7-point outer rule (one thread per pair and outer point
 // for the inner integrals, one thread per pair for the contraction); on the source
@@ -32,13 +34,8 @@ namespace cbfm {
 
 struct FillConsts {
   double w[7];
-  double wq[7][7];            // w_k w_l / (4 pi): point-pair weights of the regular rule
-  float wqf[7][7];
   double bary[7][3];
   double k1, k2r, k2i;
-  double rev1, rev2;          // k / (2 pi): phase in revolutions (FP32 path)
-  // output op o in {1, 2}: op_o = c_a c_b sum_i (A[o][i] X_i + B[o][i] I0_i)
-  double A[2][2][2], B[2][2][2];  // [op][medium][re/im]
   // near kernel: per-medium j k_i and 1/k_i^2 and the output weights e[o][i]
   double jk[2][2], ik2[2][2], e[2][2][2];
   double ksq_re, ksq_im;      // k1^2 + k2^2
@@ -47,6 +44,21 @@ struct FillConsts {
 template <typename R>
 struct cx {
   R re, im;
+};
+
+// Constants of the regular rule.
+constexpr double kTauA = 0.69614047802963365, kTauB = -0.41042619231534548;  // 1 - 3 (6 -+ sqrt 15) / 21
+constexpr double kW0 = 9.0 / 40.0, kWA = 0.12593918054482717, kWB = 0.13239415278850616;  // (155 -+ sqrt 15) / 1200
+template <typename R>
+struct PairConsts {
+  R k1, k2r, k2i;
+  R rev1, rev2;               // k / (2 pi): phase in revolutions
+  R wl[7], al[7][2];          // w_l / (4 pi) and w_l / (4 pi) times r~'_l's coordinates along w_0, w_1
+  // output op o in {1, 2}: op_o = c_a c_b sum_i (A[o][i] X_i + B[o][i] I0_i)
+  R A[2][2][2], B[2][2][2];   // [op][medium][re/im]
+  // centred phases (double): sin(k x) = x S(x^2), cos(k x) = 1 + x^2 C(x^2)
+  // per medium, and exp(k2i x)
+  R sn[2][8], cs[2][8], ex[8];
 };
 
 Media make_media(const cbfm_medium* med) {
@@ -78,16 +90,10 @@ static FillConsts make_consts(const Media& md, int layout) {
   for (int k = 0; k < 7; ++k) {
     fc.w[k] = W[k];
     for (int i = 0; i < 3; ++i) fc.bary[k][i] = B[k][i];
-    for (int l = 0; l < 7; ++l) {
-      fc.wq[k][l] = W[k] * W[l] * (0.25 / M_PI);
-      fc.wqf[k][l] = (float)fc.wq[k][l];
-    }
   }
   fc.k1 = md.k1;
   fc.k2r = md.k2r;
   fc.k2i = md.k2i;
-  fc.rev1 = md.k1 / (2 * M_PI);
-  fc.rev2 = md.k2r / (2 * M_PI);
   using C = std::complex<double>;
   const C j(0, 1);
   const C k[2] = {C(md.k1, 0), C(md.k2r, md.k2i)};
@@ -105,12 +111,6 @@ static FillConsts make_consts(const Media& md, int layout) {
   }
   for (int o = 0; o < 2; ++o)
     for (int i = 0; i < 2; ++i) {
-      const C alpha = j * k[i] / 4.0, beta = -j / k[i];
-      const C A = e[o][i] * alpha, Bc = e[o][i] * beta;
-      fc.A[o][i][0] = A.real();
-      fc.A[o][i][1] = A.imag();
-      fc.B[o][i][0] = Bc.real();
-      fc.B[o][i][1] = Bc.imag();
       fc.e[o][i][0] = e[o][i].real();
       fc.e[o][i][1] = e[o][i].imag();
     }
@@ -125,6 +125,58 @@ static FillConsts make_consts(const Media& md, int layout) {
   fc.ksq_re = ksq.real();
   fc.ksq_im = ksq.imag();
   return fc;
+}
+
+// Fits of sin(2 pi x) / x and (cos(2 pi x) - 1) / x^2 in u = x^2 for
+// |x| <= 2/9 (Chebyshev interpolation at 8 nodes in 50-digit arithmetic; the
+// rounded coefficients give sine and cosine to 8e-17).
+constexpr double kCentredRev = 2.0 / 9.0;
+static const double kSinC[8] = {6.283185307179586,   -41.34170224039948,  81.60524927595382, -76.70585973341251,
+                                42.05869238059981,   -15.094574916251993, 3.818329843398246, -0.6978101945091162};
+static const double kCosC[8] = {-19.739208802178716, 64.9393940226682,   -85.45681720665131,  60.24464136500272,
+                                -26.426256236163066, 7.903512705704424,  -1.7138232485388523, 0.27490612566708106};
+// |k2i x| up to which exp(k2i x) is its degree-8 Taylor polynomial (4e-17)
+constexpr double kCentredExp = 1.0 / 16.0;
+
+template <typename R>
+static PairConsts<R> make_pair_consts(const Media& md, int layout) {
+  const FillConsts fc = make_consts(md, layout);
+  PairConsts<R> pc{};
+  pc.k1 = (R)md.k1;
+  pc.k2r = (R)md.k2r;
+  pc.k2i = (R)md.k2i;
+  const double rev[2] = {md.k1 / (2 * M_PI), md.k2r / (2 * M_PI)};
+  pc.rev1 = (R)rev[0];
+  pc.rev2 = (R)rev[1];
+  for (int l = 0; l < 7; ++l) {
+    const double w = fc.w[l] * (0.25 / M_PI), tau = l == 0 ? 0.0 : (l < 4 ? kTauA : kTauB);
+    const int j = (l + 2) % 3;  // the vertex of point l > 0
+    pc.wl[l] = (R)w;
+    pc.al[l][0] = (R)(j == 0 ? w * tau : j == 2 ? -w * tau : 0.0);
+    pc.al[l][1] = (R)(j == 1 ? w * tau : j == 2 ? -w * tau : 0.0);
+  }
+  using C = std::complex<double>;
+  const C j(0, 1), k[2] = {C(md.k1, 0), C(md.k2r, md.k2i)};
+  for (int o = 0; o < 2; ++o)
+    for (int i = 0; i < 2; ++i) {
+      const C e(fc.e[o][i][0], fc.e[o][i][1]);
+      const C A = e * (j * k[i] / 4.0), B = e * (-j / k[i]);
+      pc.A[o][i][0] = (R)A.real();
+      pc.A[o][i][1] = (R)A.imag();
+      pc.B[o][i][0] = (R)B.real();
+      pc.B[o][i][1] = (R)B.imag();
+    }
+  for (int i = 0; i < 2; ++i) {
+    double p = rev[i];
+    for (int t = 0; t < 8; ++t, p *= rev[i]) {
+      pc.sn[i][t] = (R)(kSinC[t] * p);
+      p *= rev[i];
+      pc.cs[i][t] = (R)(kCosC[t] * p);
+    }
+  }
+  double p = 1.0;
+  for (int t = 0; t < 8; ++t) pc.ex[t] = (R)(p *= md.k2i / (t + 1));
+  return pc;
 }
 
 // ------------------------------------------------------------- phase helpers
@@ -186,200 +238,328 @@ __device__ __forceinline__ double expo(double x) { return exp(x); }
 __device__ __forceinline__ float expo(float x) { return __expf(x); }
 
 // ------------------------------------------------------------- regular kernel
-__device__ __forceinline__ double pair_weight(const FillConsts& fc, int k, int l, double) { return fc.wq[k][l]; }
-__device__ __forceinline__ float pair_weight(const FillConsts& fc, int k, int l, float) { return fc.wqf[k][l]; }
-
 // The 3 x 3 local blocks of the three output operators for test triangle P
 // and source triangle Q, written at o0 (row stride ldl, operator stride
 // op_stride).  P is the same on every lane of the wavefront (one row
-// triangle per block): its quadrature points are read into scalar
-// registers, and the loop over them is the inner one.  The outer loop runs
-// over the lane's own source points r~'_l, so that only one of them (and
-// e_l = d - r~'_l, with X = r~_k + e_l) is held per lane.  Per source point
-// the inner sums over the test points are
-//   A0 = S_k G,  B0 = S_k g,  B1 = S_k g r~_k,
-// and the moments follow from them and the lane's vectors:
-//   S_k g X = B1 + e_l B0,   S_k g X x r~' = (S_k g X) x r~',
-//   S_k g r~ x X = B1 x e_l, S_k g r~.(X x r~') = B1.(e_l x r~')
-// (r~ x r~ = 0 and r~.(r~ x r~') = 0 drop out exactly); Ir and Irr take
-// the test point itself and are summed in the inner loop.
-template <typename R, bool LOSSY>
-__device__ __forceinline__ void regular_pair(const TriTab<R>& tab, int32_t P, int32_t Q, const FillConsts& fc,
-                                             cx<R>* __restrict__ o0, int64_t op_stride, int64_t ldl) {
+// triangle per block): its constants come through scalar loads, and the
+// loop over its points is the inner, unrolled one; the outer loop runs over
+// the lane's own source points.  Sums are kept as a - j b.
+//
+// CENTRED (double): with R_c = |d| the phase factors are taken of R - R_c,
+// at most the sum of the two triangles' radii, so short polynomials without
+// argument reduction serve (kCentredRev, kCentredExp bound the range);
+// medium 2 is turned by e^{-j (k2 - k1) R_c} per point pair and the blocks
+// by e^{-j k1 R_c} once.
+//
+// Bound by VALU issue and then by the stores (432 bytes a pair in double):
+// per point pair and both lossless media 85 vector instructions in double
+// (R^2 2, 1/R 5, sine and cosine 35, the kernels 19, sums 14, and a seventh
+// of what each source point costs), 49 in float.  The form that summed
+// vectors and reduced every phase took 123.  19,968-triangle cylinder,
+// eight panels (225 M pairs): 62.7 -> 49.9 ms in double, 3.6 and 4.5 G pairs/s
+// (39 ms of it without the stores); 19.4 M pairs in float: 2.40 -> 1.72 ms.
+// Three waves per SIMD in double (168 registers) spill: 86 ms.
+template <typename R, bool LOSSY, bool CENTRED>
+__device__ __forceinline__ void regular_blocks(const TriTab<R>& tab, int32_t P, int32_t Q, const PairConsts<R>& pc,
+                                               cx<R>* __restrict__ o0, int64_t op_stride, int64_t ldl) {
   const int64_t nt = tab.nt;
-  P = __builtin_amdgcn_readfirstlane(P);
-
+  const R* __restrict__ tp = tab.test + (int64_t)kTestVals * P;
   const R d[3] = {(R)(tab.cen[0][P] - tab.cen[0][Q]), (R)(tab.cen[1][P] - tab.cen[1][Q]),
                   (R)(tab.cen[2][P] - tab.cen[2][Q])};
-  const R k1 = (R)fc.k1, k2r = (R)fc.k2r, k2i = (R)fc.k2i;
-  const R rev1 = (R)fc.rev1, rev2 = (R)fc.rev2;
+  R dv[2];  // d.v_i
+#pragma unroll
+  for (int i = 0; i < 2; ++i) dv[i] = d[0] * tp[3 * i] + d[1] * tp[3 * i + 1] + d[2] * tp[3 * i + 2];
+  R Rc = 0, pr = 1, pi = 0;  // |d|, and medium 2's turn pr - j pi
+  if constexpr (CENTRED) {
+    const R d2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+    Rc = d2 > (R)0 ? d2 * rsq(d2) : (R)0;
+    phase((R)0, (pc.rev2 - pc.rev1) * Rc, pi, pr);
+    if (LOSSY) {
+      const R x = expo(pc.k2i * Rc);
+      pr *= x;
+      pi *= x;
+    }
+  }
+  // [.][0] = a, [.][1] = b of a - j b
+  R I0[2][2] = {}, Ir[2][2][2] = {}, Iq[2][2][2] = {}, Irr[2][2] = {};  // G: 1, r~ (coordinates), r~', r~.r~'
+  R b0[2] = {}, hs[2][2] = {}, bq[2][2] = {}, H[2][2][2] = {};          // g: 1, r~, r~', r~ r~' (coordinates)
 
-  cx<R> I0[2] = {}, Ir[2][3] = {}, Irq[2][3] = {}, Irr[2] = {};
-  cx<R> S0 = {}, SA[3] = {}, SB[3] = {}, SC[3] = {};
-
+  // (double: the next source point is loaded one step ahead, 2 % of the
+  // launch; in float the four waves per SIMD hide the loads)
+  constexpr bool AHEAD = std::is_same<R, double>::value;
+  R nx[3] = {tab.q[0][Q], tab.q[1][Q], tab.q[2][Q]};
 #pragma unroll 1
   for (int l = 0; l < 7; ++l) {
-    const R rq[3] = {tab.q[0][l * nt + Q], tab.q[1][l * nt + Q], tab.q[2][l * nt + Q]};
+    const int64_t at = (AHEAD ? (l < 6 ? l + 1 : 0) : l) * nt + Q;
+    R rq[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const R v = tab.q[c][at];
+      rq[c] = AHEAD ? nx[c] : v;
+      nx[c] = v;
+    }
     const R e[3] = {d[0] - rq[0], d[1] - rq[1], d[2] - rq[2]};
-    cx<R> A0[2] = {}, B0 = {}, B1[3] = {};
+    const R s0 = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
+    R D[3];  // e.v_i
+#pragma unroll
+    for (int i = 0; i < 2; ++i) D[i] = e[0] * tp[3 * i] + e[1] * tp[3 * i + 1] + e[2] * tp[3 * i + 2];
+    D[2] = -D[0] - D[1];
+    const R wl = pc.wl[l], a0 = pc.al[l][0], a1 = pc.al[l][1];
+    const R rv0 = wl * (dv[0] - D[0]), rv1 = wl * (dv[1] - D[1]);  // r~'.v_i
+    R A0[2][2] = {}, h[2][2][2] = {}, B0[2] = {}, hg[2][2] = {};
 #pragma unroll
     for (int k = 0; k < 7; ++k) {
-      const R rk[3] = {tab.q[0][k * nt + P], tab.q[1][k * nt + P], tab.q[2][k * nt + P]};
-      const R x0 = rk[0] + e[0], x1 = rk[1] + e[1], x2 = rk[2] + e[2];
-      const R R2 = x0 * x0 + x1 * x1 + x2 * x2;
+      const int i = (k + 2) % 3;  // the vertex of point k > 0
+      const R tau = (R)(k < 4 ? kTauA : kTauB), wk = (R)(k == 0 ? kW0 : k < 4 ? kWA : kWB);
+      const R R2 = k == 0 ? s0 : fma((R)2 * tau, D[i], s0 + tp[9 + (k - 1)]);
       const R iR = rsq(R2);
       const R Rl = R2 * iR;
-      const R f = pair_weight(fc, k, l, R(0)) * iR;  // w_k w_l / (4 pi R)
       const R t = iR * iR;
-      // exterior medium
-      const R ph1 = k1 * Rl;
-      R s1, c1;
-      phase(ph1, rev1 * Rl, s1, c1);
-      const cx<R> G1 = {c1 * f, -s1 * f};
-      // interior medium
-      const R ph2 = k2r * Rl;
-      R s2, c2;
-      phase(ph2, rev2 * Rl, s2, c2);
-      R f2 = f;
-      R u = (R)1;
-      if (LOSSY) {
-        f2 = f * expo(k2i * Rl);
-        u = (R)1 - k2i * Rl;
+      const R x1 = pc.k1 * Rl, x2 = pc.k2r * Rl;
+      R s1, c1, s2, c2;
+      if constexpr (CENTRED) {
+        const R dl = Rl - Rc, u = dl * dl;
+        s1 = pc.sn[0][7];
+        s2 = pc.sn[1][7];
+        c1 = pc.cs[0][7];
+        c2 = pc.cs[1][7];
+#pragma unroll
+        for (int q = 6; q >= 0; --q) {
+          s1 = fma(s1, u, pc.sn[0][q]);
+          s2 = fma(s2, u, pc.sn[1][q]);
+          c1 = fma(c1, u, pc.cs[0][q]);
+          c2 = fma(c2, u, pc.cs[1][q]);
+        }
+        s1 *= dl;
+        s2 *= dl;
+        c1 = fma(c1, u, (R)1);
+        c2 = fma(c2, u, (R)1);
+        if (LOSSY) {
+          R x = pc.ex[7];
+#pragma unroll
+          for (int q = 6; q >= 0; --q) x = fma(x, dl, pc.ex[q]);
+          x = fma(x, dl, (R)1);
+          s2 *= x;
+          c2 *= x;
+        }
+        const R c = c2 * pr - s2 * pi;
+        s2 = s2 * pr + c2 * pi;
+        c2 = c;
+      } else {
+        phase(x1, pc.rev1 * Rl, s1, c1);
+        phase(x2, pc.rev2 * Rl, s2, c2);
+        if (LOSSY) {
+          const R x = expo(pc.k2i * Rl);
+          s2 *= x;
+          c2 *= x;
+        }
       }
-      const cx<R> G2 = {c2 * f2, -s2 * f2};
-      // g = -G (1 + j k R) / R^2, summed over media (weights included)
-      const cx<R> g = {-((G1.re - ph1 * G1.im) + (u * G2.re - ph2 * G2.im)) * t,
-                       -((G1.im + ph1 * G1.re) + (u * G2.im + ph2 * G2.re)) * t};
-      A0[0].re += G1.re;
-      A0[0].im += G1.im;
-      A0[1].re += G2.re;
-      A0[1].im += G2.im;
-      B0.re += g.re;
-      B0.im += g.im;
-      const R rr = rk[0] * rq[0] + rk[1] * rq[1] + rk[2] * rq[2];
-      Irr[0].re += G1.re * rr;
-      Irr[0].im += G1.im * rr;
-      Irr[1].re += G2.re * rr;
-      Irr[1].im += G2.im * rr;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const R q = rk[c];
-        Ir[0][c].re += G1.re * q;
-        Ir[0][c].im += G1.im * q;
-        Ir[1][c].re += G2.re * q;
-        Ir[1][c].im += G2.im * q;
-        B1[c].re += g.re * q;
-        B1[c].im += g.im * q;
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      I0[m].re += A0[m].re;
-      I0[m].im += A0[m].im;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        Irq[m][c].re += A0[m].re * rq[c];
-        Irq[m][c].im += A0[m].im * rq[c];
-      }
-    }
-    // K moments of this source point
-    cx<R> X[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      X[c].re = B1[c].re + e[c] * B0.re;  // S_k g X
-      X[c].im = B1[c].im + e[c] * B0.im;
-    }
-    R ex[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const int c1 = (c + 1) % 3, c2 = (c + 2) % 3;
-      ex[c] = e[c1] * rq[c2] - e[c2] * rq[c1];                  // e_l x r~'
-      SC[c].re += X[c].re;
-      SC[c].im += X[c].im;
-      SA[c].re += X[c1].re * rq[c2] - X[c2].re * rq[c1];         // (S_k g X) x r~'
-      SA[c].im += X[c1].im * rq[c2] - X[c2].im * rq[c1];
-      SB[c].re += B1[c1].re * e[c2] - B1[c2].re * e[c1];         // B1 x e_l
-      SB[c].im += B1[c1].im * e[c2] - B1[c2].im * e[c1];
-    }
-    S0.re += B1[0].re * ex[0] + B1[1].re * ex[1] + B1[2].re * ex[2];
-    S0.im += B1[0].im * ex[0] + B1[1].im * ex[1] + B1[2].im * ex[2];
-  }
-
-  // epilogue: 3 x 3 local blocks of K, op1, op2
-  R pv[3][3], qv[3][3], ca[3], cb[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    ca[a] = tab.c[a * nt + P];
-    cb[a] = tab.c[a * nt + Q];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      pv[a][c] = tab.v[c][a * nt + P];
-      qv[a][c] = tab.v[c][a * nt + Q];
-    }
-  }
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const R* p = pv[a];
-    const cx<R> pSA = {p[0] * SA[0].re + p[1] * SA[1].re + p[2] * SA[2].re,
-                       p[0] * SA[0].im + p[1] * SA[1].im + p[2] * SA[2].im};
-    cx<R> pIrq[2];
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      pIrq[m].re = p[0] * Irq[m][0].re + p[1] * Irq[m][1].re + p[2] * Irq[m][2].re;
-      pIrq[m].im = p[0] * Irq[m][0].im + p[1] * Irq[m][1].im + p[2] * Irq[m][2].im;
-    }
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      const R* q = qv[b];
-      const R cab = ca[a] * cb[b];
-      // K
-      cx<R> SCxq[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const int c1 = (c + 1) % 3, c2 = (c + 2) % 3;
-        SCxq[c].re = SC[c1].re * q[c2] - SC[c2].re * q[c1];
-        SCxq[c].im = SC[c1].im * q[c2] - SC[c2].im * q[c1];
-      }
-      const R kre = S0.re - pSA.re - (q[0] * SB[0].re + q[1] * SB[1].re + q[2] * SB[2].re) +
-                    (p[0] * SCxq[0].re + p[1] * SCxq[1].re + p[2] * SCxq[2].re);
-      const R kim = S0.im - pSA.im - (q[0] * SB[0].im + q[1] * SB[1].im + q[2] * SB[2].im) +
-                    (p[0] * SCxq[0].im + p[1] * SCxq[1].im + p[2] * SCxq[2].im);
-      const R kf = (R)(-0.25) * cab;
-      o0[a * ldl + b] = cx<R>{kf * kre, kf * kim};
-      // T per medium: X_m = Irr - q.Ir - p.Irq + (p.q) I0
-      const R pq = p[0] * q[0] + p[1] * q[1] + p[2] * q[2];
-      cx<R> X[2];
+      // G = ga - j gb; g = -G (1 + j k R) / R^2, summed over the media
+      const R ga[2] = {c1 * iR, c2 * iR}, gb[2] = {s1 * iR, s2 * iR};
+      const R u2 = LOSSY ? (R)1 - pc.k2i * Rl : (R)1;
+      const R p = (fma(gb[0], x1, ga[0]) + fma(gb[1], x2, LOSSY ? u2 * ga[1] : ga[1])) * t;
+      const R q = (fma(-ga[0], x1, gb[0]) + fma(-ga[1], x2, LOSSY ? u2 * gb[1] : gb[1])) * t;
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
-        X[m].re = Irr[m].re - (q[0] * Ir[m][0].re + q[1] * Ir[m][1].re + q[2] * Ir[m][2].re) -
-                  pIrq[m].re + pq * I0[m].re;
-        X[m].im = Irr[m].im - (q[0] * Ir[m][0].im + q[1] * Ir[m][1].im + q[2] * Ir[m][2].im) -
-                  pIrq[m].im + pq * I0[m].im;
+        A0[m][0] = fma(wk, ga[m], A0[m][0]);
+        A0[m][1] = fma(wk, gb[m], A0[m][1]);
       }
+      B0[0] = fma(wk, p, B0[0]);
+      B0[1] = fma(wk, q, B0[1]);
+      if (k > 0) {
+        const R wt = i == 2 ? -wk * tau : wk * tau;
 #pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        R re = 0, im = 0;
+        for (int c = 0; c < 2; ++c)
+          if (i == c || i == 2) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          const R Ar = (R)fc.A[o][m][0], Ai = (R)fc.A[o][m][1];
-          const R Br = (R)fc.B[o][m][0], Bi = (R)fc.B[o][m][1];
-          re += Ar * X[m].re - Ai * X[m].im + Br * I0[m].re - Bi * I0[m].im;
-          im += Ar * X[m].im + Ai * X[m].re + Br * I0[m].im + Bi * I0[m].re;
-        }
-        o0[(o + 1) * op_stride + a * ldl + b] = cx<R>{cab * re, cab * im};
+            for (int m = 0; m < 2; ++m) {
+              h[m][c][0] = fma(wt, ga[m], h[m][c][0]);
+              h[m][c][1] = fma(wt, gb[m], h[m][c][1]);
+            }
+            hg[c][0] = fma(wt, p, hg[c][0]);
+            hg[c][1] = fma(wt, q, hg[c][1]);
+          }
+      }
+    }
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        I0[m][z] = fma(wl, A0[m][z], I0[m][z]);
+        Ir[m][0][z] = fma(wl, h[m][0][z], Ir[m][0][z]);
+        Ir[m][1][z] = fma(wl, h[m][1][z], Ir[m][1][z]);
+        Iq[m][0][z] = fma(a0, A0[m][z], Iq[m][0][z]);
+        Iq[m][1][z] = fma(a1, A0[m][z], Iq[m][1][z]);
+        Irr[m][z] = fma(rv0, h[m][0][z], fma(rv1, h[m][1][z], Irr[m][z]));
+      }
+      b0[z] = fma(wl, B0[z], b0[z]);
+      hs[0][z] = fma(wl, hg[0][z], hs[0][z]);
+      hs[1][z] = fma(wl, hg[1][z], hs[1][z]);
+      bq[0][z] = fma(a0, B0[z], bq[0][z]);
+      bq[1][z] = fma(a1, B0[z], bq[1][z]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        H[i][0][z] = fma(a0, hg[i][z], H[i][0][z]);
+        H[i][1][z] = fma(a1, hg[i][z], H[i][1][z]);
+      }
+    }
+  }
+
+  // ---- the blocks.  cab = c_a c_b; every index-2 value is minus the sum of
+  // the other two (v_2 = -v_0 - v_1, w_2 = -w_0 - w_1).
+  R w[2][3], cb[3];
+#pragma unroll
+  for (int b = 0; b < 3; ++b) cb[b] = tab.c[b * nt + Q];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) w[b][c] = tab.v[c][b * nt + Q];
+  const R* ca = tp + 15;
+  R ec = 1, es = 0;  // the turn e^{-j k1 R_c} = ec - j es of every sum
+  if constexpr (CENTRED) phase((R)0, pc.rev1 * Rc, es, ec);
+  {
+    // K = -(c_a c_b / 4) [S0 + U_a + W_b - b0 D_ab + ch_a n_b - m_a cq_b]:
+    //   S0 = -sum_ij H_ij D_ij,
+    //   U_0 = -Y_1 + sum_j bq_j D_0j, U_1 = Y_0 + sum_j bq_j D_1j,  Y_i = sum_j H_ij n_j,
+    //   W_0 = -Z_1 + sum_i hs_i D_i0, W_1 = Z_0 + sum_i hs_i D_i1,  Z_j = sum_i H_ij m_i,
+    //   ch = (hs_1, -hs_0, .), cq = (-bq_1, bq_0, .)
+    auto turn = [&](R(&z)[2]) {  // times -(g's sign) e^{-j k1 R_c} / 4, to re, im
+      const R a = z[0], b = z[1];
+      z[0] = (R)0.25 * (a * ec - b * es);
+      z[1] = (R)-0.25 * (a * es + b * ec);
+    };
+    turn(b0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      turn(hs[i]);
+      turn(bq[i]);
+      turn(H[i][0]);
+      turn(H[i][1]);
+    }
+    R Dm[3][3], n[3], m[3];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      // D_ab = d.(v_a x w_b) = v_a.(w_b x d)
+      const R x[3] = {w[b][1] * d[2] - w[b][2] * d[1], w[b][2] * d[0] - w[b][0] * d[2], w[b][0] * d[1] - w[b][1] * d[0]};
+#pragma unroll
+      for (int a = 0; a < 2; ++a) Dm[a][b] = x[0] * tp[3 * a] + x[1] * tp[3 * a + 1] + x[2] * tp[3 * a + 2];
+      Dm[2][b] = -Dm[0][b] - Dm[1][b];
+      n[b] = w[b][0] * tp[6] + w[b][1] * tp[7] + w[b][2] * tp[8];
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) Dm[a][2] = -Dm[a][0] - Dm[a][1];
+    n[2] = -n[0] - n[1];
+    const R nq[3] = {w[0][1] * w[1][2] - w[0][2] * w[1][1], w[0][2] * w[1][0] - w[0][0] * w[1][2],
+                     w[0][0] * w[1][1] - w[0][1] * w[1][0]};
+#pragma unroll
+    for (int a = 0; a < 2; ++a) m[a] = nq[0] * tp[3 * a] + nq[1] * tp[3 * a + 1] + nq[2] * tp[3 * a + 2];
+    m[2] = -m[0] - m[1];
+    R out[3][3][2];
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+      const R S0 = -(H[0][0][z] * Dm[0][0] + H[0][1][z] * Dm[0][1] + H[1][0][z] * Dm[1][0] + H[1][1][z] * Dm[1][1]);
+      R U[3], W[3];
+      U[0] = bq[0][z] * Dm[0][0] + bq[1][z] * Dm[0][1] - (H[1][0][z] * n[0] + H[1][1][z] * n[1]);
+      U[1] = bq[0][z] * Dm[1][0] + bq[1][z] * Dm[1][1] + (H[0][0][z] * n[0] + H[0][1][z] * n[1]);
+      U[2] = -U[0] - U[1];
+      W[0] = hs[0][z] * Dm[0][0] + hs[1][z] * Dm[1][0] - (H[0][1][z] * m[0] + H[1][1][z] * m[1]);
+      W[1] = hs[0][z] * Dm[0][1] + hs[1][z] * Dm[1][1] + (H[0][0][z] * m[0] + H[1][0][z] * m[1]);
+      W[2] = -W[0] - W[1];
+      const R ch[3] = {hs[1][z], -hs[0][z], hs[0][z] - hs[1][z]}, cq[3] = {-bq[1][z], bq[0][z], bq[1][z] - bq[0][z]};
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const R ua = S0 + U[a];
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+          out[a][b][z] = ua + W[b] - b0[z] * Dm[a][b] + ch[a] * n[b] - m[a] * cq[b];
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        const R cab = ca[a] * cb[b];
+        o0[a * ldl + b] = cx<R>{cab * out[a][b][0], cab * out[a][b][1]};
+      }
+  }
+  // T: X_m = Irr - q_b.Ir - p_a.Iq + (p_a.q_b) I0 per medium, with
+  // q_b.Ir = sum_i Ir_i G_ib and p_a.Iq = sum_j Iq_j G_aj; the media are
+  // combined (A, B) before the nine pairs
+  R G[3][3];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a) G[a][b] = w[b][0] * tp[3 * a] + w[b][1] * tp[3 * a + 1] + w[b][2] * tp[3 * a + 2];
+    G[2][b] = -G[0][b] - G[1][b];
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) G[a][2] = -G[a][0] - G[a][1];
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    R M[6][2] = {};  // Irr (+ the B term), Ir_0, Ir_1, Iq_0, Iq_1, I0 of this operator: re, im
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      // (A e^{-j k1 R_c}) (a - j b)
+      auto add = [&](R(&z)[2], R Ar, R Ai, const R(&x)[2]) {
+        z[0] += Ar * x[0] + Ai * x[1];
+        z[1] += Ai * x[0] - Ar * x[1];
+      };
+      const R Ar = pc.A[o][m][0] * ec + pc.A[o][m][1] * es, Ai = pc.A[o][m][1] * ec - pc.A[o][m][0] * es;
+      const R Br = pc.B[o][m][0] * ec + pc.B[o][m][1] * es, Bi = pc.B[o][m][1] * ec - pc.B[o][m][0] * es;
+      add(M[0], Ar, Ai, Irr[m]);
+      add(M[0], Br, Bi, I0[m]);
+      add(M[1], Ar, Ai, Ir[m][0]);
+      add(M[2], Ar, Ai, Ir[m][1]);
+      add(M[3], Ar, Ai, Iq[m][0]);
+      add(M[4], Ar, Ai, Iq[m][1]);
+      add(M[5], Ar, Ai, I0[m]);
+    }
+    R qb[3][2];
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+      qb[0][z] = M[1][z] * G[0][0] + M[2][z] * G[1][0];
+      qb[1][z] = M[1][z] * G[0][1] + M[2][z] * G[1][1];
+      qb[2][z] = -qb[0][z] - qb[1][z];
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      R pa[2];
+#pragma unroll
+      for (int z = 0; z < 2; ++z) pa[z] = M[0][z] - (M[3][z] * G[a][0] + M[4][z] * G[a][1]);
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        const R cab = ca[a] * cb[b];
+        o0[(o + 1) * op_stride + a * ldl + b] =
+            cx<R>{cab * (pa[0] - qb[b][0] + M[5][0] * G[a][b]), cab * (pa[1] - qb[b][1] + M[5][1] * G[a][b])};
       }
     }
   }
 }
 
 template <typename R, bool LOSSY>
+__device__ __forceinline__ void regular_pair(const TriTab<R>& tab, int32_t P, int32_t Q, const PairConsts<R>& pc,
+                                             cx<R>* __restrict__ o0, int64_t op_stride, int64_t ldl) {
+  P = __builtin_amdgcn_readfirstlane(P);
+  if constexpr (std::is_same<R, double>::value) {
+    // |R - R_c| is at most the sum of the triangles' radii
+    const double x = tab.rad[P] + tab.rad[Q];
+    const bool wide = fmax(pc.rev1, pc.rev2) * x > kCentredRev || (LOSSY && -pc.k2i * x > kCentredExp);
+    if (!__any(wide)) {
+      regular_blocks<R, LOSSY, true>(tab, P, Q, pc, o0, op_stride, ldl);
+      return;
+    }
+  }
+  regular_blocks<R, LOSSY, false>(tab, P, Q, pc, o0, op_stride, ldl);
+}
+
+template <typename R, bool LOSSY>
 __global__ void __launch_bounds__(256, 2) fill_regular_kernel(
     TriTab<R> tab, const int32_t* __restrict__ rowTris, const int32_t* __restrict__ colTris,
-    int64_t nct, FillConsts fc, cx<R>* __restrict__ out, int64_t op_stride, int64_t ldl) {
+    int64_t nct, PairConsts<R> pc, cx<R>* __restrict__ out, int64_t op_stride, int64_t ldl) {
   const int64_t i = blockIdx.y;
   const int64_t jq = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (jq >= nct) return;
-  regular_pair<R, LOSSY>(tab, rowTris[i], colTris[jq], fc, out + (3 * i) * ldl + 3 * jq, op_stride, ldl);
+  regular_pair<R, LOSSY>(tab, rowTris[i], colTris[jq], pc, out + (3 * i) * ldl + 3 * jq, op_stride, ldl);
 }
 
 // Many fills (scatterers of any size, each with its own medium) in one
@@ -388,16 +568,17 @@ __global__ void __launch_bounds__(256, 2) fill_regular_kernel(
 template <typename R>
 struct FillJob {
   TriTab<R> tab;
-  FillConsts fc;
+  PairConsts<R> pc;
   const int32_t* rowTris;
   const int32_t* colTris;
   int64_t nct, op_stride, ldl;
   cx<R>* out;
-  int32_t lossy;
   int64_t item0;  // first work item of the job
 };
 
-template <typename R>
+// (LOSSY: some job's medium is lossy; the factors it adds are exactly 1 for
+// the others.  One instantiation with both forms inside spilled registers.)
+template <typename R, bool LOSSY>
 __global__ void __launch_bounds__(256, 2) fill_regular_batch_kernel(const FillJob<R>* __restrict__ jobs, int njobs,
                                                                      int64_t total) {
   for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
@@ -415,10 +596,7 @@ __global__ void __launch_bounds__(256, 2) fill_regular_batch_kernel(const FillJo
     const int64_t i = local / chunks, jq = (local % chunks) * 256 + threadIdx.x;
     if (jq >= J.nct) continue;
     cx<R>* o0 = J.out + (3 * i) * J.ldl + 3 * jq;
-    if (J.lossy)
-      regular_pair<R, true>(J.tab, J.rowTris[i], J.colTris[jq], J.fc, o0, J.op_stride, J.ldl);
-    else
-      regular_pair<R, false>(J.tab, J.rowTris[i], J.colTris[jq], J.fc, o0, J.op_stride, J.ldl);
+    regular_pair<R, LOSSY>(J.tab, J.rowTris[i], J.colTris[jq], J.pc, o0, J.op_stride, J.ldl);
   }
 }
 
@@ -707,19 +885,19 @@ void fill_local(const cbfm_mesh_s* m, const Media& md, int precision, int layout
     auto* out = static_cast<cx<double>*>(local);
     if (lossy)
       hipLaunchKernelGGL((fill_regular_kernel<double, true>), grid, dim3(256), 0, s, m->tab64(), rowTris,
-                         colTris, nct, fc, out, op_stride, ldl);
+                         colTris, nct, make_pair_consts<double>(md, layout), out, op_stride, ldl);
     else
       hipLaunchKernelGGL((fill_regular_kernel<double, false>), grid, dim3(256), 0, s, m->tab64(), rowTris,
-                         colTris, nct, fc, out, op_stride, ldl);
+                         colTris, nct, make_pair_consts<double>(md, layout), out, op_stride, ldl);
     CBFM_HIP(hipGetLastError());
   } else {
     auto* out = static_cast<cx<float>*>(local);
     if (lossy)
       hipLaunchKernelGGL((fill_regular_kernel<float, true>), grid, dim3(256), 0, s, m->tab32(), rowTris,
-                         colTris, nct, fc, out, op_stride, ldl);
+                         colTris, nct, make_pair_consts<float>(md, layout), out, op_stride, ldl);
     else
       hipLaunchKernelGGL((fill_regular_kernel<float, false>), grid, dim3(256), 0, s, m->tab32(), rowTris,
-                         colTris, nct, fc, out, op_stride, ldl);
+                         colTris, nct, make_pair_consts<float>(md, layout), out, op_stride, ldl);
   }
   CBFM_HIP(hipGetLastError());
   }
@@ -753,6 +931,7 @@ static void batch_launch(const std::vector<FillBatchItem>& items, hipStream_t s)
   std::vector<FillJob<R>> jobs;
   int64_t total = 0;
   double pairs = 0;
+  bool lossy = false;
   for (const FillBatchItem& it : items) {
     if (it.nrt == 0 || it.nct == 0) continue;
     FillJob<R> j{};
@@ -760,14 +939,14 @@ static void batch_launch(const std::vector<FillBatchItem>& items, hipStream_t s)
       j.tab = it.m->tab64();
     else
       j.tab = it.m->tab32();
-    j.fc = make_consts(it.md, it.layout);
+    j.pc = make_pair_consts<R>(it.md, it.layout);
     j.rowTris = it.rowTris;
     j.colTris = it.colTris;
     j.nct = it.nct;
     j.ldl = 3 * it.nct;
     j.op_stride = 3 * it.nrt * j.ldl;
     j.out = static_cast<cx<R>*>(it.local);
-    j.lossy = it.md.k2i != 0.0;
+    lossy = lossy || it.md.k2i != 0.0;
     j.item0 = total;
     total += it.nrt * ((it.nct + 255) / 256);
     pairs += (double)it.nrt * (double)it.nct;
@@ -783,8 +962,8 @@ static void batch_launch(const std::vector<FillBatchItem>& items, hipStream_t s)
   {
     TimedLaunch tl(std::is_same<R, double>::value ? T_FILL_REGULAR : T_FILL_REGULAR_F32, s,
                    pairs);  // work: triangle pairs
-    hipLaunchKernelGGL(fill_regular_batch_kernel<R>, dim3((unsigned)grid), dim3(256), 0, s, dev.as<FillJob<R>>(),
-                       (int)jobs.size(), total);
+    hipLaunchKernelGGL((lossy ? fill_regular_batch_kernel<R, true> : fill_regular_batch_kernel<R, false>),
+                       dim3((unsigned)grid), dim3(256), 0, s, dev.as<FillJob<R>>(), (int)jobs.size(), total);
     CBFM_HIP(hipGetLastError());
   }
   CBFM_HIP(hipStreamSynchronize(s));  // the job table is host memory of this frame

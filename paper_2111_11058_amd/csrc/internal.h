@@ -166,8 +166,12 @@ struct TriTab {
   const R* v[3];    // vertices (free vertices of the local functions), [a * nt + t]
   const R* c;       // s_a * l_a, [a * nt + t]
   const double* cen[3];  // centroid
+  const R* test;         // a test triangle's constants, kTestVals per triangle (upload in mesh.cpp)
+  const double* rad;     // largest distance of a quadrature point from the centroid
   int64_t nt;
 };
+// v_0, v_1, v_0 x v_1, |tau_a v_i|^2, |tau_b v_i|^2 and c_i (three each)
+constexpr int kTestVals = 18;
 
 struct NearPair {
   int32_t p, q;     // triangles
@@ -207,7 +211,8 @@ struct cbfm_mesh_s {
   std::vector<double> shift;   // nblocks * 3
   std::vector<int32_t> tcell;  // triangle -> its cell (translated meshes)
   // device tables
-  cbfm::DevBuf q64, v64, c64, q32, v32, c32, cen;   // SoA geometry
+  cbfm::DevBuf q64, v64, c64, q32, v32, c32, cen, rad;   // SoA geometry
+  cbfm::DevBuf test64, test32;  // test-side constants, one record per triangle
   cbfm::DevBuf tri_edge, tri_sign, tplus, tminus, aplus, aminus, length, area;
   cbfm::DevBuf tri_xyz;        // nt*9 absolute vertex coordinates (double)
   cbfm::DevBuf perm, iperm;    // int32

@@ -206,6 +206,8 @@ cbfm::TriTab<double> cbfm_mesh_s::tab64() const {
     t.cen[i] = cen.as<double>() + i * nt;
   }
   t.c = c64.as<double>();
+  t.test = test64.as<double>();
+  t.rad = rad.as<double>();
   t.nt = nt;
   return t;
 }
@@ -219,6 +221,8 @@ cbfm::TriTab<float> cbfm_mesh_s::tab32() const {
     t.cen[i] = cen.as<double>() + i * nt;
   }
   t.c = c32.as<float>();
+  t.test = test32.as<float>();
+  t.rad = rad.as<double>();
   t.nt = nt;
   return t;
 }
@@ -271,8 +275,9 @@ static void upload(cbfm_mesh_s* m) {
   const int64_t nt = h.nt;
   double bary[7][3];
   quad_rule(bary);
-  std::vector<double> q64(3 * 7 * nt), v64(3 * 3 * nt), c64(3 * nt), cen(3 * nt), xyz9(9 * nt);
-  std::vector<float> q32(q64.size()), v32(v64.size()), c32(c64.size());
+  std::vector<double> q64(3 * 7 * nt), v64(3 * 3 * nt), c64(3 * nt), cen(3 * nt), xyz9(9 * nt), rad(nt),
+      test64(kTestVals * nt);
+  std::vector<float> q32(q64.size()), v32(v64.size()), c32(c64.size()), test32(test64.size());
   for (int64_t t = 0; t < nt; ++t) {
     const double* P[3] = {&h.V[3 * h.T[t * 3]], &h.V[3 * h.T[t * 3 + 1]], &h.V[3 * h.T[t * 3 + 2]]};
     const double* c = &h.centroid[3 * t];
@@ -289,10 +294,24 @@ static void upload(cbfm_mesh_s* m) {
     }
     for (int a = 0; a < 3; ++a)
       c64[a * nt + t] = h.tri_sign[t * 3 + a] * h.length[h.tri_edge[t * 3 + a]];
+    double* tt = &test64[kTestVals * t];
+    for (int i = 0; i < 3; ++i) {
+      const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
+      auto v = [&](int a, int x) { return v64[(x * 3 + a) * nt + t]; };
+      auto q = [&](int k, int x) { return q64[(x * 7 + k) * nt + t]; };
+      tt[i] = v(0, i);
+      tt[3 + i] = v(1, i);
+      tt[6 + i] = v(0, i1) * v(1, i2) - v(0, i2) * v(1, i1);
+      tt[9 + i] = q(1 + i, 0) * q(1 + i, 0) + q(1 + i, 1) * q(1 + i, 1) + q(1 + i, 2) * q(1 + i, 2);
+      tt[12 + i] = q(4 + i, 0) * q(4 + i, 0) + q(4 + i, 1) * q(4 + i, 1) + q(4 + i, 2) * q(4 + i, 2);
+      tt[15 + i] = c64[i * nt + t];
+      rad[t] = std::max({rad[t], std::sqrt(tt[9 + i]), std::sqrt(tt[12 + i])});
+    }
   }
   for (size_t i = 0; i < q64.size(); ++i) q32[i] = (float)q64[i];
   for (size_t i = 0; i < v64.size(); ++i) v32[i] = (float)v64[i];
   for (size_t i = 0; i < c64.size(); ++i) c32[i] = (float)c64[i];
+  for (size_t i = 0; i < test64.size(); ++i) test32[i] = (float)test64[i];
   m->q64.upload(q64);
   m->v64.upload(v64);
   m->c64.upload(c64);
@@ -300,6 +319,9 @@ static void upload(cbfm_mesh_s* m) {
   m->v32.upload(v32);
   m->c32.upload(c32);
   m->cen.upload(cen);
+  m->rad.upload(rad);
+  m->test64.upload(test64);
+  m->test32.upload(test32);
   m->tri_xyz.upload(xyz9);
   m->tri_edge.upload(h.tri_edge);
   m->tri_sign.upload(h.tri_sign);
