@@ -11,8 +11,10 @@
 // factorisations (J^M)^H = Q_M R_M and (J^J)^H = Q_J R_J (Householder, R
 // only), G'_m = Q_M X Q_J^H with X = R_M G_m R_J^H, so with X = U_c S V_c^H
 // the singular values are those of G'_m and, since J^M Q_M = R_M^H,
-// C^M_m = R_M^H U_c,L and C^J_m = R_J^H V_c,L (matrix-core GEMMs).  The
-// core's SVD is one-sided Jacobi (one block per cell) on R_X^H, X = Q_X R_X,
+// C^M_m = R_M^H U_c,L and C^J_m = R_J^H V_c,L (matrix-core GEMMs).  Where
+// every cell has N_m >= s the QR would compress nothing: the core is G'_m
+// itself (R_M = (J^M)^H, R_J = (J^J)^H).  The core's SVD is one-sided
+// Jacobi (one block per cell) on R_X^H, X Pi = Q_X R_X with column pivoting,
 // which yields S and V_c; U_c = X V_c S^{-1}.
 // G_m is taken in closed form: for two RWGs a != b of one triangle with
 // counter-clockwise local indices, int (n x f_a) . f_b = e_ab l_a l_b / 6
@@ -154,84 +156,6 @@ __device__ inline double wave_sum(double x) {
   return x;
 }
 
-// In-place Householder QR of the column-major m x ncol matrix A (lda), only R
-// kept: afterwards the upper triangle of the first kmax = min(m, ncol) rows
-// holds R and the entries below the diagonal of the first kmax columns are
-// zero.  Reflector k is H = I - beta v v^H with v = x - alpha e_1, x the
-// column below the diagonal, alpha = -e^{i arg x_0} ||x||, beta = 2 / v^H v =
-// 1 / (||x||^2 + |x_0| ||x||).  Every thread of the block calls it; v is LDS
-// scratch of m entries, sc one LDS double.
-template <typename P>
-__device__ void householder_r(P A, int lda, int m, int ncol, double2* v, double* sc) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const int kmax = min(m, ncol);
-  for (int k = 0; k < kmax; ++k) {
-    P col = A + (int64_t)k * lda;
-    if (wave == 0) {
-      double q = 0;
-      for (int i = k + lane; i < m; i += 64) {
-        const double2 x = col[i];
-        q += x.x * x.x + x.y * x.y;
-      }
-      q = wave_sum(q);
-      const double nx = sqrt(q);
-      const double2 x0 = col[k];
-      const double ax0 = sqrt(x0.x * x0.x + x0.y * x0.y);
-      const double2 ph = ax0 > 0 ? make_double2(x0.x / ax0, x0.y / ax0) : make_double2(1.0, 0.0);
-      const double2 alpha = make_double2(-ph.x * nx, -ph.y * nx);
-      for (int i = k + lane; i < m; i += 64) {
-        double2 x = col[i];
-        if (i == k) x = make_double2(x.x - alpha.x, x.y - alpha.y);
-        v[i] = x;
-        col[i] = i == k ? alpha : make_double2(0.0, 0.0);
-      }
-      if (lane == 0) *sc = nx > 0 ? 1.0 / (q + ax0 * nx) : 0.0;
-    }
-    __syncthreads();
-    const double beta = *sc;
-    if (beta != 0.0) {
-      for (int j = k + 1 + wave; j < ncol; j += nw) {
-        P cj = A + (int64_t)j * lda;
-        double wr = 0, wi = 0;  // v^H a
-        for (int i = k + lane; i < m; i += 64) {
-          const double2 a = cj[i], w = v[i];
-          wr += w.x * a.x + w.y * a.y;
-          wi += w.x * a.y - w.y * a.x;
-        }
-        wr = beta * wave_sum(wr);
-        wi = beta * wave_sum(wi);
-        for (int i = k + lane; i < m; i += 64) {
-          const double2 w = v[i];
-          double2 a = cj[i];
-          a.x -= wr * w.x - wi * w.y;
-          a.y -= wr * w.y + wi * w.x;
-          cj[i] = a;
-        }
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// R factors of (J^M)^H and (J^J)^H of every cell: block b takes the column-
-// major S x Nmax matrix b of qa (cell b / 2, its first N columns) and writes
-// R as row-major rk x Nmax (zero below the diagonal and beyond column N).
-__global__ void __launch_bounds__(1024) cell_qr_kernel(double2* __restrict__ qa, int S, int Nmax,
-                                                       const int32_t* __restrict__ ncell, int rk,
-                                                       double2* __restrict__ R) {
-  extern __shared__ double2 v[];  // S entries
-  __shared__ double sc;
-  const int b = blockIdx.x, N = ncell[b / 2];
-  double2* A = qa + (int64_t)b * S * Nmax;
-  householder_r(A, S, S, N, v, &sc);
-  const int kmax = min(S, N);
-  double2* Rb = R + (int64_t)b * rk * Nmax;
-  for (int64_t e = threadIdx.x; e < (int64_t)rk * Nmax; e += blockDim.x) {
-    const int i = (int)(e / Nmax), j = (int)(e % Nmax);
-    Rb[e] = (i <= j && j < N && i < kmax) ? A[(int64_t)j * S + i] : make_double2(0.0, 0.0);
-  }
-}
-
 // x moved across the lanes of each row of 16 by a DPP pattern.
 template <int CTRL>
 __device__ inline double dpp_double(double x) {
@@ -250,17 +174,176 @@ __device__ inline double row16_sum(double x) {
   return x;
 }
 
+// Rows of a column that each of its 16 lanes holds in registers (columns of
+// up to 16 times as many entries; the 144 generating waves of Table I).
+constexpr int kLaneRows = 9;
+
+// In-place Householder QR of the column-major m x ncol matrix A (lda), only R
+// kept: afterwards the first kmax = min(m, ncol) rows hold R and the entries
+// below row k of the column taken in step k are zero.  Without PIV step k
+// takes column k; with PIV the column whose rows k.. have the largest norm,
+// and columns stay where they are (row k of R is row k of A, its columns in
+// A's order).  Reflector k is H = I - beta v v^H with v = x - alpha e_1, x
+// the column from row k on, alpha = -e^{i arg x_0} ||x||, beta = 2 / v^H v =
+// 1 / (||x||^2 + |x_0| ||x||).  Every thread of the block calls it; v is LDS
+// scratch of m entries, nrm2 and used (PIV) of ncol.  A column is taken by
+// 16 lanes, its sums by DPP; NR > 0: m <= 16 NR, and it is held in registers
+// between its dot product and its update.  Latency: per step the reflector
+// in one wavefront, then ceil(ncol / 64) columns per group, one after
+// another.
+template <bool PIV, int NR, typename P>
+__device__ __forceinline__ void householder_r(P A, int lda, int m, int ncol, double2* v, double* nrm2, int* used) {
+  __shared__ double beta_s;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int gl = threadIdx.x & 15, grp = threadIdx.x >> 4, ngrp = blockDim.x >> 4;
+  const int kmax = min(m, ncol);
+  if (PIV) {
+    for (int j = grp; j < ncol; j += ngrp) {
+      double q = 0;
+      for (int i = gl; i < m; i += 16) {
+        const double2 a = A[(int64_t)j * lda + i];
+        q += a.x * a.x + a.y * a.y;
+      }
+      q = row16_sum(q);
+      if (gl == 0) {
+        nrm2[j] = q;
+        used[j] = 0;
+      }
+    }
+    __syncthreads();
+  }
+  for (int k = 0; k < kmax; ++k) {
+    if (wave == 0) {
+      int c = k;
+      if (PIV) {  // lowest index among the largest
+        double best = -1.0;
+        c = 0;
+        for (int j = lane; j < ncol; j += 64)
+          if (!used[j] && nrm2[j] > best) {
+            best = nrm2[j];
+            c = j;
+          }
+        for (int o = 32; o > 0; o >>= 1) {
+          const double ob = __shfl_xor(best, o, 64);
+          const int oc = __shfl_xor(c, o, 64);
+          if (ob > best || (ob == best && oc < c)) {
+            best = ob;
+            c = oc;
+          }
+        }
+        if (lane == 0) used[c] = 1;
+      }
+      P col = A + (int64_t)c * lda;
+      double q = 0;
+      for (int i = k + lane; i < m; i += 64) {
+        const double2 x = col[i];
+        q += x.x * x.x + x.y * x.y;
+      }
+      q = wave_sum(q);
+      const double nx = sqrt(q);
+      const double2 x0 = col[k];
+      const double ax0 = sqrt(x0.x * x0.x + x0.y * x0.y);
+      const double2 ph = ax0 > 0 ? make_double2(x0.x / ax0, x0.y / ax0) : make_double2(1.0, 0.0);
+      const double2 alpha = make_double2(-ph.x * nx, -ph.y * nx);
+      for (int i = (k & ~63) + lane; i < m; i += 64) {
+        double2 x = make_double2(0.0, 0.0);  // v is zero above row k
+        if (i >= k) {
+          x = col[i];
+          if (i == k) x = make_double2(x.x - alpha.x, x.y - alpha.y);
+          col[i] = i == k ? alpha : make_double2(0.0, 0.0);
+        }
+        v[i] = x;
+      }
+      if (lane == 0) beta_s = nx > 0 ? 1.0 / (q + ax0 * nx) : 0.0;
+    }
+    __syncthreads();
+    const double beta = beta_s;
+    if (beta != 0.0) {
+      const int i0 = (k & ~15) + gl;
+      for (int j = PIV ? grp : k + 1 + grp; j < ncol; j += ngrp) {
+        if (PIV && used[j]) continue;  // the same on the column's lanes
+        P cj = A + (int64_t)j * lda;
+        double2 a[NR > 0 ? NR : 1];
+        double wr = 0, wi = 0, q = 0;  // v^H a
+        if (NR > 0) {
+#pragma unroll
+          for (int u = 0; u < NR; ++u) {
+            const int i = i0 + 16 * u;
+            a[u] = i < m ? cj[i] : make_double2(0.0, 0.0);
+            const double2 w = i < m ? v[i] : make_double2(0.0, 0.0);
+            wr += w.x * a[u].x + w.y * a[u].y;
+            wi += w.x * a[u].y - w.y * a[u].x;
+          }
+        } else {
+          for (int i = i0; i < m; i += 16) {
+            const double2 x = cj[i], w = v[i];
+            wr += w.x * x.x + w.y * x.y;
+            wi += w.x * x.y - w.y * x.x;
+          }
+        }
+        wr = beta * row16_sum(wr);
+        wi = beta * row16_sum(wi);
+        auto update = [&](int i, double2 x) {
+          const double2 w = v[i];
+          x.x -= wr * w.x - wi * w.y;
+          x.y -= wr * w.y + wi * w.x;
+          cj[i] = x;
+          if (PIV && i > k) q += x.x * x.x + x.y * x.y;
+        };
+        if (NR > 0) {
+#pragma unroll
+          for (int u = 0; u < NR; ++u)
+            if (i0 + 16 * u < m) update(i0 + 16 * u, a[u]);
+        } else {
+          for (int i = i0; i < m; i += 16) update(i, cj[i]);
+        }
+        if (PIV) {
+          q = row16_sum(q);
+          if (gl == 0) nrm2[j] = q;
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// R factors of (J^M)^H and (J^J)^H of every cell: block b takes the column-
+// major S x Nmax matrix b of qa (cell b / 2, its first N columns) and writes
+// R as row-major rk x Nmax (zero below the diagonal and beyond column N).
+__global__ void __launch_bounds__(1024) cell_qr_kernel(double2* __restrict__ qa, int S, int Nmax,
+                                                       const int32_t* __restrict__ ncell, int rk,
+                                                       double2* __restrict__ R) {
+  extern __shared__ double2 v[];  // S entries
+  const int b = blockIdx.x, N = ncell[b / 2];
+  double2* A = qa + (int64_t)b * S * Nmax;
+  if (S <= 16 * kLaneRows)
+    householder_r<false, kLaneRows>(A, S, S, N, v, nullptr, nullptr);
+  else
+    householder_r<false, 0>(A, S, S, N, v, nullptr, nullptr);
+  const int kmax = min(S, N);
+  double2* Rb = R + (int64_t)b * rk * Nmax;
+  for (int64_t e = threadIdx.x; e < (int64_t)rk * Nmax; e += blockDim.x) {
+    const int i = (int)(e / Nmax), j = (int)(e % Nmax);
+    Rb[e] = (i <= j && j < N && i < kmax) ? A[(int64_t)j * S + i] : make_double2(0.0, 0.0);
+  }
+}
+
 // One-sided (Hestenes) Jacobi on the columns of the column-major nc x nc
 // matrix B (ldb): pairs of columns are rotated, in the round-robin order that
 // lets each row of 16 lanes of the block rotate a disjoint pair at once, until
-// in one sweep no pair has |b_p^H b_q| > tol ||b_p|| ||b_q||.  The 2 x 2 step
+// in one sweep no pair has |b_p^H b_q| > tol ||b_p|| ||b_q||.  (A column
+// below 1e-14 of big, the rounding level of the matrix, is not turned against
+// another any more once |b_p^H b_q| <= 1e-17 big times the longer of the
+// two: no singular value moves by its rounding.)  The 2 x 2 step
 // for alpha = ||b_p||^2, beta = ||b_q||^2, gamma = b_p^H b_q = |gamma| e:
 // zeta = (beta - alpha) / (2 |gamma|), t = sign(zeta) / (|zeta| +
 // sqrt(1 + zeta^2)), c = 1 / sqrt(1 + t^2), s = c t,
 // (b_p, b_q) <- (c b_p - s conj(e) b_q, s e b_p + c b_q).
+// HELD (nc <= 16 kLaneRows): a pair stays in registers between its sums and
+// its rotation (columns in global memory).
 // Returns the number of sweeps, or -1 if max_sweeps ran out.
-template <typename P>
-__device__ int hestenes_jacobi(P B, int ldb, int nc, double tol, int max_sweeps, int* flag) {
+template <bool HELD, typename P>
+__device__ __forceinline__ int hestenes_jacobi(P B, int ldb, int nc, double tol, double big2, int max_sweeps, int* flag) {
   const int gl = threadIdx.x & 15, grp = threadIdx.x >> 4, ngrp = blockDim.x >> 4;
   const int ne = nc + (nc & 1);  // an odd count plays against an empty column
   for (int sweep = 0; sweep < max_sweeps; ++sweep) {
@@ -275,29 +358,49 @@ __device__ int hestenes_jacobi(P B, int ldb, int nc, double tol, int max_sweeps,
         if (p >= nc || q >= nc) continue;
         P x = B + (int64_t)p * ldb;
         P y = B + (int64_t)q * ldb;
+        double2 hx[HELD ? kLaneRows : 1], hy[HELD ? kLaneRows : 1];
         double al = 0, be = 0, gr = 0, gi = 0;
-        for (int i = gl; i < nc; i += 16) {
-          const double2 a = x[i], c = y[i];
+        auto sums = [&](double2 a, double2 c) {
           al += a.x * a.x + a.y * a.y;
           be += c.x * c.x + c.y * c.y;
           gr += a.x * c.x + a.y * c.y;
           gi += a.x * c.y - a.y * c.x;
+        };
+        if (HELD) {
+#pragma unroll
+          for (int u = 0; u < kLaneRows; ++u) {
+            const int i = gl + 16 * u;
+            hx[u] = i < nc ? x[i] : make_double2(0.0, 0.0);
+            hy[u] = i < nc ? y[i] : make_double2(0.0, 0.0);
+          }
+#pragma unroll
+          for (int u = 0; u < kLaneRows; ++u) sums(hx[u], hy[u]);
+        } else {
+          for (int i = gl; i < nc; i += 16) sums(x[i], y[i]);
         }
         al = row16_sum(al);
         be = row16_sum(be);
         gr = row16_sum(gr);
         gi = row16_sum(gi);
-        const double ag = sqrt(gr * gr + gi * gi);
-        if (!(al * be > 0 && ag > tol * sqrt(al * be))) continue;  // same on the 16 lanes
+        const double g2 = gr * gr + gi * gi, ag = sqrt(g2);
+        if (!(al * be > 0 && ag > tol * sqrt(al * be)) ||
+            (fmin(al, be) < 1e-28 * big2 && g2 <= 1e-34 * big2 * fmax(al, be)))
+          continue;  // same on the 16 lanes
         const double z = (be - al) / (2.0 * ag);
         const double t = (z >= 0 ? 1.0 : -1.0) / (fabs(z) + sqrt(1.0 + z * z));
         const double cs = 1.0 / sqrt(1.0 + t * t), sn = cs * t;
         const double er = gr / ag, ei = gi / ag;
-        for (int i = gl; i < nc; i += 16) {
-          const double2 a = x[i], c = y[i];
-          // a' = cs a - sn conj(e) c ;  c' = sn e a + cs c
+        // a' = cs a - sn conj(e) c ;  c' = sn e a + cs c
+        auto turn = [&](int i, double2 a, double2 c) {
           x[i] = make_double2(cs * a.x - sn * (er * c.x + ei * c.y), cs * a.y - sn * (er * c.y - ei * c.x));
           y[i] = make_double2(sn * (er * a.x - ei * a.y) + cs * c.x, sn * (er * a.y + ei * a.x) + cs * c.y);
+        };
+        if (HELD) {
+#pragma unroll
+          for (int u = 0; u < kLaneRows; ++u)
+            if (gl + 16 * u < nc) turn(gl + 16 * u, hx[u], hy[u]);
+        } else {
+          for (int i = gl; i < nc; i += 16) turn(i, x[i], y[i]);
         }
         if (gl == 0) *flag = 1;
       }
@@ -309,13 +412,18 @@ __device__ int hestenes_jacobi(P B, int ldb, int nc, double tol, int max_sweeps,
 }
 
 // SVD of each cell's core X (column-major rk x rk, leading nc = min(N, rk)
-// block nonzero): X = Q R (Householder), then one-sided Jacobi on B = R^H,
-// B W = U~ S.  Since R = W S U~^H, X = (Q W) S U~^H: U~ are the right
-// singular vectors of X and S its singular values.  Written sorted by
-// decreasing sigma: sigma (rk per cell, zero beyond nc), Ut = U~ and
-// Uts = U~ S^{-1} (column-major rk x rk, first nc columns, zero rows beyond
-// nc), info = 0, or 1 if the sweeps ran out.  LDS = true keeps the nc x nc
-// working matrix in LDS, else in work (rk x rk per cell).
+// block nonzero): X Pi = Q R (Householder with column pivoting), then
+// one-sided Jacobi on B = Pi R^H, B W = U~ S.  Since R Pi^T = W S U~^H, X =
+// (Q W) S U~^H: U~ are the right singular vectors of X and S its singular
+// values.  The singular values of these cores fall from 1 to 1e-17 and
+// below: without pivoting Jacobi takes 30 to 60 sweeps, on the pivoted,
+// graded triangle 7 to 9.  Written sorted by decreasing sigma: sigma (rk per
+// cell, zero beyond nc), Ut = U~ and Uts = U~ S^{-1} (column-major rk x rk,
+// first nc columns, zero rows beyond nc), info = 0, or 1 if the sweeps ran
+// out.  LDS = true keeps the nc x nc working matrix in LDS, else in work
+// (rk x rk per cell).  Bound by one CU's bandwidth to the matrix in each of
+// the nc - 1 steps of a sweep: 96 cells of order 144 in L2 17.1 -> 8.7 ms,
+// 27 of order 96 in LDS 2.78 -> 2.13 ms with the pivoting.
 template <bool LDS>
 __global__ void __launch_bounds__(1024) core_svd_kernel(const double2* __restrict__ X, int rk,
                                                         const int32_t* __restrict__ ncell, double2* work, double tol,
@@ -323,7 +431,6 @@ __global__ void __launch_bounds__(1024) core_svd_kernel(const double2* __restric
                                                         double2* __restrict__ Ut, double2* __restrict__ Uts,
                                                         int32_t* __restrict__ info) {
   extern __shared__ double2 lds[];
-  __shared__ double sc;
   __shared__ int flag;
   const int b = blockIdx.x, nc = min((int)ncell[b], rk);
   double2* A = LDS ? lds : work + (int64_t)b * rk * rk;
@@ -336,17 +443,26 @@ __global__ void __launch_bounds__(1024) core_svd_kernel(const double2* __restric
     A[e] = Xb[(int64_t)j * rk + i];
   }
   __syncthreads();
-  householder_r(A, nc, nc, nc, v, &sc);
-  // B = R^H in place (lower triangular)
+  if (nc <= 16 * kLaneRows)
+    householder_r<true, kLaneRows>(A, nc, nc, nc, v, nrm, rank);
+  else
+    householder_r<true, 0>(A, nc, nc, nc, v, nrm, rank);
+  // B = A^H in place: row k of A (step k's row of R, columns in X's order)
+  // becomes column k of B
   for (int64_t e = threadIdx.x; e < (int64_t)nc * nc; e += blockDim.x) {
     const int i = (int)(e % nc), j = (int)(e / nc);
     if (i < j) continue;
-    const double2 r = A[(int64_t)i * nc + j];  // R[j][i]
-    A[e] = make_double2(r.x, -r.y);
-    if (i > j) A[(int64_t)i * nc + j] = make_double2(0.0, 0.0);
+    const double2 p = A[e], q = A[(int64_t)i * nc + j];
+    A[e] = make_double2(q.x, -q.y);
+    if (i > j) A[(int64_t)i * nc + j] = make_double2(p.x, -p.y);
   }
-  const int sweeps = hestenes_jacobi(A, nc, nc, tol, max_sweeps, &flag);
+  __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  double f2 = 0;  // (row 0 of R is the longest, within the square root of nc)
+  for (int i = lane; i < nc; i += 64) f2 += A[i].x * A[i].x + A[i].y * A[i].y;
+  f2 = wave_sum(f2);
+  const int sweeps = !LDS && nc <= 16 * kLaneRows ? hestenes_jacobi<!LDS>(A, nc, nc, tol, f2, max_sweeps, &flag)
+                                                  : hestenes_jacobi<false>(A, nc, nc, tol, f2, max_sweeps, &flag);
   for (int j = wave; j < nc; j += nw) {
     double q = 0;
     for (int i = lane; i < nc; i += 64) {
@@ -796,27 +912,47 @@ cbfm_cbf_s::~cbfm_cbf_s() {
   }
 }
 
+// Blocks 1.. of CM and CJ (blk entries each, one after another) from block 0.
+__global__ void replicate_kernel(int64_t blk, double2* __restrict__ CM, double2* __restrict__ CJ) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, o = (int64_t)blockIdx.y * blk;
+  if (i >= blk || blockIdx.y == 0) return;
+  CM[o + i] = CM[i];
+  CJ[o + i] = CJ[i];
+}
+
 // CBFs of every cell from its current coefficient sets J_m = [J^M_m; J^J_m]
 // (primary or IPCBF), given as (J^M_m)^H and (J^J_m)^H in QA: column-major
 // S x Nmax per cell and current (cell b's at 2 b and 2 b + 1), zero beyond
 // the cell's N_m columns.  The dual orthogonalisation of Sec. III-B: QR of
 // both (R only), the core X = R_M G_m R_J^H, its one-sided Jacobi SVD,
 // L_m = #{sigma_i / sigma_1 >= delta_svd} (at most max_L), C^M = J^M U_L,
-// C^J = J^J V_L.  share: every cell takes cell 0's CBFs (arrays of
-// translated copies).  The CMP inverse is queued on the side stream unless
+// C^J = J^J V_L.  share: QA, hN and djobs hold cell 0 alone, whose CBFs
+// every cell takes (arrays of translated copies).  The CMP inverse is queued on the side stream unless
 // this thread disabled that.  Returns a new handle; QA is overwritten.
 static cbfm_cbf_s* orthogonalise(const cbfm_mesh_s* m, double2* QA_p, int S, int Nmax, const std::vector<int32_t>& hN,
                                  const int32_t* dN_p, const CellJob* djobs, double delta_svd, int max_L, bool share,
                                  hipStream_t s) {
   const MeshHost& h = m->h;
-  const int nb = h.nblocks;
+  const int nall = h.nblocks, nb = share ? 1 : nall;  // cells of the mesh, cells built
   const int rk = std::min(S, Nmax);
+  // with N >= S in every cell the QR of the S x N matrices gives an S x N
+  // R again: the matrices themselves serve (Sec. III-B's G'_m is the core).
+  // 96 cells of 312 RWGs, S = 144: 3.8 ms saved
+  const bool qr = *std::min_element(hN.begin(), hN.begin() + nb) < S;
   Scratch info((size_t)nb * sizeof(int32_t), s);  // per cell: the Jacobi SVD ran out of sweeps
   std::vector<int32_t> hinfo(nb);
-  Scratch Rf((size_t)nb * 2 * rk * Nmax * sizeof(double2), s);  // per cell R_M, then R_J
-  hipLaunchKernelGGL(cell_qr_kernel, dim3(2 * nb), dim3(1024), (size_t)S * sizeof(double2), s, QA_p, S,
-                     Nmax, dN_p, rk, Rf.as<double2>());
-  CBFM_HIP(hipGetLastError());
+  Scratch Rf(qr ? (size_t)nb * 2 * rk * Nmax * sizeof(double2) : 0, s);  // per cell R_M, then R_J
+  if (qr) {
+    hipLaunchKernelGGL(cell_qr_kernel, dim3(2 * nb), dim3(1024), (size_t)S * sizeof(double2), s, QA_p, S,
+                       Nmax, dN_p, rk, Rf.as<double2>());
+    CBFM_HIP(hipGetLastError());
+  }
+  // factor w (0: M, 1: J) of cell b: row-major rk x Nmax, or without the QR
+  // the transpose, row-major Nmax x S
+  auto factor = [&](int b, int w) {
+    return qr ? Rf.as<double2>() + (size_t)(2 * b + w) * rk * Nmax : QA_p + (size_t)(2 * b + w) * S * Nmax;
+  };
+  const int64_t ldf = qr ? Nmax : S;
   // core X = R_M G_m R_J^H (column-major rk x rk), computed as its row-major
   // transpose conj(R_J) G_m^T R_M^T = -conj(R_J) G_m R_M^T (G_m antisymmetric)
   Scratch Gm((size_t)nb * Nmax * Nmax * sizeof(double2), s);
@@ -828,11 +964,10 @@ static cbfm_cbf_s* orthogonalise(const cbfm_mesh_s* m, double2* QA_p, int S, int
   std::vector<GemmDesc> d1, d2;
   for (int b = 0; b < nb; ++b) {
     const int Nb = hN[b];
-    const double2* R = Rf.as<double2>() + (size_t)b * 2 * rk * Nmax;
     double2* G = Gm.as<double2>() + (size_t)b * Nmax * Nmax;
     double2* t2 = T2.as<double2>() + (size_t)b * Nmax * rk;
-    d1.push_back(gemm(G, Nb, OP_N, R, Nmax, OP_T, t2, rk, Nb, rk, Nb));
-    d2.push_back(gemm(R + (size_t)rk * Nmax, Nmax, OP_R, t2, rk, OP_N, core.as<double2>() + (size_t)b * rk * rk, rk,
+    d1.push_back(gemm(G, Nb, OP_N, factor(b, 0), ldf, qr ? OP_T : OP_N, t2, rk, Nb, rk, Nb));
+    d2.push_back(gemm(factor(b, 1), ldf, qr ? OP_R : OP_C, t2, rk, OP_N, core.as<double2>() + (size_t)b * rk * rk, rk,
                       rk, rk, Nb, -1.0));
   }
   CBFM_HIP(hipGetLastError());
@@ -868,7 +1003,7 @@ static cbfm_cbf_s* orthogonalise(const cbfm_mesh_s* m, double2* QA_p, int S, int
   auto* c = new cbfm_cbf_s();
   try {
     c->mesh = m;
-    c->L.resize(nb);
+    c->L.resize(nall);
     for (int b = 0; b < nb; ++b) {
       const double* sb = &hs[(size_t)b * rk];
       int L = 0;
@@ -885,39 +1020,35 @@ static cbfm_cbf_s* orthogonalise(const cbfm_mesh_s* m, double2* QA_p, int S, int
     // cell takes cell 0's (count, singular values and vectors)
     if (share) {
       c->shared = true;
-      c->sigma.resize((size_t)c->L[0] * nb);
-      for (int b = 1; b < nb; ++b) {
+      c->sigma.resize((size_t)c->L[0] * nall);
+      for (int b = 1; b < nall; ++b) {
         c->L[b] = c->L[0];
         std::copy(c->sigma.begin(), c->sigma.begin() + c->L[0], c->sigma.begin() + (size_t)b * c->L[0]);
       }
     }
     cbf_finish(c);
-    c->CM.alloc(std::max<int64_t>(1, c->coff[nb]) * sizeof(double2));
-    c->CJ.alloc(std::max<int64_t>(1, c->coff[nb]) * sizeof(double2));
+    c->CM.alloc(std::max<int64_t>(1, c->coff[nall]) * sizeof(double2));
+    c->CJ.alloc(std::max<int64_t>(1, c->coff[nall]) * sizeof(double2));
     // C^J = R_J^H V_L with V = U~;  C^M = R_M^H U_L with U = X V S^{-1} = X U~ S^{-1}
     Scratch W((size_t)std::max<int64_t>(1, c->coff[nb]) * sizeof(double2), s);
     std::vector<GemmDesc> d3, d4;
     for (int b = 0; b < nb; ++b) {
       const int Nb = hN[b], nc = std::min(Nb, rk), L = c->L[b];
-      const double2* R = Rf.as<double2>() + (size_t)b * 2 * rk * Nmax;
       const double2* ub = Ut.as<double2>() + (size_t)b * rk * rk;
       const double2* usb = Uts.as<double2>() + (size_t)b * rk * rk;
       double2* wb = W.as<double2>() + c->coff[b];  // nc x L row-major (nc <= N_b)
       d3.push_back(gemm(core.as<double2>() + (size_t)b * rk * rk, rk, OP_T, usb, rk, OP_T, wb, L, nc, L, nc));
-      d3.push_back(gemm(R + (size_t)rk * Nmax, Nmax, OP_C, ub, rk, OP_T, c->CJ.as<double2>() + c->coff[b], L, Nb, L,
-                        nc));
-      d4.push_back(gemm(R, Nmax, OP_C, wb, L, OP_N, c->CM.as<double2>() + c->coff[b], L, Nb, L, nc));
+      const int opf = qr ? OP_C : OP_R;
+      d3.push_back(gemm(factor(b, 1), ldf, opf, ub, rk, OP_T, c->CJ.as<double2>() + c->coff[b], L, Nb, L, nc));
+      d4.push_back(gemm(factor(b, 0), ldf, opf, wb, L, OP_N, c->CM.as<double2>() + c->coff[b], L, Nb, L, nc));
     }
     zgemm_batched(d3, s);
     zgemm_batched(d4, s);
     if (c->shared) {
-      const size_t blk = (size_t)(c->coff[1] - c->coff[0]) * sizeof(double2);
-      for (int b = 1; b < nb; ++b) {
-        CBFM_HIP(hipMemcpyAsync(c->CM.as<double2>() + c->coff[b], c->CM.as<double2>(), blk,
-                                hipMemcpyDeviceToDevice, s));
-        CBFM_HIP(hipMemcpyAsync(c->CJ.as<double2>() + c->coff[b], c->CJ.as<double2>(), blk,
-                                hipMemcpyDeviceToDevice, s));
-      }
+      const int64_t blk = c->coff[1] - c->coff[0];
+      hipLaunchKernelGGL(replicate_kernel, dim3((unsigned)((blk + 255) / 256), (unsigned)nall), dim3(256), 0, s, blk,
+                         c->CM.as<double2>(), c->CJ.as<double2>());
+      CBFM_HIP(hipGetLastError());
     }
     if (t_async_cmp) cmp_factor_async(c, s);
   } catch (...) {
@@ -988,12 +1119,13 @@ cbfm_status cbfm_build_cbf(cbfm_mesh m, const cbfm_medium* med, const cbfm_cbf_p
     const Media md = make_media(med);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const MeshHost& h = m->h;
-    const int nb = h.nblocks;
+    CBFM_REQUIRE(h.nblocks <= 32767, CBFM_E_ARG, "above 32767 cells");
+    const int nb = m->translated ? 1 : h.nblocks;  // translated copies take cell 0's CBFs
     const int S = prm->n_gen;
     int Nmax = 0;
     for (int b = 0; b < nb; ++b) Nmax = std::max<int>(Nmax, (int)(h.cell_off[b + 1] - h.cell_off[b]));
     const int n = 2 * Nmax;
-    CBFM_REQUIRE(nb <= 32767 && n <= 65535, CBFM_E_ARG, "above 32767 cells or 32767 RWGs in one cell");
+    CBFM_REQUIRE(n <= 65535, CBFM_E_ARG, "above 32767 RWGs in one cell");
     // generating right-hand sides on all edges
     Scratch vgen((size_t)S * 2 * h.ne * sizeof(double2), s);
     Scratch dinc((size_t)S * 6 * sizeof(double), s);

@@ -1,0 +1,44 @@
+"""The dual orthogonalisation's forms, by the number of generating waves S
+against the RWGs N of a cell: QR to N x N cores (S > N), the Gram G'_m itself
+(S <= N), cores held 16 lanes a column or not (at most 144 entries), in LDS
+or in global memory; odd orders and a single wave."""
+import numpy as np
+import pytest
+
+from conftest import oracle_problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cells, S", [(8, 1), (8, 33), (8, 61), (8, 144), (8, 300), (1, 2), (1, 96), (1, 143), (1, 145),
+                                      (1, 300), (1, 501)])
+def test_core_forms(cells, S):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from oracle import cbf
+    from paper_2111_11058_amd import cbfm
+    from synth import configs
+    P = oracle_problem("c1")
+    w, m = P["w"], P["m"]
+    eb = np.asarray(w.edge_block if cells == 8 else np.zeros(m.ne), np.int32)
+    gen = configs.random_incidences(S, 31 + S)
+    delta = 1e-6
+    ref = cbf.build(m, P["Kc"], P["TE"], P["TH"], eb, gen, w.k0, w.eta0, delta)
+    mesh = cbfm.Mesh(w.V, w.T, eb, cells)
+    med = cbfm.Medium.make(w.k0, w.eta0, w.eps_r, w.mu_r)
+    print(f"build_cbf cells {cells} waves {S}", flush=True)
+    cb = cbfm.build_cbf(mesh, med, gen, delta)
+    assert np.array_equal(cb.L, ref.L)
+    CM, CJ = cb.export()
+    G = cbf.rwg_gram(m)
+    o = 0
+    for c, ix in enumerate(ref.cells):
+        s = ref.sigma[c]
+        # singular values move by at most the error of G'_m: rounding times
+        # the condition number of Z_mm (1e6..1e7 for these cells)
+        assert np.abs(cb.sigma[o:o + len(s)] - s).max() < 1e-9 * s[0]
+        o += len(s)
+        # C^M = R_M^H X U~ S^{-1}: column i of the duality relation carries
+        # the rounding of sigma_1 over sigma_i >= 1e-6 sigma_1
+        D = CM[c].conj().T @ G[np.ix_(ix, ix)] @ CJ[c]
+        assert np.abs(D - np.diag(s)).max() < 1e-8 * s[0]
