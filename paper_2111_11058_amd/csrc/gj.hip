@@ -50,20 +50,39 @@ __device__ inline double gj_cabs1(double2 z) { return fabs(z.x) + fabs(z.y); }
 __device__ inline double2 gj_mul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
+// 1 / p: the hardware reciprocal of |p|^2 and two Newton steps (a quarter of
+// a division's latency, which sits on every step's critical path), away from
+// the ends of the range where |p|^2 or its reciprocal is subnormal.
 __device__ inline double2 gj_recip(double2 p) {
   const double d = p.x * p.x + p.y * p.y;
-  return make_double2(p.x / d, -p.y / d);
+  if (!(d > 1e-290 && d < 1e290)) return make_double2(p.x / d, -p.y / d);
+  double y = __builtin_amdgcn_rcp(d);
+  y = fma(fma(-d, y, 1.0), y, y);
+  y = fma(fma(-d, y, 1.0), y, y);
+  return make_double2(p.x * y, -p.y * y);
 }
 // Pivot key of a row: |re| + |im| rounded to float (a positive value stays
-// positive) in the high word, the complement of the thread in the low word,
-// so that the largest key is the largest entry and, among equals, the lowest
-// thread; 0 for a thread without a candidate row.
-__device__ inline uint64_t gj_key(bool alive, double2 z, int t) {
-  if (!alive) return 0;
+// positive) above 1; 1 for a zero (or NaN) entry, 0 for a thread without a
+// candidate row.
+__device__ inline uint32_t gj_key(bool alive, double2 z) {
   const double m = gj_cabs1(z);
-  uint32_t hi = 0;
-  if (m > 0.0) hi = __float_as_uint((float)m) | 1u;  // (NaN counts as zero)
-  return ((uint64_t)hi << 32) | (uint32_t)~t;
+  return !alive ? 0u : m > 0.0 ? (__float_as_uint((float)m) | 1u) + 1u : 1u;
+}
+template <int CTRL>
+__device__ inline uint32_t gj_dpp_max(uint32_t x) {
+  const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
+  return y > x ? y : x;
+}
+// The largest value over the wavefront (uniform).
+__device__ inline uint32_t gj_wave_max(uint32_t x) {
+  x = gj_dpp_max<0xB1>(x);   // within rows of 16 lanes
+  x = gj_dpp_max<0x4E>(x);
+  x = gj_dpp_max<0x141>(x);
+  x = gj_dpp_max<0x140>(x);
+  const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 0), r1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 16),
+                 r2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 32), r3 = (uint32_t)__builtin_amdgcn_readlane((int)x, 48);
+  const uint32_t a = r0 > r1 ? r0 : r1, b = r2 > r3 ? r2 : r3;
+  return a > b ? a : b;
 }
 
 struct SelectArgs {
@@ -124,96 +143,125 @@ __global__ void __launch_bounds__(kGroup) gj_select_kernel(SelectArgs p) {
         if (j < w) Pc[(int64_t)row * kW + j] = a[j];
     }
   }
-  __shared__ uint64_t s_key[kGroup / 64];
-  __shared__ double2 s_prow[kW];
+  // LU with partial pivoting over the group's rows; column c picks row
+  // s_sel[c].  Bound by the latency of its 32 steps (62 % of wave cycles wait,
+  // on LDS and barriers): the argmax by DPP and scalar maxima, the winner's
+  // row alone written to LDS (one lane's 16-byte stores cost as much as a
+  // full wavefront's), wavefronts whose rows are all chosen skip the update.
+  // Eight columns are unrolled and the registers move down by eight between
+  // blocks: 27 KB of code instead of 105.  Per launch 75 -> 41 (first round),
+  // 47 us (last round, with D^{-1}).
+  constexpr int kWaves = kGroup / 64, kB = 8;
+  __shared__ uint32_t s_key[2][kWaves];
+  __shared__ double2 s_prow[2][kW];
   __shared__ int s_sel[kW];
   bool alive = row >= 0;
   int nsel = 0;
+  bool open = true;  // uniform: false from the first column with no row left
   const int lane = t & 63, wave = t >> 6;
-  // LU with partial pivoting over the group's rows; column c picks row s_sel[c]
+#pragma unroll 1
+  for (int c0 = 0; c0 < kW; c0 += kB) {
+    // a[j] holds column c0 + j; live: columns of a still in the panel
+    const int live = kW - c0;
 #pragma unroll
-  for (int c = 0; c < kW; ++c) {
-    if (c < w && nsel == c) {  // (uniform: stops at the first column with no row left)
-      uint64_t key = gj_key(alive, a[c], t);
-      for (int off = 32; off > 0; off >>= 1) {
-        const uint64_t o = __shfl_xor(key, off, 64);
-        key = o > key ? o : key;
-      }
-      if (lane == 0) s_key[wave] = key;
+    for (int c = 0; c < kB; ++c) {
+      const int buf = c & 1;
+      const uint32_t key = gj_key(alive, a[c]), top = gj_wave_max(key);
+      const bool mine = lane == __builtin_ctzll(__ballot(key == top));
+      if (lane == 0) s_key[buf][wave] = top;
       __syncthreads();
-      uint64_t best = s_key[0];
-      for (int q = 1; q < kGroup / 64; ++q) best = s_key[q] > best ? s_key[q] : best;
-      const int bw = (int)~(uint32_t)best;
-      const bool nonzero = (best >> 32) != 0;
-      if (best != 0) {
-        if (t == bw) {
+      int bw = 0;
+      uint32_t best = s_key[buf][0];
 #pragma unroll
-          for (int j = c; j < kW; ++j) s_prow[j] = a[j];
-          s_sel[c] = row;
-          alive = false;
+      for (int q = 1; q < kWaves; ++q)
+        if (s_key[buf][q] > best) {
+          best = s_key[buf][q];
+          bw = q;
         }
-        __syncthreads();
-        nsel = c + 1;
-        if (nonzero) {
-          if (alive) {
-            const double2 l = gj_mul(a[c], gj_recip(s_prow[c]));
+      if (mine && wave == bw) {
+        double2* pr = s_prow[buf];
 #pragma unroll
-            for (int j = c + 1; j < kW; ++j) {
-              const double2 x = s_prow[j];
-              a[j].x -= l.x * x.x - l.y * x.y;
-              a[j].y -= l.x * x.y + l.y * x.x;
-            }
-          }
-        } else if (p.final_round && t == 0 && p.info[b] == 0) {
-          p.info[b] = k + c + 1;
-        }
+        for (int j = c; j < kB; ++j) pr[j] = a[j];
+#pragma unroll
+        for (int g8 = kB; g8 < kW; g8 += kB)
+          if (g8 < live)
+#pragma unroll
+            for (int j = g8; j < g8 + kB; ++j) pr[j] = a[j];
       }
+      __syncthreads();
+      open = open && best != 0 && c0 + c < w;
+      if (open) {
+        nsel = c0 + c + 1;
+        if (mine && wave == bw) {
+          alive = false;
+          s_sel[c0 + c] = row;
+        }
+        if (best == 1 && p.final_round && t == 0 && p.info[b] == 0) p.info[b] = k + c0 + c + 1;
+      }
+      const double2* pr = s_prow[buf];
+      double2 l = gj_mul(a[c], gj_recip(pr[c]));
+      const bool upd = open && alive && best > 1;
+      if (!upd) l = make_double2(0.0, 0.0);
+      if (!__any(upd)) continue;  // no row of this wavefront takes part any more
+      auto sub = [&](int j) {
+        const double2 x = pr[j];
+        a[j].x = fma(l.y, x.y, fma(-l.x, x.x, a[j].x));
+        a[j].y = fma(-l.y, x.x, fma(-l.x, x.y, a[j].y));
+      };
+#pragma unroll
+      for (int j = c + 1; j < kB; ++j) sub(j);
+#pragma unroll
+      for (int g8 = kB; g8 < kW; g8 += kB)
+        if (g8 < live)
+#pragma unroll
+          for (int j = g8; j < g8 + kB; ++j) sub(j);
     }
+#pragma unroll
+    for (int j = 0; j < kW - kB; ++j) a[j] = a[j + kB];
   }
+  __syncthreads();
   if (!p.final_round) {
     if (t < kW) p.cand_out[(int64_t)b * p.cand_stride + (int64_t)g * kW + t] = t < nsel ? s_sel[t] : -1;
     return;
   }
   if (nsel < w && t == 0 && p.info[b] == 0) p.info[b] = k + nsel + 1;
-  // D (the pivot rows' panel entries, identity-padded) and I, then
-  // Gauss-Jordan without further interchanges: [D | I] -> [I | D^{-1}]
-  __shared__ double2 s_m[kW][2 * kW + 1];
-  for (int e = t; e < kW * 2 * kW; e += kGroup) {
-    const int i = e / (2 * kW), j = e % (2 * kW);
-    double2 v = make_double2(0.0, 0.0);
-    if (j < kW) {
-      if (i < nsel && j < w)
-        v = Ab[(int64_t)s_sel[i] * p.ld + k + j];
-      else if (i == j && i >= w)
-        v = make_double2(1.0, 0.0);
-    } else if (j - kW == i) {
-      v = make_double2(1.0, 0.0);
-    }
-    s_m[i][j] = v;
+  // D (the pivot rows' panel entries, identity-padded) to D^{-1} by
+  // Gauss-Jordan in place without further interchanges, in registers: this
+  // thread holds row mi, columns mq + 8 u.  Step c's row and column pass
+  // through LDS (two buffers: one barrier a step).
+  __shared__ double2 s_r[2][kW], s_f[2][kW];
+  const int mi = t >> 3, mq = t & 7;
+  double2 m[kW / 8];
+#pragma unroll
+  for (int u = 0; u < kW / 8; ++u) {
+    const int j = mq + 8 * u;
+    m[u] = mi < nsel && j < w ? Ab[(int64_t)s_sel[mi] * p.ld + k + j] : make_double2(mi == j && mi >= w ? 1.0 : 0.0, 0.0);
   }
-  const int mi = t >> 3, mq = t & 7;  // this thread: row mi, columns mq + 8 u
-  for (int c = 0; c < kW; ++c) {
-    __syncthreads();
-    const double2 rp = gj_recip(s_m[c][c]);
-    const double2 f = s_m[mi][c];
-    double2 x[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) x[u] = gj_mul(s_m[c][mq + 8 * u], rp);
-    __syncthreads();
+  for (int cu = 0; cu < kW / 8; ++cu) {
+#pragma unroll 1
+    for (int cq = 0; cq < 8; ++cq) {
+      const int c = cq + 8 * cu;
+      double2* r = s_r[cq & 1];
+      double2* f = s_f[cq & 1];
+      if (mi == c)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      double2& y = s_m[mi][mq + 8 * u];
-      if (mi == c) {
-        y = x[u];
-      } else {
-        y.x -= f.x * x[u].x - f.y * x[u].y;
-        y.y -= f.x * x[u].y + f.y * x[u].x;
+        for (int u = 0; u < kW / 8; ++u) r[mq + 8 * u] = m[u];
+      if (mq == cq) f[mi] = m[cu];
+      __syncthreads();
+      const double2 rp = gj_recip(r[c]), fm = f[mi];
+#pragma unroll
+      for (int u = 0; u < kW / 8; ++u) {
+        const bool diag = u == cu && mq == cq;
+        const double2 x = diag ? rp : gj_mul(r[mq + 8 * u], rp);
+        const double2 y = diag ? make_double2(0.0, 0.0) : m[u];
+        m[u] = mi == c ? x : make_double2(y.x - (fm.x * x.x - fm.y * x.y), y.y - (fm.x * x.y + fm.y * x.x));
       }
     }
   }
-  __syncthreads();
   double2* Db = p.Dinv + (int64_t)b * kW * kW;
-  for (int e = t; e < kW * kW; e += kGroup) Db[e] = s_m[e / kW][kW + e % kW];
+#pragma unroll
+  for (int u = 0; u < kW / 8; ++u) Db[mi * kW + mq + 8 * u] = m[u];
   // the permutation: position k + i takes row s_row[i]; the rows of K that
   // were not chosen take the positions s_dd[] that chosen rows outside K
   // leave (s_ds[]: where each comes from)
