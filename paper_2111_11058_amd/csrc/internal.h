@@ -64,6 +64,7 @@ struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
   ReleaseFn rel = nullptr;  // the caller's release routine, or nullptr (hipFree)
+  bool owned = true;        // false: a part of another buffer
   DevBuf() = default;
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
@@ -93,8 +94,17 @@ struct DevBuf {
     alloc(v.size() * sizeof(T));
     if (!v.empty()) CBFM_HIP(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
   }
+  // n bytes of b from off on; b must outlive this
+  void view(const DevBuf& b, size_t off, size_t n) {
+    release();
+    p = static_cast<char*>(b.p) + off;
+    bytes = n;
+    owned = false;
+  }
   void release() {
-    if (p && rel) {
+    if (!owned) {
+      // nothing of its own
+    } else if (p && rel) {
       rel(p, nullptr);
     } else if (p) {
       (void)hipFree(p);
@@ -103,6 +113,7 @@ struct DevBuf {
     p = nullptr;
     bytes = 0;
     rel = nullptr;
+    owned = true;
   }
   template <typename T>
   T* as() const { return static_cast<T*>(p); }
@@ -210,7 +221,8 @@ struct cbfm_mesh_s {
   bool translated = false;
   std::vector<double> shift;   // nblocks * 3
   std::vector<int32_t> tcell;  // triangle -> its cell (translated meshes)
-  // device tables
+  // device tables: one allocation, and the parts of it
+  cbfm::DevBuf tables;
   cbfm::DevBuf q64, v64, c64, q32, v32, c32, cen, rad;   // SoA geometry
   cbfm::DevBuf test64, test32;  // test-side constants, one record per triangle
   cbfm::DevBuf tri_edge, tri_sign, tplus, tminus, aplus, aminus, length, area;

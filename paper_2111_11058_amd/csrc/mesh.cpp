@@ -6,7 +6,6 @@
 #include <cmath>
 #include <cstring>
 #include <numeric>
-#include <unordered_map>
 
 #include "internal.h"
 
@@ -30,35 +29,56 @@ static void build_tables(MeshHost& h) {
   const int64_t nt = h.nt;
   // local function a of triangle t: edge opposite vertex a, directed
   // v[a+1] -> v[a+2] in the triangle's counter-clockwise cycle.
-  std::vector<std::array<int64_t, 3>> keys(nt * 3);  // (lo, hi, slot)
+  // Slots in the order (lo, hi, slot) of their edges: counted into buckets
+  // by lo, each of the few entries of a bucket then sorted by (hi, slot).
+  struct Key {
+    int32_t lo, hi;
+    int64_t slot;
+  };
+  std::vector<int64_t> first(h.nv + 1, 0);
+  std::vector<Key> keys(nt * 3);
+  auto edge_of = [&](int64_t t, int a) {
+    const int32_t u = h.T[t * 3 + (a + 1) % 3], v = h.T[t * 3 + (a + 2) % 3];
+    return std::make_pair(std::min(u, v), std::max(u, v));
+  };
   for (int64_t t = 0; t < nt; ++t)
-    for (int a = 0; a < 3; ++a) {
-      int32_t u = h.T[t * 3 + (a + 1) % 3], v = h.T[t * 3 + (a + 2) % 3];
-      keys[t * 3 + a] = {std::min(u, v), std::max(u, v), t * 3 + a};
-    }
-  std::sort(keys.begin(), keys.end());
+    for (int a = 0; a < 3; ++a) ++first[edge_of(t, a).first + 1];
+  for (int64_t v = 0; v < h.nv; ++v) first[v + 1] += first[v];
+  {
+    std::vector<int64_t> at(first.begin(), first.end() - 1);
+    for (int64_t t = 0; t < nt; ++t)
+      for (int a = 0; a < 3; ++a) {
+        const auto e = edge_of(t, a);
+        keys[at[e.first]++] = Key{e.first, e.second, t * 3 + a};
+      }
+  }
+  for (int64_t v = 0; v < h.nv; ++v)
+    std::sort(keys.begin() + first[v], keys.begin() + first[v + 1], [](const Key& x, const Key& y) {
+      return x.hi != y.hi ? x.hi < y.hi : x.slot < y.slot;
+    });
   h.tri_edge.assign(nt * 3, -1);
   h.tri_sign.assign(nt * 3, 0);
   h.edges.clear();
+  h.edges.reserve(nt * 3);
   h.tplus.clear();
   h.tminus.clear();
   h.aplus.clear();
   h.aminus.clear();
   for (size_t i = 0; i < keys.size();) {
     size_t j = i;
-    while (j < keys.size() && keys[j][0] == keys[i][0] && keys[j][1] == keys[i][1]) ++j;
+    while (j < keys.size() && keys[j].lo == keys[i].lo && keys[j].hi == keys[i].hi) ++j;
     CBFM_REQUIRE(j - i == 2, CBFM_E_MESH,
-                 "edge (" + std::to_string(keys[i][0]) + "," + std::to_string(keys[i][1]) +
+                 "edge (" + std::to_string(keys[i].lo) + "," + std::to_string(keys[i].hi) +
                      ") is used by " + std::to_string(j - i) + " triangles (need 2)");
     const int32_t e = (int32_t)(h.edges.size() / 2);
-    h.edges.push_back((int32_t)keys[i][0]);
-    h.edges.push_back((int32_t)keys[i][1]);
+    h.edges.push_back(keys[i].lo);
+    h.edges.push_back(keys[i].hi);
     int32_t tp = -1, tm = -1, ap = -1, am = -1;
     for (size_t k = i; k < j; ++k) {
-      const int64_t slot = keys[k][2], t = slot / 3;
+      const int64_t slot = keys[k].slot, t = slot / 3;
       const int a = (int)(slot % 3);
       const int32_t from = h.T[t * 3 + (a + 1) % 3];
-      const bool fwd = (from == (int32_t)keys[k][0]);
+      const bool fwd = (from == keys[k].lo);
       if (fwd) {
         CBFM_REQUIRE(tp < 0, CBFM_E_MESH, "inconsistent triangle orientation");
         tp = (int32_t)t;
@@ -122,7 +142,11 @@ static void build_tables(MeshHost& h) {
 
 // Near pairs: P == Q, a shared vertex, or |c_P - c_Q|^2 < 1.5^2 max(hP^2, hQ^2)
 // with h the longest edge.  Candidates come from a uniform grid of cell size
-// 1.5 max h, so no pair that passes the test is missed.
+// 1.5 max h or more, so no pair that passes the test is missed.  The grid is
+// stored by cell (triangles of one cell in a row, cells of one z column one
+// after another): nine ranges hold a triangle's candidates, each pair is
+// tested once, and the lists come out in order without sorting (a hash map
+// of cells and a sort per triangle took three times as long).
 static void build_near(MeshHost& h) {
   const int64_t nt = h.nt;
   std::vector<double> h2(nt);
@@ -138,58 +162,110 @@ static void build_near(MeshHost& h) {
     h2[t] = m;
     hmax = std::max(hmax, std::sqrt(m));
   }
-  const double cell = 1.5 * hmax * (1 + 1e-9);
-  double lo[3] = {1e300, 1e300, 1e300};
+  double cell = 1.5 * hmax * (1 + 1e-9);
+  double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
   for (int64_t t = 0; t < nt; ++t)
-    for (int i = 0; i < 3; ++i) lo[i] = std::min(lo[i], h.centroid[t * 3 + i]);
-  auto key = [&](int64_t x, int64_t y, int64_t z) { return (x * 1000003 + y) * 1000033 + z; };
-  std::unordered_map<int64_t, std::vector<int32_t>> grid;
-  std::vector<std::array<int64_t, 3>> gc(nt);
+    for (int i = 0; i < 3; ++i) {
+      lo[i] = std::min(lo[i], h.centroid[t * 3 + i]);
+      hi[i] = std::max(hi[i], h.centroid[t * 3 + i]);
+    }
+  // (coarser where a scattered body would make far more cells than triangles)
+  auto cells_along = [&](int i) { return std::floor((hi[i] - lo[i]) / cell) + 1.0; };
+  while (cells_along(0) * cells_along(1) * cells_along(2) > 16.0 * (double)nt + 4096.0) cell *= 1.25;
+  int64_t dim[3];
+  for (int i = 0; i < 3; ++i) dim[i] = (int64_t)cells_along(i);
+  std::vector<std::array<int32_t, 3>> gc(nt);
+  std::vector<int64_t> first(dim[0] * dim[1] * dim[2] + 1, 0);
+  auto id = [&](int64_t x, int64_t y, int64_t z) { return (x * dim[1] + y) * dim[2] + z; };
   for (int64_t t = 0; t < nt; ++t) {
-    for (int i = 0; i < 3; ++i) gc[t][i] = (int64_t)std::floor((h.centroid[t * 3 + i] - lo[i]) / cell);
-    grid[key(gc[t][0], gc[t][1], gc[t][2])].push_back((int32_t)t);
+    for (int i = 0; i < 3; ++i)
+      gc[t][i] = (int32_t)std::min(dim[i] - 1, (int64_t)std::floor((h.centroid[t * 3 + i] - lo[i]) / cell));
+    ++first[id(gc[t][0], gc[t][1], gc[t][2]) + 1];
+  }
+  for (size_t c = 1; c < first.size(); ++c) first[c] += first[c - 1];
+  std::vector<int32_t> members(nt);
+  {
+    std::vector<int64_t> at(first.begin(), first.end() - 1);
+    for (int64_t t = 0; t < nt; ++t) members[at[id(gc[t][0], gc[t][1], gc[t][2])]++] = (int32_t)t;
   }
   // vertex -> triangles
-  std::vector<std::vector<int32_t>> vt(h.nv);
-  for (int64_t t = 0; t < nt; ++t)
-    for (int a = 0; a < 3; ++a) vt[h.T[t * 3 + a]].push_back((int32_t)t);
-  h.near.clear();
-  std::vector<int32_t> cand;
+  std::vector<int64_t> vfirst(h.nv + 1, 0);
+  std::vector<int32_t> vt(nt * 3);
+  for (int64_t e = 0; e < nt * 3; ++e) ++vfirst[h.T[e] + 1];
+  for (int64_t v = 0; v < h.nv; ++v) vfirst[v + 1] += vfirst[v];
+  {
+    std::vector<int64_t> at(vfirst.begin(), vfirst.end() - 1);
+    for (int64_t e = 0; e < nt * 3; ++e) vt[at[h.T[e]]++] = (int32_t)(e / 3);
+  }
+  // pairs p < q, each once (seen[q] = p: already taken), counted by q
+  std::vector<std::pair<int32_t, int32_t>> up;
+  up.reserve(nt * 16);
+  std::vector<int32_t> seen(nt, -1);
+  std::vector<int64_t> lfirst(nt + 1, 0), ufirst(nt + 1, 0);
   for (int64_t p = 0; p < nt; ++p) {
-    cand.clear();
-    for (int dx = -1; dx <= 1; ++dx)
-      for (int dy = -1; dy <= 1; ++dy)
-        for (int dz = -1; dz <= 1; ++dz) {
-          auto it = grid.find(key(gc[p][0] + dx, gc[p][1] + dy, gc[p][2] + dz));
-          if (it == grid.end()) continue;
-          for (int32_t q : it->second) {
-            const double d0 = h.centroid[q * 3 + 0] - h.centroid[p * 3 + 0];
-            const double d1 = h.centroid[q * 3 + 1] - h.centroid[p * 3 + 1];
-            const double d2 = h.centroid[q * 3 + 2] - h.centroid[p * 3 + 2];
-            const double d2s = (d0 * d0 + d1 * d1) + d2 * d2;
-            if (d2s < 2.25 * std::max(h2[p], h2[q])) cand.push_back(q);
-          }
+    auto take = [&](int32_t q) {
+      seen[q] = (int32_t)p;
+      up.push_back({(int32_t)p, q});
+      ++lfirst[q + 1];
+      ++ufirst[p + 1];
+    };
+    const double cp[3] = {h.centroid[p * 3], h.centroid[p * 3 + 1], h.centroid[p * 3 + 2]}, hp = h2[p];
+    const int64_t z0 = std::max<int64_t>(0, gc[p][2] - 1), z1 = std::min<int64_t>(dim[2] - 1, gc[p][2] + 1);
+    for (int64_t x = std::max<int64_t>(0, gc[p][0] - 1); x <= std::min<int64_t>(dim[0] - 1, gc[p][0] + 1); ++x)
+      for (int64_t y = std::max<int64_t>(0, gc[p][1] - 1); y <= std::min<int64_t>(dim[1] - 1, gc[p][1] + 1); ++y)
+        for (int64_t e = first[id(x, y, z0)]; e < first[id(x, y, z1) + 1]; ++e) {
+          const int32_t q = members[e];
+          if (q <= p) continue;
+          const double d0 = h.centroid[q * 3 + 0] - cp[0];
+          const double d1 = h.centroid[q * 3 + 1] - cp[1];
+          const double d2 = h.centroid[q * 3 + 2] - cp[2];
+          const double d2s = (d0 * d0 + d1 * d1) + d2 * d2;
+          if (d2s < 2.25 * std::max(hp, h2[q])) take(q);
         }
-    for (int a = 0; a < 3; ++a)
-      for (int32_t q : vt[h.T[p * 3 + a]]) cand.push_back(q);
-    std::sort(cand.begin(), cand.end());
-    cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
-    for (int32_t q : cand) {
+    for (int a = 0; a < 3; ++a) {
+      const int32_t v = h.T[p * 3 + a];
+      for (int64_t e = vfirst[v]; e < vfirst[v + 1]; ++e)
+        if (vt[e] > p && seen[vt[e]] != p) take(vt[e]);
+    }
+  }
+  for (int64_t t = 0; t < nt; ++t) {
+    lfirst[t + 1] += lfirst[t];
+    ufirst[t + 1] += ufirst[t];
+  }
+  // every triangle's lower partners come in ascending order of p, and read
+  // back by q they put its upper ones in order: nothing is sorted
+  std::vector<int32_t> lower(up.size()), upper(up.size());
+  {
+    std::vector<int64_t> at(lfirst.begin(), lfirst.end() - 1);
+    for (const auto& u : up) lower[at[u.second]++] = u.first;
+    at.assign(ufirst.begin(), ufirst.end() - 1);
+    for (int64_t q = 0; q < nt; ++q)
+      for (int64_t e = lfirst[q]; e < lfirst[q + 1]; ++e) upper[at[lower[e]]++] = (int32_t)q;
+  }
+  h.near.clear();
+  h.near.reserve(2 * up.size() + nt);
+  for (int64_t p = 0; p < nt; ++p) {
+    const double* n1 = &h.normal[p * 3];
+    const double* cp = &h.centroid[p * 3];
+    const double flat = 1e-10 * std::sqrt(h.area[p]);
+    auto add = [&](int32_t q) {
       NearPair np{(int32_t)p, q, (int32_t)p, q, 0, 0};
       // coplanar: parallel normals and Q's centroid in P's plane
-      const double* n1 = &h.normal[p * 3];
       const double* n2 = &h.normal[q * 3];
       const double c0 = n1[1] * n2[2] - n1[2] * n2[1];
       const double c1 = n1[2] * n2[0] - n1[0] * n2[2];
       const double c2 = n1[0] * n2[1] - n1[1] * n2[0];
       if ((c0 * c0 + c1 * c1) + c2 * c2 <= 1e-20) {
         double dc = 0;
-        for (int i = 0; i < 3; ++i) dc += n1[i] * (h.centroid[q * 3 + i] - h.centroid[p * 3 + i]);
-        if (std::fabs(dc) <= 1e-10 * std::sqrt(h.area[p])) np.coplanar = 1;
+        for (int i = 0; i < 3; ++i) dc += n1[i] * (h.centroid[q * 3 + i] - cp[i]);
+        if (std::fabs(dc) <= flat) np.coplanar = 1;
       }
       if (p == q) np.coplanar = 1;
       h.near.push_back(np);
-    }
+    };
+    for (int64_t e = lfirst[p]; e < lfirst[p + 1]; ++e) add(lower[e]);
+    add((int32_t)p);
+    for (int64_t e = ufirst[p]; e < ufirst[p + 1]; ++e) add(upper[e]);
   }
 }
 
@@ -312,27 +388,46 @@ static void upload(cbfm_mesh_s* m) {
   for (size_t i = 0; i < v64.size(); ++i) v32[i] = (float)v64[i];
   for (size_t i = 0; i < c64.size(); ++i) c32[i] = (float)c64[i];
   for (size_t i = 0; i < test64.size(); ++i) test32[i] = (float)test64[i];
-  m->q64.upload(q64);
-  m->v64.upload(v64);
-  m->c64.upload(c64);
-  m->q32.upload(q32);
-  m->v32.upload(v32);
-  m->c32.upload(c32);
-  m->cen.upload(cen);
-  m->rad.upload(rad);
-  m->test64.upload(test64);
-  m->test32.upload(test32);
-  m->tri_xyz.upload(xyz9);
-  m->tri_edge.upload(h.tri_edge);
-  m->tri_sign.upload(h.tri_sign);
-  m->tplus.upload(h.tplus);
-  m->tminus.upload(h.tminus);
-  m->aplus.upload(h.aplus);
-  m->aminus.upload(h.aminus);
-  m->length.upload(h.length);
-  m->area.upload(h.area);
-  m->perm.upload(h.perm);
-  m->iperm.upload(h.iperm);
+  // one device allocation and one copy for all the tables (each was its own
+  // of both before: 1.3 of a small mesh's 1.9 ms)
+  std::vector<std::pair<const void*, size_t>> parts;
+  std::vector<DevBuf*> bufs;
+  auto add = [&](DevBuf& d, const auto& v) {
+    parts.push_back({v.data(), v.size() * sizeof(v[0])});
+    bufs.push_back(&d);
+  };
+  add(m->q64, q64);
+  add(m->v64, v64);
+  add(m->c64, c64);
+  add(m->q32, q32);
+  add(m->v32, v32);
+  add(m->c32, c32);
+  add(m->cen, cen);
+  add(m->rad, rad);
+  add(m->test64, test64);
+  add(m->test32, test32);
+  add(m->tri_xyz, xyz9);
+  add(m->tri_edge, h.tri_edge);
+  add(m->tri_sign, h.tri_sign);
+  add(m->tplus, h.tplus);
+  add(m->tminus, h.tminus);
+  add(m->aplus, h.aplus);
+  add(m->aminus, h.aminus);
+  add(m->length, h.length);
+  add(m->area, h.area);
+  add(m->perm, h.perm);
+  add(m->iperm, h.iperm);
+  size_t total = 0;
+  for (const auto& p : parts) total += (p.second + 255) & ~(size_t)255;
+  std::vector<char> host(total);
+  m->tables.alloc(total);
+  size_t off = 0;
+  for (size_t i = 0; i < parts.size(); ++i) {
+    std::memcpy(host.data() + off, parts[i].first, parts[i].second);
+    bufs[i]->view(m->tables, off, parts[i].second);
+    off += (parts[i].second + 255) & ~(size_t)255;
+  }
+  CBFM_HIP(hipMemcpy(m->tables.p, host.data(), total, hipMemcpyHostToDevice));
 }
 
 extern "C" {
