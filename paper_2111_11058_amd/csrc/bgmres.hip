@@ -43,7 +43,7 @@ namespace {
 
 constexpr int PMAX = 32;  // right-hand sides per block (a power of two: indices below use e >> 5)
 static_assert(PMAX == 32, "index arithmetic assumes 32");
-constexpr int GCH = 32;   // vector entries per block of the Gram partial sums
+constexpr int GCH = 16;   // vector entries per block of the Gram partial sums
 constexpr int OMS = 2 * PMAX;  // row stride of a stored 2p x 2p factor (zero past 2p)
 constexpr int RBUF = 6144;     // rows of a block column staged in LDS (mb p <= RBUF)
 
@@ -127,43 +127,50 @@ enum { CTL_STATE = 0, CTL_DONE = 1 };
 // < p over the GCH entries of this block, real and imaginary parts in
 // double-double (DD) or in double (low parts zero: the second pass, whose
 // rows the first has made orthonormal to within about 1e-3 at worst); entry
-// (a, b) at a * PMAX + b of the
-// block's PMAX^2 slots.
+// (a, b) at a * PMAX + b of the block's PMAX^2 slots.  One thread per pair
+// a <= b: the double-double sums are chains of dependent additions, so
+// their count per thread is the launch (38 us with four slots of 32 entries
+// a thread, half of them below the diagonal; 4,068-entry vectors).
+constexpr int GTH = (PMAX * (PMAX + 1) / 2 + 63) / 64 * 64;
 template <bool DD>
-__global__ void __launch_bounds__(256) gram_partial_kernel(const double2* __restrict__ W, int64_t n, int p,
+__global__ void __launch_bounds__(GTH) gram_partial_kernel(const double2* __restrict__ W, int64_t n, int p,
                                                            double* __restrict__ part, const int32_t* __restrict__ ctl) {
   if (ctl[CTL_STATE] != 0) return;  // uniform over the launch
   __shared__ double2 ws[PMAX][GCH + 1];
   const int64_t i0 = (int64_t)blockIdx.x * GCH;
-  for (int e = threadIdx.x; e < p * GCH; e += 256) {
+  for (int e = threadIdx.x; e < p * GCH; e += GTH) {
     const int a = e / GCH, k = e % GCH;
     ws[a][k] = i0 + k < n ? W[a * n + i0 + k] : make_double2(0.0, 0.0);
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < p * p; e += 256) {
-    const int a = e / p, b = e % p;
-    if (a > b) continue;
-    dd sr{0.0, 0.0}, si{0.0, 0.0};
-    if (DD) {
-      for (int k = 0; k < GCH; ++k) {
-        const double2 x = ws[a][k], y = ws[b][k];
-        sr = dd_add(sr, dd_add(dd_prod(x.x, y.x), dd_prod(x.y, y.y)));
-        si = dd_add(si, dd_add(dd_prod(x.x, y.y), dd_prod(-x.y, y.x)));
-      }
-    } else {
-#pragma unroll 8
-      for (int k = 0; k < GCH; ++k) {
-        const double2 x = ws[a][k], y = ws[b][k];
-        sr.hi = fma(x.x, y.x, fma(x.y, y.y, sr.hi));
-        si.hi = fma(x.x, y.y, fma(-x.y, y.x, si.hi));
-      }
+  // pair e of the upper triangle, by columns: b (b + 1) / 2 <= e
+  const int e = threadIdx.x;
+  if (e >= p * (p + 1) / 2) return;
+  int b = (int)((sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
+  b += (b + 1) * (b + 2) / 2 <= e ? 1 : 0;
+  b -= b * (b + 1) / 2 > e ? 1 : 0;
+  const int a = e - b * (b + 1) / 2;
+  dd sr{0.0, 0.0}, si{0.0, 0.0};
+  if (DD) {
+#pragma unroll 4
+    for (int k = 0; k < GCH; ++k) {
+      const double2 x = ws[a][k], y = ws[b][k];
+      sr = dd_add(sr, dd_add(dd_prod(x.x, y.x), dd_prod(x.y, y.y)));
+      si = dd_add(si, dd_add(dd_prod(x.x, y.y), dd_prod(-x.y, y.x)));
     }
-    double* o = part + ((int64_t)blockIdx.x * PMAX * PMAX + a * PMAX + b) * 4;
-    o[0] = sr.hi;
-    o[1] = sr.lo;
-    o[2] = si.hi;
-    o[3] = si.lo;
+  } else {
+#pragma unroll 8
+    for (int k = 0; k < GCH; ++k) {
+      const double2 x = ws[a][k], y = ws[b][k];
+      sr.hi = fma(x.x, y.x, fma(x.y, y.y, sr.hi));
+      si.hi = fma(x.x, y.y, fma(-x.y, y.x, si.hi));
+    }
   }
+  double* o = part + ((int64_t)blockIdx.x * PMAX * PMAX + a * PMAX + b) * 4;
+  o[0] = sr.hi;
+  o[1] = sr.lo;
+  o[2] = si.hi;
+  o[3] = si.lo;
 }
 
 // ---- The partial sums of every Gram entry added over the nchunk blocks in
@@ -225,10 +232,6 @@ __global__ void __launch_bounds__(256) chol_pivot_kernel(const double* __restric
       S[a][b] = cdd{dd{g[0], g[1]}, dd{g[2], g[3]}};
     }
   }
-  for (int e = tid; e < PMAX * PMAX; e += 256) {
-    R[e / PMAX][e % PMAX] = make_double2(0.0, 0.0);
-    U[e / PMAX][e % PMAX] = make_double2(0.0, 0.0);
-  }
   if (tid < PMAX) {
     used[tid] = 0;
     pos[tid] = -1;
@@ -250,66 +253,90 @@ __global__ void __launch_bounds__(256) chol_pivot_kernel(const double* __restric
   // every pivot of the scaled matrix stays above 1e-10 (its condition below
   // 1e5, where Cholesky QR in double loses at most about 1e-6 of
   // orthogonality, which the second pass restores); otherwise the
-  // factorisation is redone in double-double with pivoting.  One barrier
-  // per step: each thread takes the pivot row from the matrix itself.
+  // factorisation is redone in double-double with pivoting.
+  // [S | I] is eliminated in registers (thread: row a, columns q + 8 u of
+  // both halves), step k's row passing through LDS in two buffers, one
+  // barrier a step: S's rows over the square roots of their pivots give R,
+  // I's give R^{-H}.  Bound by the latency of the p steps: 47 us a call with
+  // the matrix in LDS and the inverse one column per thread afterwards.
   {
-    double2(*Sd)[PMAX] = U;  // U is free until the inverse
     __shared__ double dsc[PMAX];
-    if (tid < p) {
-      const double d = S[tid][tid].re.hi + S[tid][tid].re.lo;
+    __shared__ double2 row[2][2 * PMAX];
+    if (tid < PMAX) {
+      const double d = tid < p ? S[tid][tid].re.hi + S[tid][tid].re.lo : 1.0;
       dsc[tid] = d > 0 ? sqrt(d) : 0.0;
-      if (!(d >= 1e-20 * dmax0)) redo_s = 1;
+      if (tid < p && !(d >= 1e-20 * dmax0)) redo_s = 1;
+    }
+    __syncthreads();
+    if (!redo_s) {  // uniform
+      const int a = tid >> 3, q = tid & 7;
+      double2 x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int b = q + 8 * u;
+        y[u] = make_double2(a == b ? 1.0 : 0.0, 0.0);
+        x[u] = y[u];
+        if (a < p && b < p && a != b) {
+          const cdd z = a < b ? S[a][b] : S[b][a];
+          const double sc = 1.0 / (dsc[a] * dsc[b]);
+          x[u] = make_double2((z.re.hi + z.re.lo) * sc, (a < b ? 1.0 : -1.0) * (z.im.hi + z.im.lo) * sc);
+        }
+      }
+      bool ok = true;
+      double mine = 1.0;  // the pivot of row a
+#pragma unroll 1
+      for (int k = 0; k < p; ++k) {
+        double2* r = row[k & 1];
+        if (a == k)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            r[q + 8 * u] = x[u];
+            r[PMAX + q + 8 * u] = y[u];
+          }
+        __syncthreads();
+        const double pk = r[k].x;
+        if (!(pk > 1e-10)) {
+          ok = false;
+          break;  // uniform
+        }
+        if (a == k) mine = pk;
+        double inv = __builtin_amdgcn_rcp(pk);  // 1e-10 < pk: two Newton steps
+        inv = fma(fma(-pk, inv, 1.0), inv, inv);
+        inv = fma(fma(-pk, inv, 1.0), inv, inv);
+        const double2 s = r[a];  // S[k][a]; row a loses conj(S[k][a]) / pk times row k
+        const double2 f = a > k ? make_double2(s.x * inv, -s.y * inv) : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          x[u] = c_sub(x[u], c_mul(f, r[q + 8 * u]));
+          y[u] = c_sub(y[u], c_mul(f, r[PMAX + q + 8 * u]));
+        }
+      }
+      if (ok) {
+        const double g = 1.0 / sqrt(mine);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int b = q + 8 * u;
+          if (a >= p || b >= p) continue;
+          const double fr = b >= a ? g * dsc[b] : 0.0;
+          M[a * p + b] = make_double2(x[u].x * fr, x[u].y * fr);
+          // T = R^{-1}: T[b][a] = conj((R^{-H})[a][b]), zero below the diagonal
+          const double ft = b <= a ? g / dsc[b] : 0.0;
+          T[b * p + a] = make_double2(y[u].x * ft, -y[u].y * ft);
+        }
+        if (tid == 0) rank[0] = p;
+        return;
+      }
+      __syncthreads();
+      if (tid == 0) redo_s = 1;
     }
     __syncthreads();
     for (int e = tid; e < PMAX * PMAX; e += 256) {
-      const int a = e >> 5, b = e & (PMAX - 1);
-      if (a >= p || b >= p) continue;
-      if (a <= b && !redo_s) {
-        const double sc = 1.0 / (dsc[a] * dsc[b]);
-        Sd[a][b] = make_double2((S[a][b].re.hi + S[a][b].re.lo) * sc, (S[a][b].im.hi + S[a][b].im.lo) * sc);
-      }
-    }
-    __syncthreads();
-    for (int k = 0; k < p && !redo_s; ++k) {  // redo_s: uniform after each barrier
-      const double pk = Sd[k][k].x;
-      if (!(pk > 1e-10)) {
-        if (tid == 0) redo_s = 1;
-        __syncthreads();
-        break;
-      }
-      const double sq = sqrt(pk), inv = 1.0 / pk;
-      if (tid < p) {  // row k of the scaled factor, unscaled by the column norm
-        const int m = tid;
-        const double2 v = m < k ? make_double2(0.0, 0.0) : (m == k ? make_double2(sq, 0.0) : Sd[k][m]);
-        const double f = (m == k ? 1.0 : 1.0 / sq) * dsc[m];
-        R[k][m] = make_double2(v.x * f, v.y * f);
-      }
-      for (int e = tid; e < PMAX * PMAX; e += 256) {  // Schur update of the trailing pairs
-        const int a = e >> 5, b = e & (PMAX - 1);
-        if (a <= k || a > b || b >= p) continue;
-        const double2 t = c_cjmul(Sd[k][a], Sd[k][b]);
-        Sd[a][b] = make_double2(Sd[a][b].x - t.x * inv, Sd[a][b].y - t.y * inv);
-      }
-      __syncthreads();
-    }
-    if (!redo_s && tid < p) {
-      piv[tid] = tid;
-      pos[tid] = tid;
-      used[tid] = 1;
-    }
-    if (redo_s) {  // uniform: start again in double-double
-      for (int e = tid; e < PMAX * PMAX; e += 256) {
-        R[e / PMAX][e % PMAX] = make_double2(0.0, 0.0);
-        U[e / PMAX][e % PMAX] = make_double2(0.0, 0.0);
-      }
-      if (tid < PMAX) {
-        used[tid] = 0;
-        pos[tid] = -1;
-      }
+      R[e / PMAX][e % PMAX] = make_double2(0.0, 0.0);
+      U[e / PMAX][e % PMAX] = make_double2(0.0, 0.0);
     }
     __syncthreads();
   }
-  for (int k = 0; k < p && redo_s; ++k) {
+  for (int k = 0; k < p; ++k) {
     if (tid < 64) {  // pivot: the largest remaining diagonal, lowest index on ties
       double v = tid < p && !used[tid] ? S[tid][tid].re.hi : -1.0;
       int qi = tid;
@@ -659,45 +686,92 @@ __global__ void __launch_bounds__(256) bls_qr_kernel(const double2* __restrict__
   }
 }
 
-// ---- One step of the block back substitution Y = R^{-1} G (R upper
-// triangular, column-major with ldr, in p x p diagonal blocks; G and Y
-// row-major, p columns): every block solves the diagonal block b for all p
-// columns (thread c takes column c; a zero diagonal, a direction with no
-// part in the least-squares solution, gives a zero entry), block (0, 0)
-// stores Y_b, and each thread then removes R[k][block b] Y_b from its row
-// k < b p of G, in the eight columns of its blockIdx.y.
-__global__ void __launch_bounds__(256) backsolve_step_kernel(const double2* __restrict__ Rb, int64_t ldr,
-                                                             double2* __restrict__ G, int p, int64_t b,
-                                                             double2* __restrict__ Y) {
+// ---- The inverses of the p x p diagonal blocks of R (upper triangular,
+// column-major with ldr), one block each: Di[b] row-major.  A zero diagonal
+// (a direction with no part in the least-squares solution) gives a zero row,
+// hence a zero entry of the solution.
+__global__ void __launch_bounds__(64) diag_inverse_kernel(const double2* __restrict__ Rb, int64_t ldr, int p,
+                                                          double2* __restrict__ Di) {
   __shared__ double2 Rbb[PMAX][PMAX + 1];
-  __shared__ double2 yb[PMAX][PMAX + 1];
-  const int tid = threadIdx.x;
-  const int64_t r0 = b * p;
-  for (int e = tid; e < p * p; e += 256) {
+  const int64_t r0 = (int64_t)blockIdx.x * p;
+  for (int e = threadIdx.x; e < p * p; e += 64) {
     const int r = e % p, k = e / p;  // column k of the block, row r
     Rbb[r][k] = Rb[(r0 + k) * ldr + r0 + r];
   }
-  for (int e = tid; e < p * p; e += 256) yb[e / p][e % p] = G[(r0 + e / p) * p + e % p];
   __syncthreads();
-  if (tid < p) {
-    const int c = tid;
-    for (int r = p - 1; r >= 0; --r) {
-      double2 g = yb[r][c];
-#pragma unroll 8
-      for (int k = r + 1; k < p; ++k) g = c_sub(g, c_mul(Rbb[r][k], yb[k][c]));
-      const double2 d = Rbb[r][r];
-      const double dn = d.x * d.x + d.y * d.y;
-      yb[r][c] = dn > 0 ? make_double2((g.x * d.x + g.y * d.y) / dn, (g.y * d.x - g.x * d.y) / dn)
-                        : make_double2(0.0, 0.0);
-    }
+  const int c = threadIdx.x;
+  if (c >= p) return;
+  double2 y[PMAX];
+#pragma unroll
+  for (int r = PMAX - 1; r >= 0; --r) {
+    y[r] = make_double2(0.0, 0.0);
+    if (r >= p) continue;
+    double2 g = make_double2(r == c ? 1.0 : 0.0, 0.0);
+#pragma unroll
+    for (int k = r + 1; k < PMAX; ++k)
+      if (k < p) g = c_sub(g, c_mul(Rbb[r][k], y[k]));
+    const double2 d = Rbb[r][r];
+    const double dn = d.x * d.x + d.y * d.y;
+    if (dn > 0) y[r] = make_double2((g.x * d.x + g.y * d.y) / dn, (g.y * d.x - g.x * d.y) / dn);
+    Di[((int64_t)blockIdx.x * p + r) * p + c] = y[r];
+  }
+}
+
+// ---- One step of the block back substitution Y = R^{-1} G (R upper
+// triangular, column-major with ldr, in p x p diagonal blocks with inverses
+// Di; G and Y row-major, p columns): every block forms the diagonal block's
+// solution Di[b] G_b in the eight columns of its blockIdx.y, blocks (0, .)
+// store Y_b, and each thread then removes R[k][block b] Y_b from its row
+// k < b p of G in those columns.  (Solving the triangle in every step took
+// 37 us a step, two thirds of it in 32 dependent divisions.)
+__global__ void __launch_bounds__(256) backsolve_step_kernel(const double2* __restrict__ Rb, int64_t ldr,
+                                                             const double2* __restrict__ Di,
+                                                             double2* __restrict__ G, int p, int64_t b,
+                                                             double2* __restrict__ Y) {
+  __shared__ double2 D[PMAX][PMAX + 1];
+  __shared__ double2 Rbb[PMAX][PMAX + 1];
+  __shared__ double2 gb[PMAX][8];
+  __shared__ double2 yb[PMAX][8];
+  const int tid = threadIdx.x;
+  const int64_t r0 = b * p;
+  const int c0 = blockIdx.y * 8;
+  const int64_t k = (int64_t)blockIdx.x * 256 + tid;
+  for (int e = tid; e < p * p; e += 256) {
+    D[e / p][e % p] = Di[b * p * p + e];
+    Rbb[e % p][e / p] = Rb[(r0 + e / p) * ldr + r0 + e % p];
+  }
+  for (int e = tid; e < p * 8; e += 256) {
+    const int c = c0 + e % 8;
+    gb[e / 8][e % 8] = c < p ? G[(r0 + e / 8) * p + c] : make_double2(0.0, 0.0);
   }
   __syncthreads();
-  if (blockIdx.x == 0 && blockIdx.y == 0)
-    for (int e = tid; e < p * p; e += 256) Y[(r0 + e / p) * p + e % p] = yb[e / p][e % p];
-  // row k, the eight columns c0..c0+7 of blockIdx.y
-  const int64_t k = (int64_t)blockIdx.x * 256 + tid;
-  const int c0 = blockIdx.y * 8;
-  if (k >= r0 || c0 >= p) return;
+  // y = D g, then once y += D (g - R y): the inverse alone would leave a
+  // residual of its condition times the rounding
+  const int yr = tid / 8, yc = tid % 8;
+  const bool on = tid < p * 8;
+  double2 y = make_double2(0.0, 0.0), res = y;
+  if (on) {
+#pragma unroll 8
+    for (int l = 0; l < p; ++l) y = c_add(y, c_mul(D[yr][l], gb[l][yc]));
+    yb[yr][yc] = y;
+  }
+  __syncthreads();
+  if (on) {
+    res = gb[yr][yc];
+#pragma unroll 8
+    for (int l = yr; l < p; ++l) res = c_sub(res, c_mul(Rbb[yr][l], yb[l][yc]));
+  }
+  __syncthreads();
+  if (on) gb[yr][yc] = res;
+  __syncthreads();
+  if (on) {
+#pragma unroll 8
+    for (int l = 0; l < p; ++l) y = c_add(y, c_mul(D[yr][l], gb[l][yc]));
+    yb[yr][yc] = y;
+    if (blockIdx.x == 0 && c0 + yc < p) Y[(r0 + yr) * p + c0 + yc] = y;
+  }
+  __syncthreads();
+  if (k >= r0) return;
   double2 acc[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) acc[u] = make_double2(0.0, 0.0);
@@ -709,7 +783,7 @@ __global__ void __launch_bounds__(256) backsolve_step_kernel(const double2* __re
     for (int u = 0; u < 8; ++u) {
       const int j = j0 + u < p ? j0 + u : j0;  // rv[u] is zero past p
 #pragma unroll
-      for (int c = 0; c < 8; ++c) acc[c] = c_add(acc[c], c_mul(rv[u], yb[j][c0 + c]));
+      for (int c = 0; c < 8; ++c) acc[c] = c_add(acc[c], c_mul(rv[u], yb[j][c]));
     }
   }
 #pragma unroll
@@ -878,10 +952,14 @@ class BlockGmres {
       CBFM_HIP(hipStreamSynchronize(s));
       const int64_t nb = ctl[CTL_DONE], K = nb * p;
       if (K > 0) {
+        Scratch di((size_t)nb * p * p * sizeof(double2), s);
+        hipLaunchKernelGGL(diag_inverse_kernel, dim3((unsigned)nb), dim3(64), 0, s, Rb_.as<double2>(), mb_ * p, p,
+                           di.as<double2>());
         for (int64_t bb = nb - 1; bb >= 0; --bb)
           hipLaunchKernelGGL(backsolve_step_kernel,
                              dim3((unsigned)std::max<int64_t>(1, (bb * p + 255) / 256), (unsigned)((p + 7) / 8)),
-                             dim3(256), 0, s, Rb_.as<double2>(), mb_ * p, G_.as<double2>(), p, bb, Y_.as<double2>());
+                             dim3(256), 0, s, Rb_.as<double2>(), mb_ * p, di.as<double2>(), G_.as<double2>(), p, bb,
+                             Y_.as<double2>());
         CBFM_HIP(hipGetLastError());
         // x += Y^T V_0..V_{nb-1}
         std::vector<std::vector<GemmDesc>> xg(1);
@@ -918,10 +996,10 @@ class BlockGmres {
   void orthonormalise(const double2* W, double2* Out, double2* M, uint64_t sd, bool must_full) {
     const int32_t* ctl = ctl_.as<int32_t>();
     if (must_full)  // the second pass: rows already nearly orthonormal
-      hipLaunchKernelGGL(gram_partial_kernel<false>, dim3((unsigned)nch_), dim3(256), 0, s_, W, n_, p_,
+      hipLaunchKernelGGL(gram_partial_kernel<false>, dim3((unsigned)nch_), dim3(GTH), 0, s_, W, n_, p_,
                          part_.as<double>(), ctl);
     else
-      hipLaunchKernelGGL(gram_partial_kernel<true>, dim3((unsigned)nch_), dim3(256), 0, s_, W, n_, p_,
+      hipLaunchKernelGGL(gram_partial_kernel<true>, dim3((unsigned)nch_), dim3(GTH), 0, s_, W, n_, p_,
                          part_.as<double>(), ctl);
     hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)((p_ * p_ + 3) / 4)), dim3(256), 0, s_, part_.as<double>(),
                        nch_, p_, gdd_.as<double>(), ctl);
