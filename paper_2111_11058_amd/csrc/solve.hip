@@ -16,7 +16,9 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <map>
 #include <memory>
+#include <mutex>
 #include <type_traits>
 
 #include "cbf.h"
@@ -79,6 +81,25 @@ __device__ inline double dpp_double(double x) {
 
 // Sum over the 64 lanes of a wavefront as a butterfly: every lane ends with
 // the same bits.
+// Sum over each row of 16 lanes (a DPP butterfly: every lane has it).
+template <int CTRL>
+__device__ inline double dpp_move(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ inline double row16_total(double x) {
+  x += dpp_move<0xB1>(x);   // quad_perm [1, 0, 3, 2]
+  x += dpp_move<0x4E>(x);   // quad_perm [2, 3, 0, 1]
+  x += dpp_move<0x141>(x);  // row_half_mirror
+  x += dpp_move<0x140>(x);  // row_mirror
+  return x;
+}
+// x of a lane known at compile time, uniform
+__device__ inline double lane_value(double x, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                          __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
 __device__ inline double wave_sum(double x) {
   x += dpp_double<0xB1>(x);   // quad_perm [1, 0, 3, 2]
   x += dpp_double<0x4E>(x);   // quad_perm [2, 3, 0, 1]
@@ -1109,19 +1130,37 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
 // T_new their rows j..j+S-1 (upper triangular).  The shifts are the Ritz
 // values of a first plain cycle of S iterations in Leja order.
 
-// z = u - theta q (written to basis slot jd, q = slot jd - 1) and the
-// partial sums of |z|^2 of each 256-row block
+// sigma of a vector from the np partial sums of its squares
+__device__ __forceinline__ double sigma_of(const double* __restrict__ part, int np) {
+  double q = 0;
+  for (int b = 0; b < np; ++b) q += part[b];
+  return sqrt(q);
+}
+
+// Newton step i = ti + 1 of a block: slot jd takes sigma_i z_i =
+// (A - theta) z_{i-1} from u = A times slot jd - 1, which holds z_{i-1}
+// (ti = 0) or sigma_{i-1} z_{i-1}; the partial sums of |.|^2 of each 256-row
+// block go to part (nrhs x np per step).  One scaling pass for the block
+// (nscale_kernel) instead of one per step: 4 us and a launch gap saved for
+// each of S - 1 steps at 846 x 64.
 __global__ void __launch_bounds__(256) newton_kernel(const double2* __restrict__ u, double2* __restrict__ V,
                                                      int64_t vstride, int64_t n, int64_t jd,
                                                      const double2* __restrict__ theta, int S, int ti,
                                                      GmresState st, double* __restrict__ part) {
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x, c = blockIdx.y;
   if (!st.active[c]) return;  // uniform over the block
+  const int np = gridDim.x;
+  const int64_t step = (int64_t)gridDim.y * np;
+  double r = 1.0;
+  if (ti > 0) {
+    const double sg = sigma_of(part + (ti - 1) * step + c * np, np);
+    r = sg > 0 ? 1.0 / sg : 0.0;
+  }
   double q2 = 0;
   if (k < n) {
     const double2 th = theta[c * S + ti];
     const double2 q = V[(jd - 1) * vstride + c * n + k], w = u[c * n + k];
-    const double2 z = make_double2(w.x - (th.x * q.x - th.y * q.y), w.y - (th.x * q.y + th.y * q.x));
+    const double2 z = make_double2(r * (w.x - (th.x * q.x - th.y * q.y)), r * (w.y - (th.x * q.y + th.y * q.x)));
     V[jd * vstride + c * n + k] = z;
     q2 = z.x * z.x + z.y * z.y;
   }
@@ -1129,23 +1168,25 @@ __global__ void __launch_bounds__(256) newton_kernel(const double2* __restrict__
   q2 = wave_sum(q2);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = q2;
   __syncthreads();
-  if (threadIdx.x == 0) part[c * gridDim.x + blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+  if (threadIdx.x == 0) part[ti * step + c * np + blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// sigma = sqrt(sum of the partial sums); slot jd /= sigma
-__global__ void __launch_bounds__(256) nscale_kernel(double2* __restrict__ V, int64_t vstride, int64_t n, int64_t jd,
-                                                     const double* __restrict__ part, int np, double* __restrict__ sig,
-                                                     int S, int ti, GmresState st) {
+// sigma_i and z_i = slot / sigma_i for the S slots from Z on
+__global__ void __launch_bounds__(256) nscale_kernel(double2* __restrict__ Z, int64_t vstride, int64_t n,
+                                                     const double* __restrict__ part, double* __restrict__ sig, int S,
+                                                     GmresState st) {
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x, c = blockIdx.y;
   if (!st.active[c]) return;
-  double q = 0;
-  for (int b = 0; b < np; ++b) q += part[c * np + b];
-  const double sg = sqrt(q);
-  if (blockIdx.x == 0 && threadIdx.x == 0) sig[c * S + ti] = sg;
-  if (k < n) {
-    const double r = sg > 0 ? 1.0 / sg : 0.0;
-    double2* p = V + jd * vstride + c * n + k;
-    *p = make_double2(p->x * r, p->y * r);
+  const int np = gridDim.x;
+  const int64_t step = (int64_t)gridDim.y * np;
+  for (int i = 0; i < S; ++i) {
+    const double sg = sigma_of(part + i * step + c * np, np);
+    if (blockIdx.x == 0 && threadIdx.x == 0) sig[c * S + i] = sg;
+    if (k < n) {
+      const double r = sg > 0 ? 1.0 / sg : 0.0;
+      double2* p = Z + i * vstride + c * n + k;
+      *p = make_double2(p->x * r, p->y * r);
+    }
   }
 }
 
@@ -1381,6 +1422,151 @@ __global__ void __launch_bounds__(256) trmul_kernel(double2* __restrict__ Z, int
   }
 }
 
+// Both Cholesky QR passes of one right-hand side's block in one launch, the
+// S vectors held in LDS (S n complex: cholqr_lds below says when): Gram
+// matrix, its factor and inverse, Z <- Z R^{-1}, twice; Rt = R_2 R_1.  The
+// same breakdown rule as chol_kernel.  Bound by latency, not by its loads:
+// six launches of 8 to 18 us (91 us a block of iterations, 64 right-hand
+// sides, S = 8, 27 cells) became one of 31.
+template <int S>
+struct CholLds {
+  double2 red[32][S * (S + 1) / 2];  // Gram partials of each row of 16 lanes
+  double2 R[S][S], Ri[S][S], Rt[S][S];
+  int bad;
+};
+template <int S>
+__global__ void __launch_bounds__(512) cholqr_kernel(double2* __restrict__ Z, int64_t vstride, int64_t n,
+                                                     double2* __restrict__ Rt, GmresState st,
+                                                     int32_t* __restrict__ broken) {
+  constexpr int NP = S * (S + 1) / 2;
+  const int64_t c = blockIdx.x;
+  if (!st.active[c]) return;  // uniform over the block
+  extern __shared__ double2 zs[];  // [i * n + k]
+  __shared__ CholLds<S> L;
+  const int tid = threadIdx.x;
+  for (int i = 0; i < S; ++i)
+    for (int64_t k = tid; k < n; k += 512) zs[i * n + k] = Z[i * vstride + c * n + k];
+  for (int pass = 0; pass < 2; ++pass) {
+    __syncthreads();
+    double2 acc[NP];
+#pragma unroll
+    for (int e = 0; e < NP; ++e) acc[e] = make_double2(0, 0);
+    for (int64_t k = tid; k < n; k += 512) {
+      double2 z[S];
+#pragma unroll
+      for (int i = 0; i < S; ++i) z[i] = zs[i * n + k];
+#pragma unroll
+      for (int i = 0, e = 0; i < S; ++i)
+#pragma unroll
+        for (int q = i; q < S; ++q, ++e) {
+          acc[e].x = fma(z[i].x, z[q].x, fma(z[i].y, z[q].y, acc[e].x));
+          acc[e].y = fma(z[i].x, z[q].y, fma(-z[i].y, z[q].x, acc[e].y));
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < NP; ++e) {
+      const double2 v = make_double2(row16_total(acc[e].x), row16_total(acc[e].y));
+      if ((tid & 15) == 0) L.red[tid >> 4][e] = v;
+    }
+    __syncthreads();
+    if (tid < 64) {
+      // lane (i, q): G[i][q] (unit diagonal outside S x S), and row i of I
+      const int i = (tid / S) % S, q = tid % S, lo = min(i, q), hi = max(i, q);
+      double2 g = make_double2(0, 0);
+      for (int r = 0; r < 32; ++r) g = cadd(g, L.red[r][lo * S - lo * (lo - 1) / 2 + hi - lo]);
+      if (i > q) g.y = -g.y;
+      double2 y = make_double2(i == q ? 1.0 : 0.0, 0);
+      double gmax = 0, mine = 1.0;
+#pragma unroll
+      for (int k = 0; k < S; ++k) gmax = fmax(gmax, lane_value(g.x, k * S + k));
+      bool ok = gmax > 0;
+#pragma unroll
+      for (int k = 0; k < S; ++k) {
+        const double pk = lane_value(g.x, k * S + k);
+        ok = ok && pk > 1e-28 * gmax;  // uniform
+        const double inv = ok ? 1.0 / pk : 0.0;
+        if (i == k) mine = pk;
+        // row i > k loses conj(G[k][i]) / pk times row k of [G | I]
+        const double2 gi = make_double2(__shfl(g.x, k * S + i), -__shfl(g.y, k * S + i));
+        const double2 gq = make_double2(__shfl(g.x, k * S + q), __shfl(g.y, k * S + q));
+        const double2 yq = make_double2(__shfl(y.x, k * S + q), __shfl(y.y, k * S + q));
+        if (i > k) {
+          const double2 f = make_double2(gi.x * inv, gi.y * inv);
+          const double2 a = cmul(f, gq), b = cmul(f, yq);
+          g = make_double2(g.x - a.x, g.y - a.y);
+          y = make_double2(y.x - b.x, y.y - b.y);
+        }
+      }
+      const double f = ok ? 1.0 / sqrt(mine) : 0.0;
+      if (tid < S * S) {
+        L.R[i][q] = q >= i ? make_double2(g.x * f, q == i ? 0.0 : g.y * f) : make_double2(0, 0);
+        L.Ri[q][i] = q <= i ? make_double2(y.x * f, -y.y * f) : make_double2(0, 0);  // R^{-1} = (R^{-H})^H
+      }
+      if (tid == 0) L.bad = ok ? 0 : 1;
+    }
+    __syncthreads();
+    if (L.bad) {  // uniform
+      if (tid == 0) broken[c] = 1;
+      return;
+    }
+    double2 nt = make_double2(0, 0);
+    if (tid < S * S) {
+      const int i = tid / S, q = tid % S;
+      if (pass == 0)
+        nt = L.R[i][q];
+      else
+        for (int p = i; p <= q; ++p) nt = cadd(nt, cmul(L.R[i][p], L.Rt[p][q]));
+    }
+    for (int64_t k = tid; k < n; k += 512) {
+      double2 z[S];
+#pragma unroll
+      for (int i = 0; i < S; ++i) z[i] = zs[i * n + k];
+#pragma unroll
+      for (int i = 0; i < S; ++i) {
+        double2 a = make_double2(0, 0);
+#pragma unroll
+        for (int p = 0; p <= i; ++p) a = cadd(a, cmul(z[p], L.Ri[p][i]));
+        if (pass == 0)
+          zs[i * n + k] = a;
+        else
+          Z[i * vstride + c * n + k] = a;
+      }
+    }
+    __syncthreads();  // (every Rt entry read before any is replaced)
+    if (tid < S * S) {
+      L.Rt[tid / S][tid % S] = nt;
+      if (pass == 1) Rt[c * S * S + tid] = nt;
+    }
+  }
+}
+
+// Dynamic LDS of cholqr_kernel<S> for vectors of length n, or 0 where they do
+// not fit beside its own arrays (up to n = 1,100 for S = 8 and 2,500 for S =
+// 4; longer ones take the Gram, factor and product kernels).
+template <int S>
+static size_t cholqr_lds(int64_t n) {
+  static std::mutex mu;
+  static std::map<int, size_t> limit;  // per device, its attribute raised once
+  std::lock_guard<std::mutex> lk(mu);
+  int dev = 0;
+  CBFM_HIP(hipGetDevice(&dev));
+  auto it = limit.find(dev);
+  if (it == limit.end()) {
+    int most = 0;
+    CBFM_HIP(hipDeviceGetAttribute(&most, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    const size_t own = (sizeof(CholLds<S>) + 255) & ~(size_t)255;
+    size_t lim = (size_t)most > own ? (size_t)most - own : 0;
+    if (lim + own > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(&cholqr_kernel<S>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim) != hipSuccess) {
+      (void)hipGetLastError();
+      lim = own < 65536 ? 65536 - own : 0;
+    }
+    it = limit.emplace(dev, lim).first;
+  }
+  const size_t need = (size_t)S * n * sizeof(double2);
+  return need <= it->second ? need : 0;
+}
+
 // C1 += C2 over rows 0..j of every right-hand side (the two Gram-Schmidt
 // passes' coefficients, summed once per block of iterations)
 __global__ void csum_kernel(double2* __restrict__ C1, const double2* __restrict__ C2, int64_t cst, int S, int64_t j,
@@ -1426,9 +1612,9 @@ __global__ void __launch_bounds__(256) sstep_hcols_kernel(GmresState st, double2
                                                           const double2* __restrict__ Rt,
                                                           const double* __restrict__ sig,
                                                           const double2* __restrict__ theta,
-                                                          const int32_t* __restrict__ broken, int64_t j) {
+                                                          const int32_t* __restrict__ bad, int64_t j) {
   const int64_t c = blockIdx.y;
-  if (!st.active[c] || broken[c]) return;  // uniform over the block
+  if (!st.active[c] || bad[c]) return;  // uniform over the block
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   __shared__ double2 Tinv[S][S], Rs[S][S], th[S], cj[S];
   __shared__ double sg[S];
@@ -1501,14 +1687,18 @@ __global__ void __launch_bounds__(256) sstep_hcols_kernel(GmresState st, double2
 // broke down keeps the columns before this block and ends its cycle.
 template <int S>
 __global__ void __launch_bounds__(256) sstep_givens_kernel(GmresState st, const double2* __restrict__ H, int64_t M1,
-                                                           int64_t HS, const int32_t* __restrict__ broken, int64_t j,
-                                                           int64_t m, int64_t nrhs) {
+                                                           int64_t HS, const int32_t* __restrict__ bad,
+                                                           int32_t* __restrict__ broken, int64_t j, int64_t m,
+                                                           int64_t nrhs) {
   constexpr int T = 256 / S;  // threads per column
   const int64_t c = blockIdx.x;
   const int tid = threadIdx.x;
   if (!st.active[c]) return;  // uniform over the block
-  if (broken[c]) {
-    if (tid == 0) st.active[c] = 0;
+  if (bad[c]) {
+    if (tid == 0) {
+      broken[c] = 1;
+      st.active[c] = 0;
+    }
     return;
   }
   __shared__ double2 pc[S];
@@ -1675,18 +1865,51 @@ static std::vector<std::complex<double>> leja_order(std::vector<std::complex<dou
 struct SStep {
   int S;
   int64_t n, nrhs, m, M1, HS, cst;
-  Scratch C1, C2, G, Rinv, Rt, sig, theta, broken;
+  // C1, C2, Rt, sig, bad and seen: two of each, by the parity of the block
+  Scratch C1, C2, G, Rinv, Rt, sig, theta, broken, bad, seen, part;
   // the dot passes C = Q^H Z as products of the row-block GEMM, one per
   // right-hand side: descriptor 2 b + pass for block b (on the host and
   // the device) and the workspace of their K-split parts
   std::vector<GemmDesc> dots;
   std::unique_ptr<Scratch> dots_dev, dots_ws;
+  hipStream_t ls = nullptr;  // the least-squares stream (default priority)
+  hipEvent_t ev_ready[2] = {nullptr, nullptr}, ev_read[2] = {nullptr, nullptr};
   SStep(int S_, int64_t n_, int64_t nrhs_, int64_t m_, hipStream_t s)
       : S(S_), n(n_), nrhs(nrhs_), m(m_), M1(m_ + S_ + 1), HS((m_ + S_) * (m_ + S_ + 1)), cst(m_ + 1),
-        C1(nrhs_ * (m_ + 1) * S_ * sizeof(double2), s), C2(nrhs_ * (m_ + 1) * S_ * sizeof(double2), s),
+        C1(2 * nrhs_ * (m_ + 1) * S_ * sizeof(double2), s), C2(2 * nrhs_ * (m_ + 1) * S_ * sizeof(double2), s),
         G(nrhs_ * S_ * S_ * sizeof(double2), s), Rinv(nrhs_ * S_ * S_ * sizeof(double2), s),
-        Rt(nrhs_ * S_ * S_ * sizeof(double2), s), sig(nrhs_ * S_ * sizeof(double), s),
-        theta(nrhs_ * S_ * sizeof(double2), s), broken(nrhs_ * sizeof(int32_t), s) {}
+        Rt(2 * nrhs_ * S_ * S_ * sizeof(double2), s), sig(2 * nrhs_ * S_ * sizeof(double), s),
+        theta(nrhs_ * S_ * sizeof(double2), s), broken(nrhs_ * sizeof(int32_t), s),
+        bad(2 * nrhs_ * sizeof(int32_t), s), seen(2 * nrhs_ * sizeof(int32_t), s),
+        part(S_ * nrhs_ * ((n_ + 255) / 256) * sizeof(double), s) {
+    try {
+      CBFM_HIP(hipStreamCreateWithFlags(&ls, hipStreamNonBlocking));
+      for (int k = 0; k < 2; ++k) {
+        CBFM_HIP(hipEventCreateWithFlags(&ev_ready[k], hipEventDisableTiming));
+        CBFM_HIP(hipEventCreateWithFlags(&ev_read[k], hipEventDisableTiming));
+      }
+    } catch (...) {
+      close();
+      throw;
+    }
+  }
+  ~SStep() { close(); }
+  SStep(const SStep&) = delete;
+  SStep& operator=(const SStep&) = delete;
+  void close() {
+    if (ls) {
+      (void)hipStreamSynchronize(ls);
+      (void)hipStreamDestroy(ls);
+    }
+    for (int k = 0; k < 2; ++k) {
+      if (ev_ready[k]) (void)hipEventDestroy(ev_ready[k]);
+      if (ev_read[k]) (void)hipEventDestroy(ev_read[k]);
+    }
+  }
+  double2* c1(int par) const { return C1.as<double2>() + par * nrhs * cst * S; }
+  double2* c2(int par) const { return C2.as<double2>() + par * nrhs * cst * S; }
+  double2* rt(int par) const { return Rt.as<double2>() + par * nrhs * S * S; }
+  double* sg(int par) const { return sig.as<double>() + par * nrhs * S; }
   // block b (j = b S) of pass p: C_p[c][l][i] = sum_k conj(q_l[k]) z_i[k]
   // for l <= j, i < S, right-hand side c (q_l = V + l vstride + c n, the
   // block's z_i in the basis slots after q_j)
@@ -1698,7 +1921,7 @@ struct SStep {
       for (int p = 0; p < 2; ++p) {
         const int64_t j = b * S;
         GemmDesc d = gemm(V, vstride, OP_R, V + (j + 1) * vstride, vstride, OP_T,
-                          (p == 0 ? C1 : C2).as<double2>(), S, j + 1, S, n);
+                          p == 0 ? c1(b & 1) : c2(b & 1), S, j + 1, S, n);
         dots.push_back(d);
         ws = std::max(ws, panel_batch_ws_bytes(d, nrhs));
       }
@@ -1746,29 +1969,40 @@ static void sstep_shifts(SStep& ss, const GmresState& gs, int64_t m1, const std:
 // x += Q y.  Returns whether some right-hand side broke down (its cycle
 // then ends at the last complete block).
 static bool run_sstep_cycle(SStep& ss, const GemmPlan& matvec, double2* V, double2* u, int64_t vstride,
-                            int64_t max_iter, int64_t& total, GmresState gs, double* part, int np, PinnedFlags& flags,
-                            double2* x, double2* H, hipStream_t s) {
+                            int64_t max_iter, int64_t& total, GmresState gs, int np, PinnedFlags& flags, double2* x,
+                            double2* H, hipStream_t s) {
   const int S = ss.S;
   const int64_t n = ss.n, nrhs = ss.nrhs, m = ss.m;
   const int np256 = (int)((n + 255) / 256);
   CBFM_HIP(hipMemsetAsync(ss.broken.p, 0, nrhs * sizeof(int32_t), s));
+  CBFM_HIP(hipMemsetAsync(ss.bad.p, 0, 2 * nrhs * sizeof(int32_t), s));
+  for (int k = 0; k < 2; ++k)
+    CBFM_HIP(hipMemcpyAsync(ss.seen.as<int32_t>() + k * nrhs, gs.active, nrhs * sizeof(int32_t),
+                            hipMemcpyDeviceToDevice, s));
   auto all_done = [&](const int32_t* a) { return std::none_of(a, a + nrhs, [](int32_t v) { return v != 0; }); };
   int pending = 0;
   for (int64_t b = 0; b * S < m && total + S <= max_iter; ++b) {
     const int64_t j = b * S;
+    const int par = (int)(b & 1);
+    int32_t* bad = ss.bad.as<int32_t>() + par * nrhs;
+    // what block b - 2 left (or the start): the main stream's kernels take a
+    // right-hand side as long as it was active then
+    GmresState gm = gs;
+    gm.active = ss.seen.as<int32_t>() + par * nrhs;
+    if (b >= 2) CBFM_HIP(hipStreamWaitEvent(s, ss.ev_read[par], 0));
     for (int i = 1; i <= S; ++i) {  // z_i = (A - theta_i) z_{i-1} / sigma_i into slot j + i
       matvec.launch((size_t)(j + i - 1), s);
       hipLaunchKernelGGL(newton_kernel, dim3((unsigned)np256, (unsigned)nrhs), dim3(256), 0, s, u, V, vstride, n, j + i,
-                         ss.theta.as<double2>(), S, i - 1, gs, part);
-      hipLaunchKernelGGL(nscale_kernel, dim3((unsigned)np256, (unsigned)nrhs), dim3(256), 0, s, V, vstride, n, j + i,
-                         part, np256, ss.sig.as<double>(), S, i - 1, gs);
+                         ss.theta.as<double2>(), S, i - 1, gm, ss.part.as<double>());
     }
+    hipLaunchKernelGGL(nscale_kernel, dim3((unsigned)np256, (unsigned)nrhs), dim3(256), 0, s, V + (j + 1) * vstride,
+                       vstride, n, ss.part.as<double>(), ss.sg(par), S, gm);
     // two block Gram-Schmidt passes against q_0..q_j, then Cholesky QR twice
     double2* Z = V + (j + 1) * vstride;
     const int npu = (int)((n + 127) / 128);
     const double vb = 16.0 * (double)(j + 1) * (double)nrhs * (double)n;  // bytes of q_0..q_j
     for (int pass = 0; pass < 2; ++pass) {
-      double2* Cp = pass == 0 ? ss.C1.as<double2>() : ss.C2.as<double2>();
+      double2* Cp = pass == 0 ? ss.c1(par) : ss.c2(par);
       {
         TimedLaunch tl(T_GMRES_DOTS, s, vb + 16.0 * S * (double)nrhs * (double)n);
         const size_t di = (size_t)(2 * b + pass);
@@ -1778,51 +2012,67 @@ static bool run_sstep_cycle(SStep& ss, const GemmPlan& matvec, double2* V, doubl
         TimedLaunch tl(T_GMRES_UPDATE, s, vb + 32.0 * S * (double)nrhs * (double)n);
         if (S == 4)
           hipLaunchKernelGGL(block_update_kernel<4>, dim3((unsigned)(npu * nrhs)), dim3(512), 0, s, V, vstride, Z, n,
-                             j + 1, Cp, ss.cst, npu, gs);
+                             j + 1, Cp, ss.cst, npu, gm);
         else
           hipLaunchKernelGGL(block_update_kernel<8>, dim3((unsigned)(npu * nrhs)), dim3(512), 0, s, V, vstride, Z, n,
-                             j + 1, Cp, ss.cst, npu, gs);
+                             j + 1, Cp, ss.cst, npu, gm);
       }
     }
     const unsigned gr = (unsigned)(((S + 3) / 4) * nrhs);
     const dim3 gz((unsigned)((n + 255) / 256), (unsigned)nrhs);
-    for (int pass = 0; pass < 2; ++pass) {  // Cholesky QR, in place
+    const size_t lds = S == 4 ? cholqr_lds<4>(n) : cholqr_lds<8>(n);
+    if (lds > 0 && S == 4)
+      hipLaunchKernelGGL(cholqr_kernel<4>, dim3((unsigned)nrhs), dim3(512), lds, s, Z, vstride, n, ss.rt(par), gm,
+                         bad);
+    else if (lds > 0)
+      hipLaunchKernelGGL(cholqr_kernel<8>, dim3((unsigned)nrhs), dim3(512), lds, s, Z, vstride, n, ss.rt(par), gm,
+                         bad);
+    for (int pass = 0; lds == 0 && pass < 2; ++pass) {  // Cholesky QR, in place
       if (S == 4) {
         hipLaunchKernelGGL((block_dots_kernel<4, true>), dim3(gr), dim3(256), 0, s, Z, vstride, n, Z, vstride, n, n,
-                           (int64_t)S, ss.G.as<double2>(), (int64_t)S * S, gs);
+                           (int64_t)S, ss.G.as<double2>(), (int64_t)S * S, gm);
         hipLaunchKernelGGL(chol_kernel<4>, dim3((unsigned)nrhs), dim3(64), 0, s, ss.G.as<double2>(),
-                           ss.Rinv.as<double2>(), ss.Rt.as<double2>(), pass == 0, gs, ss.broken.as<int32_t>());
-        hipLaunchKernelGGL(trmul_kernel<4>, gz, dim3(256), 0, s, Z, vstride, n, ss.Rinv.as<double2>(), gs);
+                           ss.Rinv.as<double2>(), ss.rt(par), pass == 0, gm, bad);
+        hipLaunchKernelGGL(trmul_kernel<4>, gz, dim3(256), 0, s, Z, vstride, n, ss.Rinv.as<double2>(), gm);
       } else {
         hipLaunchKernelGGL((block_dots_kernel<8, true>), dim3(gr), dim3(256), 0, s, Z, vstride, n, Z, vstride, n, n,
-                           (int64_t)S, ss.G.as<double2>(), (int64_t)S * S, gs);
+                           (int64_t)S, ss.G.as<double2>(), (int64_t)S * S, gm);
         hipLaunchKernelGGL(chol_kernel<8>, dim3((unsigned)nrhs), dim3(64), 0, s, ss.G.as<double2>(),
-                           ss.Rinv.as<double2>(), ss.Rt.as<double2>(), pass == 0, gs, ss.broken.as<int32_t>());
-        hipLaunchKernelGGL(trmul_kernel<8>, gz, dim3(256), 0, s, Z, vstride, n, ss.Rinv.as<double2>(), gs);
+                           ss.Rinv.as<double2>(), ss.rt(par), pass == 0, gm, bad);
+        hipLaunchKernelGGL(trmul_kernel<8>, gz, dim3(256), 0, s, Z, vstride, n, ss.Rinv.as<double2>(), gm);
       }
     }
+    // this block's Hessenberg columns, rotations and stop tests on the second
+    // stream, beside block b + 1: serial chains of a few wavefronts for each
+    // right-hand side, 33 and 23 us of a block's 500 in the main stream (64
+    // right-hand sides, S = 8)
+    CBFM_HIP(hipEventRecord(ss.ev_ready[par], s));
+    CBFM_HIP(hipStreamWaitEvent(ss.ls, ss.ev_ready[par], 0));
+    const hipStream_t q = ss.ls;
     const unsigned nrb = (unsigned)((j + S + 1 + 63) / 64);
-    hipLaunchKernelGGL(csum_kernel, dim3((unsigned)(((j + 1) * S + 255) / 256), (unsigned)nrhs), dim3(256), 0, s,
-                       ss.C1.as<double2>(), ss.C2.as<double2>(), ss.cst, S, j, gs);
+    hipLaunchKernelGGL(csum_kernel, dim3((unsigned)(((j + 1) * S + 255) / 256), (unsigned)nrhs), dim3(256), 0, q,
+                       ss.c1(par), ss.c2(par), ss.cst, S, j, gs);
     if (S == 4) {
-      hipLaunchKernelGGL(sstep_hcols_kernel<4>, dim3(nrb, (unsigned)nrhs), dim3(256), 0, s, gs, H, ss.M1, ss.HS,
-                         ss.C1.as<double2>(), ss.cst, ss.Rt.as<double2>(), ss.sig.as<double>(), ss.theta.as<double2>(),
-                         ss.broken.as<int32_t>(), j);
-      hipLaunchKernelGGL(sstep_givens_kernel<4>, dim3((unsigned)nrhs), dim3(256), 0, s, gs, H, ss.M1, ss.HS,
-                         ss.broken.as<int32_t>(), j, m, nrhs);
+      hipLaunchKernelGGL(sstep_hcols_kernel<4>, dim3(nrb, (unsigned)nrhs), dim3(256), 0, q, gs, H, ss.M1, ss.HS,
+                         ss.c1(par), ss.cst, ss.rt(par), ss.sg(par), ss.theta.as<double2>(), bad, j);
+      hipLaunchKernelGGL(sstep_givens_kernel<4>, dim3((unsigned)nrhs), dim3(256), 0, q, gs, H, ss.M1, ss.HS,
+                         bad, ss.broken.as<int32_t>(), j, m, nrhs);
     } else {
-      hipLaunchKernelGGL(sstep_hcols_kernel<8>, dim3(nrb, (unsigned)nrhs), dim3(256), 0, s, gs, H, ss.M1, ss.HS,
-                         ss.C1.as<double2>(), ss.cst, ss.Rt.as<double2>(), ss.sig.as<double>(), ss.theta.as<double2>(),
-                         ss.broken.as<int32_t>(), j);
-      hipLaunchKernelGGL(sstep_givens_kernel<8>, dim3((unsigned)nrhs), dim3(256), 0, s, gs, H, ss.M1, ss.HS,
-                         ss.broken.as<int32_t>(), j, m, nrhs);
+      hipLaunchKernelGGL(sstep_hcols_kernel<8>, dim3(nrb, (unsigned)nrhs), dim3(256), 0, q, gs, H, ss.M1, ss.HS,
+                         ss.c1(par), ss.cst, ss.rt(par), ss.sg(par), ss.theta.as<double2>(), bad, j);
+      hipLaunchKernelGGL(sstep_givens_kernel<8>, dim3((unsigned)nrhs), dim3(256), 0, q, gs, H, ss.M1, ss.HS,
+                         bad, ss.broken.as<int32_t>(), j, m, nrhs);
     }
+    CBFM_HIP(hipMemcpyAsync(gm.active, gs.active, nrhs * sizeof(int32_t), hipMemcpyDeviceToDevice, q));
+    CBFM_HIP(hipEventRecord(ss.ev_read[par], q));
     CBFM_HIP(hipGetLastError());
     total += S;
     if (pending > 0 && all_done(flags.wait())) break;
-    flags.post(gs.active, s);
+    flags.post(gs.active, q);
     ++pending;
   }
+  for (hipEvent_t e : ss.ev_read)  // recorded by this cycle or an earlier one (or never: no wait)
+    CBFM_HIP(hipStreamWaitEvent(s, e, 0));
   hipLaunchKernelGGL(backsolve_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, gs, m, nrhs);
   hipLaunchKernelGGL(x_update_kernel<double2>, dim3((unsigned)((int64_t)np * nrhs)), dim3(512), 0, s, gs, V, vstride,
                      x, n, nrhs, np);
@@ -2031,7 +2281,7 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
       shifts_ready = true;
     } else if (sstep_on) {
       if (run_sstep_cycle(*sst, matvec, V.as<double2>(), u.as<double2>(), vstride, p.max_iter, total, gs,
-                          part.as<double>(), np, flags, x, gs.H, s))
+                          np, flags, x, gs.H, s))
         sstep_on = false;
     } else if (dense)
       run_cycle(matvec, dyn.get(), dyn ? dyn->desc(0) : nullptr, jdev.as<int64_t>(), V.as<double2>(),
