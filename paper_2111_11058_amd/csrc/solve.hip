@@ -111,13 +111,14 @@ __device__ inline double wave_sum(double x) {
 }
 
 // nrm[c] = ||u[c]|| (one block of 256 per vector); skipped for inactive vectors
-__global__ void __launch_bounds__(256) norm_kernel(const double2* __restrict__ u, int64_t n, double* __restrict__ nrm,
+template <typename TV>
+__global__ void __launch_bounds__(256) norm_kernel(const TV* __restrict__ u, int64_t n, double* __restrict__ nrm,
                                                    const int32_t* __restrict__ active) {
   const int64_t c = blockIdx.x;
   if (active && !active[c]) return;
   double s = 0;
   for (int64_t k = threadIdx.x; k < n; k += blockDim.x) {
-    const double2 a = u[c * n + k];
+    const double2 a = ld2(u + c * n + k);
     s += a.x * a.x + a.y * a.y;
   }
   s = wave_sum(s);
@@ -173,6 +174,15 @@ __global__ void sub_from_kernel(const double2* __restrict__ b, double2* __restri
 //   H[l][j] = h_l, H[j+1][j] = ||w||, q_{j+1} = w / ||w||
 // Column j-1 is final after the correction, so the Givens rotations and the
 // convergence test run one iteration behind the matrix-vector product.
+// All of this holds for any length of q_j before its correction: with raw
+// set, w itself is the next basis vector (H[j+1][j] = 1 until the correction
+// multiplies it by gamma), which takes the norm and the scaling pass out of
+// the iteration: product, dots, update, with the least-squares steps on a
+// second stream.  406 iterations of order 594, 8 right-hand sides: 17.8 ->
+// 13.2 ms; 272 of order 526, one: 9.8 -> 6.1; 666 of order 890, 8: 37.0 ->
+// 28.5.
+constexpr int kChunk = 4;           // iterations between convergence checks
+constexpr int kSlots = 2 * kChunk;  // iterations whose dots the column steps may still read
 struct GmresState {
   double2* R;       // rotated Hessenberg (upper triangular), per right-hand side: column j, row i at
                     // [c * (m + 1) * m + j * (m + 1) + i]
@@ -180,10 +190,11 @@ struct GmresState {
   double2* cs;      // [c * m + i]
   double2* sn;      // [c * m + i]
   double2* g;       // [i * nrhs + c], i <= m
+  // iteration j's in slot j % kSlots (pst entries apart, ab and gam nrhs)
   double2* d1;      // [i * nrhs + c]: a_i, alpha at i = j
   double2* d2;      // [i * nrhs + c]: b_i, beta at i = j
   double2* ab;      // [c] a^H b
-  double* gam;      // [c] gamma
+  double* gam;      // [c] gamma, -1 at a breakdown (1 is used)
   double* nrm;      // [c]
   double* bnorm;    // [c]
   double* res;      // [c] residual estimate / bnorm
@@ -193,34 +204,47 @@ struct GmresState {
   int32_t* its;     // [c] iterations spent (all cycles)
   // per right-hand side contiguous copies for the column step (one block
   // per right-hand side reads them along i): [c * (m + 1) + i]
-  double2* d1t;     // a_i, alpha
-  double2* d2t;     // b_i, beta
+  double2* d1t;     // a_i, alpha (slots as d1)
   double2* hc;      // the newest column of H (rows 0..j+1)
+  double2* pb;      // hbulk_kernel's sums, [t * pst + c * (m + 1) + l]
   int64_t ms;       // m + 1
-  // few right-hand sides: the update pass splits the basis range of each
-  // 128-row block over `split` blocks, which leave their sums (128 rows x
-  // the two sums) in ws at [((c np + rb) split + part) 256 + 128 s + 64 r +
-  // lane]; dcgs_finish_kernel adds them in part order and completes the
-  // update
-  int split;
-  double2* ws;
+  int64_t pst;      // entries of a slot
+  int raw;          // w is stored as the next basis vector as it is
+  __device__ double2* d1s(int64_t j) const { return d1 + j % kSlots * pst; }
+  __device__ double2* d2s(int64_t j) const { return d2 + j % kSlots * pst; }
 };
 
-// The end of the update of 128 rows of one right-hand side (one wavefront,
-// RPL = 2 rows per lane) once s1 = sum a_l q_l and s2 = sum b_l q_l are
-// known: q_j <- (q_j - s1) / gamma, w <- (w - s2) / gamma - c_j q_j, and
-// the partial sum of |w|^2 of these rows.
-template <typename TB, typename TW>
+// gamma and a^H b of iteration j from |a|^2, a^H b and alpha, kept for the
+// column steps by lane 0 of row block 0.  q_j nearly inside the span of
+// q_0..q_{j-1}: the Krylov space is (numerically) invariant, taken as a
+// breakdown.
+__device__ __forceinline__ double gamma_of(const GmresState& st, int64_t j, int64_t c, int64_t nrhs, int64_t rb,
+                                           int lane, double aa, double2 ab) {
+  const double alpha = st.d1s(j)[j * nrhs + c].x, g2 = alpha - aa;
+  const bool breakdown = !(g2 > 0.25 * alpha);
+  const double gam = breakdown ? 1.0 : sqrt(g2);
+  if (rb == 0 && lane == 0) {
+    st.gam[j % kSlots * nrhs + c] = breakdown ? -1.0 : gam;
+    st.ab[j % kSlots * nrhs + c] = ab;
+  }
+  return gam;
+}
+
+// The end of the update of 64 RPL rows of one right-hand side (one wavefront,
+// RPL rows per lane) once s1 = sum a_l q_l, s2 = sum b_l q_l, |a|^2 and a^H b
+// are known: q_j <- (q_j - s1) / gamma, w <- (w - s2) / gamma - c_j q_j, and
+// the partial sum of |w|^2 of these rows; or (raw) w as the next basis vector.
+template <int RPL, typename TB, typename TW>
 __device__ inline void finish_rows(TB* V, int64_t vstride, TW* w, int64_t n, int64_t nrhs, int64_t j, int64_t c,
-                                   int64_t rb, int np, const GmresState& st, const double2 (&s1)[2],
-                                   const double2 (&s2)[2], double* part, int lane) {
-  const double ig = 1.0 / st.gam[c];
-  const double2 beta = st.d2[j * nrhs + c], ab = st.ab[c];
+                                   int64_t rb, int np, const GmresState& st, const double2 (&s1)[RPL],
+                                   const double2 (&s2)[RPL], double aa, double2 ab, double* part, int lane) {
+  const double ig = 1.0 / gamma_of(st, j, c, nrhs, rb, lane, aa, ab);
+  const double2 beta = st.d2s(j)[j * nrhs + c];
   const double2 cj = cscale(make_double2(beta.x - ab.x, beta.y - ab.y), ig * ig);
   double q2 = 0;
 #pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int64_t k = (rb * 2 + r) * 64 + lane;
+  for (int r = 0; r < RPL; ++r) {
+    const int64_t k = (rb * RPL + r) * 64 + lane;
     if (k < n) {
       TB* qj = V + j * vstride + c * n + k;
       const double2 qo = ld2(qj);
@@ -229,10 +253,15 @@ __device__ inline void finish_rows(TB* V, int64_t vstride, TW* w, int64_t n, int
       const double2 wo = ld2(w + c * n + k);
       const double2 t = cmul(cj, qn);
       const double2 wn = make_double2((wo.x - s2[r].x) * ig - t.x, (wo.y - s2[r].y) * ig - t.y);
-      st2(w + c * n + k, wn);
-      q2 += wn.x * wn.x + wn.y * wn.y;
+      if (st.raw) {
+        st2(V + (j + 1) * vstride + c * n + k, wn);
+      } else {
+        st2(w + c * n + k, wn);
+        q2 += wn.x * wn.x + wn.y * wn.y;
+      }
     }
   }
+  if (st.raw) return;
   q2 = wave_sum(q2);
   if (lane == 0) part[c * np + rb] = q2;
 }
@@ -329,15 +358,14 @@ __global__ void __launch_bounds__(256) dots2_kernel(const TB* __restrict__ V, in
 #pragma unroll
     for (int q = 0; q < 4; ++q) r[q] = (sh[0][t][q] + sh[1][t][q]) + (sh[2][t][q] + sh[3][t][q]);
     const double2 v1 = make_double2(r[0], r[1]), v2 = make_double2(r[2], r[3]);
-    st.d1[(i0 + t) * nrhs + c] = v1;
-    st.d2[(i0 + t) * nrhs + c] = v2;
-    st.d1t[c * st.ms + i0 + t] = v1;
-    st.d2t[c * st.ms + i0 + t] = v2;
+    st.d1s(j)[(i0 + t) * nrhs + c] = v1;
+    st.d2s(j)[(i0 + t) * nrhs + c] = v2;
+    st.d1t[j % kSlots * st.pst + c * st.ms + i0 + t] = v1;
   }
 }
 
-// Per right-hand side (one block of 256 threads each): gamma and a^H b,
-// then column jc = j - 1 made final (corrected for the new q_j unless
+// Per right-hand side (one block of 256 threads each): column jc = j - 1
+// made final (corrected for the new q_j, whose gamma the update left, unless
 // correct == 0, the end of a cycle, when it is taken as it stands) and
 // reduced by the Givens rotations; the new rotation updates g and the
 // convergence test.
@@ -346,22 +374,17 @@ __global__ void __launch_bounds__(256) dots2_kernel(const TB* __restrict__ V, in
 // follow an affine recurrence, so each thread composes the maps of a
 // contiguous run of rotations (at most four up to 1024 columns), a scan over
 // the block gives every run its incoming a_i, and the runs are then replayed
-// in parallel.  The kernel is bound by memory latency: every load a thread
+// in parallel.  The step is bound by memory latency: every load a thread
 // needs is issued before its first wait (up to 1024 columns), so it waits
-// on memory about once instead of once per step.
-__global__ void __launch_bounds__(256) column_kernel(GmresState st, int64_t m, int64_t j, int64_t nrhs,
-                                                      int correct, const int64_t* __restrict__ jp) {
-  if (jp) j = *jp;
-  const int64_t c = (int64_t)blockIdx.x;
+// on memory about once instead of once per rotation.
+__device__ __forceinline__ void column_step(const GmresState& st, int64_t m, int64_t j, int64_t c, int64_t nrhs,
+                                            int correct) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  if (c >= nrhs) return;
   // this right-hand side's contiguous vectors
-  const double2* d1 = st.d1t + c * st.ms;
-  const double2* d2 = st.d2t + c * st.ms;
+  const double2* d1 = st.d1t + j % kSlots * st.pst + c * st.ms;
   const double2* hcol = st.hc + c * st.ms;
   double2* sn = st.sn + c * m;
   double2* cs = st.cs + c * m;
-  __shared__ double red[4][3];
   __shared__ double2 tot[4][2];     // (P, Q) of each wavefront's runs
   __shared__ double2 incl[256][2];  // (P, Q) of runs 0..t
   __shared__ double2 afin;
@@ -370,15 +393,9 @@ __global__ void __launch_bounds__(256) column_kernel(GmresState st, int64_t m, i
   const int64_t K = (jc + 255) / 256;
   const int64_t i0 = std::min<int64_t>(jc, t * K), i1 = std::min<int64_t>(jc, i0 + K);
   // ---- loads (indices clamped to valid entries; the unused ones discarded)
-  double2 da[KR], db[KR];  // a_l, b_l of iteration j for l = t + 256 u
-#pragma unroll
-  for (int u = 0; u < KR; ++u) {
-    const int64_t l = t + 256 * u < j ? t + 256 * u : 0;
-    da[u] = d1[l];
-    db[u] = d2[l];
-  }
-  const double alpha = d1[j].x;
-  const double2 hs = hcol[jc + 1];  // H[jc+1][jc], real
+  const double gl = st.gam[j % kSlots * nrhs + c], nu = st.nrm[c];
+  // H[jc+1][jc], real; raw: 1, or the norm of the last basis vector
+  const double2 hs = st.raw ? make_double2(correct ? 1.0 : nu, 0.0) : hcol[jc + 1];
   const double2 h0 = hcol[0], a00 = d1[0], gj = st.g[jc * nrhs + c];
   const double tgt = st.tgt[c], bnorm = st.bnorm[c];
   double2 sv[KR], cv[KR], bv[KR];  // first KR rotations of this thread's run
@@ -390,48 +407,9 @@ __global__ void __launch_bounds__(256) column_kernel(GmresState st, int64_t m, i
     bv[u] = hcol[i + 1];
     if (correct) bv[u] = cadd(bv[u], cmul(hs, d1[i + 1]));
   }
-  // (the loads above are issued for converged right-hand sides too: the
-  // test comes after them so that it does not delay them)
-  if (!st.active[c]) return;  // uniform over the block
-  // ---- gamma and a^H b
-  double gam = 1.0;
-  bool breakdown = false;
-  if (correct) {
-    double aa = 0;
-    double2 ab = make_double2(0, 0);
-#pragma unroll
-    for (int u = 0; u < KR; ++u)
-      if (t + 256 * u < j) {
-        aa += da[u].x * da[u].x + da[u].y * da[u].y;
-        ab = cadd(ab, cconjmul(da[u], db[u]));
-      }
-    for (int64_t l = t + 256 * KR; l < j; l += 256) {
-      const double2 a = d1[l];
-      aa += a.x * a.x + a.y * a.y;
-      ab = cadd(ab, cconjmul(a, d2[l]));
-    }
-    aa = wave_sum(aa);
-    ab = make_double2(wave_sum(ab.x), wave_sum(ab.y));
-    if (lane == 0) {
-      red[wv][0] = aa;
-      red[wv][1] = ab.x;
-      red[wv][2] = ab.y;
-    }
-    __syncthreads();
-    aa = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
-    ab = make_double2((red[0][1] + red[1][1]) + (red[2][1] + red[3][1]),
-                      (red[0][2] + red[1][2]) + (red[2][2] + red[3][2]));
-    const double g2 = alpha - aa;
-    // q_j nearly inside the span of q_0..q_{j-1}: the Krylov space is
-    // (numerically) invariant, taken as a breakdown
-    breakdown = !(g2 > 0.25 * alpha);
-    gam = breakdown ? 1.0 : sqrt(g2);
-    if (t == 0) {
-      st.gam[c] = gam;
-      st.ab[c] = ab;
-    }
-  }
   if (j == 0) return;
+  const bool breakdown = correct && gl < 0;
+  const double gam = fabs(gl);
   const double hsub = correct ? (breakdown ? 0.0 : hs.x * gam) : hs.x;
   // ---- compose the maps of this thread's run
   double2 P = make_double2(1, 0), Q = make_double2(0, 0);
@@ -543,97 +521,78 @@ __global__ void __launch_bounds__(256) column_kernel(GmresState st, int64_t m, i
   if (ra <= tgt || den == 0.0 || breakdown) st.active[c] = 0;
 }
 
-// The update pass, with column j of H computed beside it.  With
-// p_l = sum_i H[l][i] a_i over the final columns i < j (upper Hessenberg:
-// i >= l - 1), h_l = (b_l - p_l) / gamma, h_j = ((beta - a^H b) / gamma -
-// p_j) / gamma and c_l = p_l / gamma + h_l, the update coefficients reduce
-// to c_l = b_l / gamma (l < j) and c_j = (beta - a^H b) / gamma^2, so the
-// update does not wait for p:
+// The least-squares steps of iterations j0..j0+cnt-1 of one right-hand side:
+// for each, column j - 1 made final and rotated, then column j from the sums
+// that hbulk_kernel left over the columns before j0 - 1 and the (at most
+// kChunk) columns since.  A chunk of iterations in one launch: two launches
+// instead of eight, whose host time alone (5 us each) exceeded the device's
+// on small systems (118 iterations of order 156: 4.8 ms with a launch per
+// step, 2.6).  correct == 0: the end of a cycle, column j0 - 1 alone.
+__global__ void __launch_bounds__(256) columns_kernel(GmresState st, int64_t m, int64_t j0, int cnt, int64_t nrhs,
+                                                      int correct, int32_t* __restrict__ seen,
+                                                      const int64_t* __restrict__ jp) {
+  if (jp) j0 = *jp;
+  const int64_t c = (int64_t)blockIdx.x;
+  const int tid = threadIdx.x;
+  bool act = st.active[c] != 0;
+  for (int t = 0; t < cnt && act; ++t) {  // act: uniform over the block
+    const int64_t j = j0 + t;
+    column_step(st, m, j, c, nrhs, correct);
+    __syncthreads();
+    act = st.active[c] != 0;
+    if (!correct || !act) break;
+    const double ig = 1.0 / fabs(st.gam[j % kSlots * nrhs + c]);
+    const double2 ab = st.ab[j % kSlots * nrhs + c];
+    const double2* a = st.d1t + j % kSlots * st.pst + c * st.ms;
+    const double2* b = st.d2s(j) + c;
+    const double2* P = st.pb + t * st.pst + c * st.ms;
+    const int64_t f = j0 > 0 ? j0 - 1 : 0;  // first column that the sums lack
+    for (int64_t l = tid; l <= j; l += 256) {
+      double2 p = f > 0 && l <= f ? P[l] : make_double2(0, 0);
+      for (int64_t i = std::max<int64_t>(f, l - 1); i < j; ++i) p = cadd(p, cmul(st.H[(l * m + i) * nrhs + c], a[i]));
+      const double2 bl = b[l * nrhs];
+      const double2 h = l < j ? cscale(make_double2(bl.x - p.x, bl.y - p.y), ig)
+                              : cscale(make_double2((bl.x - ab.x) * ig - p.x, (bl.y - ab.y) * ig - p.y), ig);
+      st.H[(l * m + j) * nrhs + c] = h;
+      st.hc[c * st.ms + l] = h;
+    }
+    __syncthreads();
+  }
+  if (seen && tid == 0) seen[c] = act ? 1 : 0;
+}
+
+// The update pass.  With p_l = sum_i H[l][i] a_i over the final columns i < j
+// (upper Hessenberg: i >= l - 1), h_l = (b_l - p_l) / gamma, h_j = ((beta -
+// a^H b) / gamma - p_j) / gamma and c_l = p_l / gamma + h_l, the update
+// coefficients reduce to c_l = b_l / gamma (l < j) and c_j = (beta - a^H b) /
+// gamma^2, so the update waits neither for p nor for the rotations
+// (hbulk_kernel and columns_kernel, off the critical path):
 //   q_j <- (q_j - sum_{i<j} a_i q_i) / gamma
 //   w   <- (w - sum_{i<j} b_i q_i) / gamma - c_j q_j(new)
-// Blocks [0, np nrhs split): eight wavefronts take 128 consecutive rows (two
-// per lane) of one right-hand side, wavefront v summing over the basis
-// vectors i = v mod 8 (with split > 1, part p of the row block over those
-// with i / 8 = p mod split); wavefront 0 combines the partial sums in a
-// fixed order and completes the update, storing the row block's sum of
-// |w|^2 in part (with split > 1, dcgs_finish_kernel does this).
-// Blocks from np nrhs split on: row l of column j; the lanes take up to 64
-// right-hand sides and, when there are fewer, several column offsets each
-// (added by a butterfly); the eight wavefronts take interleaved columns of
-// the row (contiguous in H), four columns in flight each, summed in a fixed
-// order.  These latency-bound blocks come last, where they fill
-// the tail of the streaming; placed first they held CUs the update blocks
-// needed, and cutting the rows into parts or running them as a separate
-// launch or stream measured slower too.
-template <typename TB, typename TW, bool SPLIT>
-__global__ void __launch_bounds__(512) dcgs_update_kernel(TB* __restrict__ V, int64_t vstride,
-                                                          TW* __restrict__ w, int64_t n, int64_t nrhs, int64_t m,
-                                                          int64_t j, int np, GmresState st,
-                                                          double* __restrict__ part, const int64_t* __restrict__ jp) {
+// W wavefronts take 64 RPL consecutive rows (RPL per lane) of one right-hand
+// side, wavefront v summing over the basis vectors i = v mod W, and |a|^2 and
+// a^H b beside them; wavefront 0 combines the partial sums in a fixed order
+// and completes the update, storing the row block's sum of |w|^2 in part.
+// Sixteen wavefronts of one row per lane where eight of two would leave CUs
+// without a block: 594 rows x 8 right-hand sides 12.3 -> 8.5 us; 4,480 x 1
+// 5.3 and 9.3 (the basis range split over eight blocks, and a pass adding
+// their sums) -> 5.8.
+template <typename TB, typename TW, int RPL>
+__global__ void __launch_bounds__(1024 / RPL) dcgs_update_kernel(TB* __restrict__ V, int64_t vstride,
+                                                                 TW* __restrict__ w, int64_t n, int64_t nrhs,
+                                                                 int64_t j, int np, GmresState st,
+                                                                 double* __restrict__ part,
+                                                                 const int64_t* __restrict__ jp) {
+  constexpr int W = 16 / RPL;
   if (jp) j = *jp;
   // wv is uniform over the wavefront: the coefficient loads below go through scalar loads
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int S = SPLIT ? st.split : 1;
-  const int64_t nub = (int64_t)np * nrhs * S;  // update blocks
-  if ((int64_t)blockIdx.x >= nub) {
-    __shared__ double2 shp[7][64];
-    const int64_t hb = (int64_t)blockIdx.x - nub;
-    const int64_t ng = (nrhs + 63) / 64;
-    // lanes: cw right-hand sides (a power of two, at least nrhs when nrhs <
-    // 64) times 64 / cw column offsets, so that few right-hand sides still
-    // fill the wavefront; with 64 or more, one column offset per lane group
-    int cw = 64;
-    while (cw > 1 && cw / 2 >= nrhs) cw >>= 1;
-    const int sub = 64 / cw, lc = lane & (cw - 1), li = lane / cw;
-    const int64_t l = hb / ng, c = (hb % ng) * 64 + lc;
-    if (l > j) return;  // graph replays launch the rows of the longest column
-    const bool on = c < nrhs && st.active[c];
-    const int64_t cc = on ? c : 0;  // idle lanes read valid entries and discard them
-    const int64_t lo = l > 0 ? l - 1 : 0;
-    const double2* Hl = st.H + l * m * nrhs + cc;  // column i at Hl[i * nrhs]: the row is contiguous
-    const double2* a = st.d1 + cc;
-    double2 acc[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc[u] = make_double2(0, 0);
-    const int64_t istep = 8 * (int64_t)sub;  // column stride of one unrolled load
-    for (int64_t ib = lo + wv * sub + li; ib < j; ib += 4 * istep) {
-      double2 hv[4], av[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t i = ib + istep * u < j ? ib + istep * u : ib;
-        hv[u] = Hl[i * nrhs];
-        av[u] = a[i * nrhs];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc[u] = ib + istep * u < j ? cadd(acc[u], cmul(hv[u], av[u])) : acc[u];
-    }
-    double2 p = cadd(cadd(acc[0], acc[1]), cadd(acc[2], acc[3]));
-    for (int off = cw; off < 64; off <<= 1)  // the column offsets of one right-hand side
-      p = make_double2(p.x + __shfl_xor(p.x, off, 64), p.y + __shfl_xor(p.y, off, 64));
-    if (wv > 0) shp[wv - 1][lane] = p;
-    __syncthreads();
-    if (wv > 0 || !on || li != 0) return;
-    for (int v = 0; v < 7; ++v) p = cadd(p, shp[v][lane]);
-    const double ig = 1.0 / st.gam[c];
-    const double2 b = st.d2[l * nrhs + c];
-    double2 h;
-    if (l < j) {
-      h = cscale(make_double2(b.x - p.x, b.y - p.y), ig);
-    } else {
-      const double2 ab = st.ab[c];
-      h = cscale(make_double2((b.x - ab.x) * ig - p.x, (b.y - ab.y) * ig - p.y), ig);
-    }
-    st.H[(l * m + j) * nrhs + c] = h;
-    st.hc[c * st.ms + l] = h;
-    return;
-  }
-  constexpr int RPL = 2;  // rows per lane (finish_rows takes two)
-  const int part_id = (int)(blockIdx.x % S);
-  const int64_t c = (int64_t)(blockIdx.x / S) / np, rb = (int64_t)(blockIdx.x / S) % np;
+  const int64_t c = blockIdx.x / np, rb = blockIdx.x % np;
   if (c >= nrhs || !st.active[c]) return;  // uniform over the block
-  const double2* d1 = st.d1;
-  const double2* d2 = st.d2;
-  double2 s1[RPL], s2[RPL];
+  const double2* d1 = st.d1s(j);
+  const double2* d2 = st.d2s(j);
+  double2 s1[RPL], s2[RPL], ab = make_double2(0, 0);
+  double aa = 0;
   int64_t kk[RPL];
 #pragma unroll
   for (int r = 0; r < RPL; ++r) {
@@ -642,92 +601,138 @@ __global__ void __launch_bounds__(512) dcgs_update_kernel(TB* __restrict__ V, in
     kk[r] = k < n ? k : 0;  // rows past n: a valid row, discarded
   }
   const TB* base = V + c * n;
-  // this block's basis vectors: i = 8 (part + S t) + wavefront
-  const int64_t istep = 8 * (int64_t)S;
-  int64_t i = wv + 8 * (int64_t)part_id;
+  int64_t i = wv;
   // U basis vectors at a time (4; 8 for a float basis beside a double w,
   // the same bytes in flight, measured 201 -> 184 us on 4,224 rows x 32
   // right-hand sides): their loads go out together (the sums still take
   // the vectors in order)
   constexpr int U = sizeof(TB) < sizeof(TW) ? 8 : 4;
-  for (; i + (U - 1) * istep < j; i += U * istep) {
+  for (; i + (U - 1) * W < j; i += U * W) {
     double2 a[U], b[U], v[U][RPL];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      a[u] = d1[(i + istep * u) * nrhs + c];
-      b[u] = d2[(i + istep * u) * nrhs + c];
+      a[u] = d1[(i + W * u) * nrhs + c];
+      b[u] = d2[(i + W * u) * nrhs + c];
 #pragma unroll
-      for (int r = 0; r < RPL; ++r) v[u][r] = ld2(base + (i + istep * u) * vstride + kk[r]);
+      for (int r = 0; r < RPL; ++r) v[u][r] = ld2(base + (i + W * u) * vstride + kk[r]);
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) {
+      aa += a[u].x * a[u].x + a[u].y * a[u].y;
+      ab = cadd(ab, cconjmul(a[u], b[u]));
 #pragma unroll
       for (int r = 0; r < RPL; ++r) {
         s1[r] = cadd(s1[r], cmul(a[u], v[u][r]));
         s2[r] = cadd(s2[r], cmul(b[u], v[u][r]));
       }
+    }
   }
-  for (; i < j; i += istep) {
+  for (; i < j; i += W) {
     const double2 a = d1[i * nrhs + c], b = d2[i * nrhs + c];
     double2 v[RPL];
 #pragma unroll
     for (int r = 0; r < RPL; ++r) v[r] = ld2(base + i * vstride + kk[r]);
+    aa += a.x * a.x + a.y * a.y;
+    ab = cadd(ab, cconjmul(a, b));
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
       s1[r] = cadd(s1[r], cmul(a, v[r]));
       s2[r] = cadd(s2[r], cmul(b, v[r]));
     }
   }
-  __shared__ double2 sh[7][RPL][64][2];
+  __shared__ double2 sh[W - 1][RPL][64][2];
+  __shared__ double shg[W - 1][3];
   if (wv > 0) {
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
       sh[wv - 1][r][lane][0] = s1[r];
       sh[wv - 1][r][lane][1] = s2[r];
     }
+    if (lane == 0) {
+      shg[wv - 1][0] = aa;
+      shg[wv - 1][1] = ab.x;
+      shg[wv - 1][2] = ab.y;
+    }
   }
   __syncthreads();
   if (wv > 0) return;
+#pragma unroll 3
+  for (int t = 0; t < W - 1; ++t) {
 #pragma unroll
-  for (int r = 0; r < RPL; ++r)
-    for (int t = 0; t < 7; ++t) {
+    for (int r = 0; r < RPL; ++r) {
       s1[r] = cadd(s1[r], sh[t][r][lane][0]);
       s2[r] = cadd(s2[r], sh[t][r][lane][1]);
     }
-  if (SPLIT) {  // dcgs_finish_kernel completes the update
-    double2* mine = st.ws + (((c * np + rb) * S) + part_id) * 256;
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-      mine[64 * r + lane] = s1[r];
-      mine[128 + 64 * r + lane] = s2[r];
-    }
-    return;
+    aa += shg[t][0];
+    ab = make_double2(ab.x + shg[t][1], ab.y + shg[t][2]);
   }
-  finish_rows(V, vstride, w, n, nrhs, j, c, rb, np, st, s1, s2, part, lane);
+  finish_rows<RPL>(V, vstride, w, n, nrhs, j, c, rb, np, st, s1, s2, aa, ab, part, lane);
 }
 
-// The update of a split pass: one wavefront per 128-row block of a
-// right-hand side adds the parts' sums in part order and completes it.
-template <typename TB, typename TW>
-__global__ void __launch_bounds__(64) dcgs_finish_kernel(TB* __restrict__ V, int64_t vstride, TW* __restrict__ w,
-                                                          int64_t n, int64_t nrhs, int64_t j, int np, GmresState st,
-                                                          double* __restrict__ part, const int64_t* __restrict__ jp) {
-  if (jp) j = *jp;
-  const int lane = threadIdx.x;
-  const int64_t c = (int64_t)blockIdx.x / np, rb = (int64_t)blockIdx.x % np;
-  if (c >= nrhs || !st.active[c]) return;
-  const int S = st.split;
-  const double2* sums = st.ws + (c * np + rb) * S * 256;
-  double2 s1[2], s2[2];
+// The sums over the columns i < f = j0 - 1 of H (final before the chunk) of
+// p^t_l = sum_i H[l][i] a^t_i for the chunk's iterations j0 + t: block l is
+// row l <= f; the lanes take up to 64 right-hand sides and, when there are
+// fewer, several column offsets each (added by a butterfly); the eight
+// wavefronts take interleaved columns of the row (contiguous in H, read once
+// for the chunk), two columns in flight each, summed in a fixed order.
+__global__ void __launch_bounds__(512) hbulk_kernel(int64_t nrhs, int64_t m, int64_t j0, int cnt, GmresState st,
+                                                    const int64_t* __restrict__ jp) {
+  if (jp) j0 = *jp;
+  const int64_t f = j0 - 1;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ double2 shp[7][kChunk][64];
+  const int64_t ng = (nrhs + 63) / 64;
+  // lanes: cw right-hand sides (a power of two, at least nrhs when nrhs <
+  // 64) times 64 / cw column offsets, so that few right-hand sides still
+  // fill the wavefront; with 64 or more, one column offset per lane group
+  int cw = 64;
+  while (cw > 1 && cw / 2 >= nrhs) cw >>= 1;
+  const int sub = 64 / cw, lc = lane & (cw - 1), li = lane / cw;
+  const int64_t l = blockIdx.x / ng, c = (blockIdx.x % ng) * 64 + lc;
+  if (l > f || f <= 0) return;  // graph replays launch the rows of the longest column
+  const bool on = c < nrhs && st.active[c];
+  const int64_t cc = on ? c : 0;  // idle lanes read valid entries and discard them
+  const int64_t lo = l > 0 ? l - 1 : 0;
+  const double2* Hl = st.H + l * m * nrhs + cc;  // column i at Hl[i * nrhs]: the row is contiguous
+  const double2* a[kChunk];
+  double2 acc[kChunk];
 #pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    s1[r] = s2[r] = make_double2(0, 0);
-    for (int q = 0; q < S; ++q) {
-      s1[r] = cadd(s1[r], sums[q * 256 + 64 * r + lane]);
-      s2[r] = cadd(s2[r], sums[q * 256 + 128 + 64 * r + lane]);
+  for (int t = 0; t < kChunk; ++t) {
+    a[t] = st.d1s(j0 + (t < cnt ? t : 0)) + cc;
+    acc[t] = make_double2(0, 0);
+  }
+  const int64_t istep = 8 * (int64_t)sub;  // column stride of one unrolled load
+  for (int64_t ib = lo + wv * sub + li; ib < f; ib += 2 * istep) {
+    const bool two = ib + istep < f;
+    const int64_t i2 = two ? ib + istep : ib;
+    const double2 h1 = Hl[ib * nrhs], h2 = Hl[i2 * nrhs];
+    double2 a1[kChunk], a2[kChunk];
+#pragma unroll
+    for (int t = 0; t < kChunk; ++t) {
+      a1[t] = a[t][ib * nrhs];
+      a2[t] = a[t][i2 * nrhs];
+    }
+#pragma unroll
+    for (int t = 0; t < kChunk; ++t) {
+      acc[t] = cadd(acc[t], cmul(h1, a1[t]));
+      acc[t] = two ? cadd(acc[t], cmul(h2, a2[t])) : acc[t];
     }
   }
-  finish_rows(V, vstride, w, n, nrhs, j, c, rb, np, st, s1, s2, part, lane);
+#pragma unroll
+  for (int t = 0; t < kChunk; ++t) {
+    for (int off = cw; off < 64; off <<= 1)  // the column offsets of one right-hand side
+      acc[t] = make_double2(acc[t].x + __shfl_xor(acc[t].x, off, 64), acc[t].y + __shfl_xor(acc[t].y, off, 64));
+    if (wv > 0) shp[wv - 1][t][lane] = acc[t];
+  }
+  __syncthreads();
+  if (wv > 0 || !on || li != 0) return;
+#pragma unroll
+  for (int t = 0; t < kChunk; ++t) {
+    if (t >= cnt) break;
+    double2 p = acc[t];
+    for (int v = 0; v < 7; ++v) p = cadd(p, shp[v][t][lane]);
+    st.pb[t * st.pst + c * st.ms + l] = p;
+  }
 }
 
 // nu = sqrt(sum of the np partial sums of |w|^2); H[j+1][j] = nu and
@@ -1039,6 +1044,42 @@ static void apply_op(const double2* A, int64_t lda, int64_t n, int64_t nrhs, con
   zgemm_batched(d, s);
 }
 
+// The second stream of plain cycles (default priority), its events and the
+// copies of the active flags that the main stream's kernels read, two of each
+// by the parity of the chunk.
+struct ColumnSide {
+  hipStream_t ls = nullptr;
+  hipEvent_t ev_ready[2] = {nullptr, nullptr}, ev_done[2] = {nullptr, nullptr};
+  int64_t nrhs;
+  Scratch flags;
+  ColumnSide(int64_t nrhs_, hipStream_t s) : nrhs(nrhs_), flags(2 * nrhs_ * sizeof(int32_t), s) {
+    try {
+      CBFM_HIP(hipStreamCreateWithFlags(&ls, hipStreamNonBlocking));
+      for (int k = 0; k < 2; ++k) {
+        CBFM_HIP(hipEventCreateWithFlags(&ev_ready[k], hipEventDisableTiming));
+        CBFM_HIP(hipEventCreateWithFlags(&ev_done[k], hipEventDisableTiming));
+      }
+    } catch (...) {
+      close();
+      throw;
+    }
+  }
+  ~ColumnSide() { close(); }
+  ColumnSide(const ColumnSide&) = delete;
+  ColumnSide& operator=(const ColumnSide&) = delete;
+  void close() {
+    if (ls) {
+      (void)hipStreamSynchronize(ls);
+      (void)hipStreamDestroy(ls);
+    }
+    for (int k = 0; k < 2; ++k) {
+      if (ev_ready[k]) (void)hipEventDestroy(ev_ready[k]);
+      if (ev_done[k]) (void)hipEventDestroy(ev_done[k]);
+    }
+  }
+  int32_t* seen(int k) const { return flags.as<int32_t>() + k * nrhs; }
+};
+
 // One GMRES cycle from the normalised residual in V[0]: up to mres Arnoldi
 // iterations (the matrix-vector products by mv.launch(j)), the last column,
 // the triangular solve and x += Q y.  total counts the iterations of all
@@ -1052,14 +1093,26 @@ static void apply_op(const double2* A, int64_t lda, int64_t n, int64_t nrhs, con
 template <typename TB, typename TW, typename MV>
 static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev, TB* V, TW* w, int64_t vstride,
                       int64_t n, int64_t nrhs, int64_t mres, int64_t max_iter, int64_t& total, GmresState gs,
-                      double* part, int np, PinnedFlags& flags, double2* x, hipStream_t s, const TB* xb = nullptr,
-                      double2* qd = nullptr) {
+                      double* part, int np, PinnedFlags& flags, double2* x, hipStream_t s, ColumnSide* side,
+                      const TB* xb = nullptr, double2* qd = nullptr) {
   const double vb = (double)sizeof(TB), wb = (double)sizeof(TW);
-  const int check_every = 4;
+  constexpr int check_every = kChunk;
+  // w is kept as the next basis vector unless that rounds it to another
+  // type (its range), or the iterate is built from another basis
+  gs.raw = std::is_same<TB, TW>::value && xb == nullptr;
   const int64_t ng = (nrhs + 63) / 64;
   auto all_done = [&](const int32_t* a) { return std::none_of(a, a + nrhs, [](int32_t v) { return v != 0; }); };
+  // 64-row update blocks where 128-row ones would not give every CU one
+  const int np64 = (int64_t)np * nrhs < 256 ? (int)((n + 63) / 64) : 0;
+  // the least-squares steps of iterations j..j+cnt-1
+  auto columns = [&](int64_t j, int cnt, const int64_t* jp, int32_t* seen, hipStream_t q) {
+    const int64_t rows = jp ? mres : j;
+    if (rows > 1)
+      hipLaunchKernelGGL(hbulk_kernel, dim3((unsigned)(rows * ng)), dim3(512), 0, q, nrhs, mres, j, cnt, gs, jp);
+    hipLaunchKernelGGL(columns_kernel, dim3((unsigned)nrhs), dim3(256), 0, q, gs, mres, j, cnt, nrhs, 1, seen, jp);
+  };
   // enqueue iteration j (jp == nullptr) or the iteration *jp (graph capture)
-  auto iteration = [&](int64_t j, const int64_t* jp, hipStream_t q) {
+  auto iteration = [&](int64_t j, const int64_t* jp, const GmresState& gs, hipStream_t q) {
     const int64_t jg = jp ? mres - 1 : j;  // grids cover the longest column
     if (jp) {
       if constexpr (std::is_same<TB, TW>::value) {
@@ -1081,34 +1134,34 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
         hipLaunchKernelGGL((dots2_kernel<TB, TW, false>), dim3((unsigned)((jg + 4) / 4 * nrhs)), dim3(256), 0, q, V,
                            vstride, w, n, nrhs, j, gs, jp);
     }
-    hipLaunchKernelGGL(column_kernel, dim3((unsigned)nrhs), dim3(256), 0, q, gs, mres, j, nrhs, 1, jp);
     {
-      // work: bytes of q_0..q_{j-1} read, q_j and w read and written, and
-      // the j + j (j + 1) / 2 entries of H read for p = H a
-      const double hr = (double)j + 0.5 * (double)j * (double)(j + 1);
-      TimedLaunch tl(T_GMRES_UPDATE, q, ((vb * (double)(j + 2) + 2.0 * wb) * (double)n + 16.0 * hr) * (double)nrhs);
-      const int64_t nhb = (jg + 1) * ng;
-      if (gs.split > 1) {
-        hipLaunchKernelGGL((dcgs_update_kernel<TB, TW, true>), dim3((unsigned)(nhb + (int64_t)np * nrhs * gs.split)),
-                           dim3(512), 0, q, V, vstride, w, n, nrhs, mres, j, np, gs, part, jp);
-        hipLaunchKernelGGL((dcgs_finish_kernel<TB, TW>), dim3((unsigned)((int64_t)np * nrhs)), dim3(64), 0, q, V,
-                           vstride, w, n, nrhs, j, np, gs, part, jp);
+      // work: bytes of q_0..q_{j-1} read, q_j and w read and written
+      TimedLaunch tl(T_GMRES_UPDATE, q, (vb * (double)(j + 2) + 2.0 * wb) * (double)n * (double)nrhs);
+      if (np64) {
+        hipLaunchKernelGGL((dcgs_update_kernel<TB, TW, 1>), dim3((unsigned)(np64 * nrhs)), dim3(1024), 0, q, V,
+                           vstride, w, n, nrhs, j, np64, gs, part, jp);
       } else {
-        hipLaunchKernelGGL((dcgs_update_kernel<TB, TW, false>), dim3((unsigned)(nhb + (int64_t)np * nrhs)), dim3(512),
-                           0, q, V, vstride, w, n, nrhs, mres, j, np, gs, part, jp);
+        hipLaunchKernelGGL((dcgs_update_kernel<TB, TW, 2>), dim3((unsigned)((int64_t)np * nrhs)), dim3(512), 0,
+                           q, V, vstride, w, n, nrhs, j, np, gs, part, jp);
       }
     }
-    hipLaunchKernelGGL((normalize_kernel<TB, TW>), grid2(n, nrhs), dim3(256), 0, q, w, V, vstride, n, part, np, gs,
-                       mres, j, nrhs, jp, qd);
-    if (jp) hipLaunchKernelGGL(counter_kernel, dim3(1), dim3(64), 0, q, jdev, (int64_t)1, 1);
+    if (!gs.raw)
+      hipLaunchKernelGGL((normalize_kernel<TB, TW>), grid2(n, nrhs), dim3(256), 0, q, w, V, vstride, n, part,
+                         np64 ? np64 : np, gs, mres, j, nrhs, jp, qd);
+    if (!jp) {  // the column steps follow on the second stream
+      CBFM_HIP(hipGetLastError());
+      return;
+    }
+    columns(j, 1, jp, nullptr, q);
+    hipLaunchKernelGGL(counter_kernel, dim3(1), dim3(64), 0, q, jdev, (int64_t)1, 1);
     CBFM_HIP(hipGetLastError());
   };
   int pending = 0;  // flag copies queued in this cycle
   int64_t j = 0;
   bool done = false;
-  auto check = [&]() {
+  auto check = [&](hipStream_t q) {
     if (pending > 0 && all_done(flags.wait())) return true;
-    flags.post(gs.active, s);
+    flags.post(gs.active, q);
     ++pending;
     return false;
   };
@@ -1120,7 +1173,7 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
       try {
-        for (int q = 0; q < check_every; ++q) iteration(0, jdev, cs);
+        for (int q = 0; q < check_every; ++q) iteration(0, jdev, gs, cs);
       } catch (...) {
         (void)hipStreamEndCapture(cs, &graph);
         if (graph) (void)hipGraphDestroy(graph);
@@ -1143,7 +1196,7 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
         CBFM_HIP(hipGraphLaunch(exec, s));
         j += check_every;
         total += check_every;
-        if (check()) {
+        if (check(s)) {
           done = true;
           break;
         }
@@ -1154,16 +1207,33 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
     }
     CBFM_HIP(hipGraphExecDestroy(exec));
   }
-  for (; !done && j < mres && total < max_iter; ++j) {
-    iteration(j, nullptr, s);
-    ++total;
-    if ((j + 1) % check_every == 0 && check()) {
-      ++j;
-      break;
-    }
+  // chunks of iterations on s; the column steps of chunk k run on the second
+  // stream beside chunk k + 1, whose kernels take a right-hand side as long
+  // as it was active after chunk k - 2
+  if (!done && j < mres && total < max_iter)
+    for (int k = 0; k < 2; ++k)
+      CBFM_HIP(hipMemcpyAsync(side->seen(k), gs.active, nrhs * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
+  for (int64_t k = 0; !done && j < mres && total < max_iter; ++k) {
+    const int par = (int)(k & 1);
+    GmresState gm = gs;
+    gm.active = side->seen(par);
+    if (k >= 2) CBFM_HIP(hipStreamWaitEvent(s, side->ev_done[par], 0));
+    const int64_t j0 = j;
+    for (; j < j0 + check_every && j < mres && total < max_iter; ++j, ++total) iteration(j, nullptr, gm, s);
+    CBFM_HIP(hipEventRecord(side->ev_ready[par], s));
+    CBFM_HIP(hipStreamWaitEvent(side->ls, side->ev_ready[par], 0));
+    columns(j0, (int)(j - j0), nullptr, gm.active, side->ls);
+    CBFM_HIP(hipEventRecord(side->ev_done[par], side->ls));
+    CBFM_HIP(hipGetLastError());
+    if (j - j0 == check_every && check(side->ls)) break;
   }
+  if (side)
+    for (hipEvent_t e : side->ev_done) CBFM_HIP(hipStreamWaitEvent(s, e, 0));
   // the last column of the cycle, taken without the delayed correction
-  if (j > 0) hipLaunchKernelGGL(column_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, gs, mres, j, nrhs, 0, nullptr);
+  if (j > 0 && gs.raw)
+    hipLaunchKernelGGL(norm_kernel<TB>, dim3((unsigned)nrhs), dim3(256), 0, s, V + j * vstride, n, gs.nrm, gs.active);
+  if (j > 0)
+    hipLaunchKernelGGL(columns_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, gs, mres, j, 1, nrhs, 0, nullptr, nullptr);
   hipLaunchKernelGGL(backsolve_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, gs, mres, nrhs);
   // x += Q y, or Z y for flexible GMRES (the preconditioned vectors z_j)
   hipLaunchKernelGGL(x_update_kernel<TB>, dim3((unsigned)((int64_t)np * nrhs)), dim3(512), 0, s, gs, xb ? xb : V,
@@ -1740,7 +1810,7 @@ __global__ void __launch_bounds__(256) sstep_hcols_kernel(GmresState st, double2
 // over the runs (in LDS) gives each run its incoming entry, and the runs are
 // replayed in parallel.  Thread 0 then applies this block's rotations in
 // order, forms each new rotation, and updates g, the residual estimate and
-// the stop test as column_kernel does.  A right-hand side whose Cholesky QR
+// the stop test as column_step does.  A right-hand side whose Cholesky QR
 // broke down keeps the columns before this block and ends its cycle.
 template <int S>
 __global__ void __launch_bounds__(256) sstep_givens_kernel(GmresState st, const double2* __restrict__ H, int64_t M1,
@@ -2197,13 +2267,9 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
   const int64_t ms = S > 0 ? mres / S * S : 0;  // s-step cycle length
   const size_t hsbytes = S > 0 ? (size_t)nrhs * (ms + S) * (ms + S + 1) * sizeof(double2) : 0;
   Scratch Rs(hbytes, s), Hs(std::max(hbytes, hsbytes), s), csb(nrhs * mres * sizeof(double2), s), snb(nrhs * mres * sizeof(double2), s),
-      gb(cbytes, s), d1b(cbytes, s), d2b(cbytes, s), d1t(cbytes, s), d2t(cbytes, s), hcb(cbytes, s),
-      abb(nrhs * sizeof(double2), s), dbl(5 * nrhs * sizeof(double), s), ints(3 * nrhs * sizeof(int32_t), s),
-      part(nrhs * np * sizeof(double), s);
-  // few 128-row update blocks (a single right-hand side): the basis range
-  // of each is split over up to 8 blocks, so that about 256 blocks stream
-  const int split = nrhs == 1 && np < 64 ? (int)std::min<int64_t>(8, (256 + np - 1) / np) : 1;
-  Scratch wsb(split > 1 ? (size_t)nrhs * np * split * 256 * sizeof(double2) : 0, s);
+      gb(cbytes, s), d1b(kSlots * cbytes, s), d2b(kSlots * cbytes, s), d1t(kSlots * cbytes, s), hcb(cbytes, s), pbb(kChunk * cbytes, s),
+      abb(kSlots * nrhs * sizeof(double2), s), dbl((4 + kSlots) * nrhs * sizeof(double), s),
+      ints(3 * nrhs * sizeof(int32_t), s), part(nrhs * ((n + 63) / 64) * sizeof(double), s);
   GmresState gs{Rs.as<double2>(),
                 Hs.as<double2>(),
                 csb.as<double2>(),
@@ -2212,25 +2278,25 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
                 d1b.as<double2>(),
                 d2b.as<double2>(),
                 abb.as<double2>(),
+                dbl.as<double>() + 4 * nrhs,
                 dbl.as<double>(),
                 dbl.as<double>() + nrhs,
                 dbl.as<double>() + 2 * nrhs,
                 dbl.as<double>() + 3 * nrhs,
-                dbl.as<double>() + 4 * nrhs,
                 ints.as<int32_t>(),
                 ints.as<int32_t>() + nrhs,
                 ints.as<int32_t>() + 2 * nrhs,
                 d1t.as<double2>(),
-                d2t.as<double2>(),
                 hcb.as<double2>(),
+                pbb.as<double2>(),
                 mres + 1,
-                split,
-                wsb.as<double2>()};
+                nrhs * (mres + 1),
+                0};
   const int64_t vstride = nrhs * n;
   const dim3 g1((unsigned)((nrhs + 63) / 64)), b1(64);
   CBFM_HIP(hipMemsetAsync(x, 0, nrhs * n * sizeof(double2), s));
   CBFM_HIP(hipMemsetAsync(gs.its, 0, nrhs * sizeof(int32_t), s));
-  hipLaunchKernelGGL(norm_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, b, n, gs.bnorm, nullptr);
+  hipLaunchKernelGGL(norm_kernel<double2>, dim3((unsigned)nrhs), dim3(256), 0, s, b, n, gs.bnorm, nullptr);
   GmresResult out;
   out.its.assign(nrhs, 0);
   out.res.assign(nrhs, 1.0);
@@ -2241,6 +2307,7 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
   // cycle; iterations queued after the last right-hand side converged do
   // nothing (every kernel skips inactive right-hand sides).
   PinnedFlags flags(nrhs);
+  std::unique_ptr<ColumnSide> side(new ColumnSide(nrhs, s));
   auto all_done = [&](const int32_t* a) {
     return std::none_of(a, a + nrhs, [](int32_t v) { return v != 0; });
   };
@@ -2303,7 +2370,7 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
       CBFM_HIP(hipMemcpyAsync(r, b, nrhs * n * sizeof(double2), hipMemcpyDeviceToDevice, s));
     else
       residual(r);
-    hipLaunchKernelGGL(norm_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, r, n, gs.nrm, nullptr);
+    hipLaunchKernelGGL(norm_kernel<double2>, dim3((unsigned)nrhs), dim3(256), 0, s, r, n, gs.nrm, nullptr);
     hipLaunchKernelGGL(cycle_init_kernel, g1, b1, 0, s, gs, mres, nrhs, tol, inner);
     if (f32 || b32)
       hipLaunchKernelGGL(scale_kernel<float2>, grid2(n, nrhs), dim3(256), 0, s, r, V.as<float2>(), n, gs.nrm,
@@ -2317,10 +2384,10 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
     if (sstep_on && shifts_ready && total + S > p.max_iter) sstep_on = false;
     if (f32)
       run_cycle(matvec32, dyn32.get(), dyn32 ? dyn32->desc(0) : nullptr, jdev.as<int64_t>(), V.as<float2>(),
-                u.as<float2>(), vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s);
+                u.as<float2>(), vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, side.get());
     else if (b32)
       run_cycle(matvec, dyn.get(), dyn ? dyn->desc(0) : nullptr, jdev.as<int64_t>(), V.as<float2>(), u.as<double2>(),
-                vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, (const float2*)nullptr,
+                vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, side.get(), (const float2*)nullptr,
                 qd.as<double2>());
     else if (sstep_on && !shifts_ready) {
       const int64_t m1 = std::min<int64_t>(S + 1, mres);
@@ -2328,7 +2395,7 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
       g1.ms = m1 + 1;
       CBFM_HIP(hipMemsetAsync(gs.H, 0, (size_t)nrhs * (m1 + 1) * m1 * sizeof(double2), s));
       run_cycle(matvec, (const GemmPlan*)nullptr, nullptr, jdev.as<int64_t>(), V.as<double2>(), u.as<double2>(),
-                vstride, n, nrhs, m1, p.max_iter, total, g1, part.as<double>(), np, flags, x, s);
+                vstride, n, nrhs, m1, p.max_iter, total, g1, part.as<double>(), np, flags, x, s, side.get());
       std::vector<int32_t> its1(nrhs);
       CBFM_HIP(hipMemcpyAsync(its1.data(), gs.its, nrhs * sizeof(int32_t), hipMemcpyDeviceToHost, s));
       CBFM_HIP(hipStreamSynchronize(s));
@@ -2342,10 +2409,10 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
         sstep_on = false;
     } else if (dense)
       run_cycle(matvec, dyn.get(), dyn ? dyn->desc(0) : nullptr, jdev.as<int64_t>(), V.as<double2>(),
-                u.as<double2>(), vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s);
+                u.as<double2>(), vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, side.get());
     else
       run_cycle(opmv, (const OpMV*)nullptr, nullptr, jdev.as<int64_t>(), V.as<double2>(), u.as<double2>(), vstride, n,
-                nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, op.xbasis());
+                nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, side.get(), op.xbasis());
     if (total >= p.max_iter) break;
   }
   CBFM_HIP(hipMemcpyAsync(out.its.data(), gs.its, nrhs * sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -2353,7 +2420,7 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
   {
     double2* r = f32 ? r64.as<double2>() : u.as<double2>();
     residual(r);
-    hipLaunchKernelGGL(norm_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, r, n, gs.nrm, nullptr);
+    hipLaunchKernelGGL(norm_kernel<double2>, dim3((unsigned)nrhs), dim3(256), 0, s, r, n, gs.nrm, nullptr);
     std::vector<double> rn(nrhs), bn(nrhs);
     CBFM_HIP(hipMemcpyAsync(rn.data(), gs.nrm, nrhs * sizeof(double), hipMemcpyDeviceToHost, s));
     CBFM_HIP(hipMemcpyAsync(bn.data(), gs.bnorm, nrhs * sizeof(double), hipMemcpyDeviceToHost, s));

@@ -1,7 +1,8 @@
 """The Krylov forms' kernels by their sizes: s-step cycles with the block of
 vectors in LDS or not (S n double complex values against a compute unit's
-160 KB: n of about 1,100 for S = 8 and 2,470 for S = 4), and block GMRES with
-full, odd and single-column groups.  Random CBFs and Z_r = I + E (E seeded,
+160 KB: n of about 1,100 for S = 8 and 2,470 for S = 4), block GMRES with
+full, odd and single-column groups, and plain cycles whose lengths fall short
+of, meet and pass the chunks of four iterations.  Random CBFs and Z_r = I + E (E seeded,
 spectral norm about 0.4), so that any size has an exact answer by LU."""
 import numpy as np
 import pytest
@@ -33,7 +34,7 @@ def _system(L):
     return h, n, Zr, *reduced.cbf_matrices(cb, m.ne)
 
 
-def _check(h, Zr, CJM, CMJ, inc, **how):
+def _check(h, Zr, CJM, CMJ, inc, restart=None, **how):
     import torch
     from oracle import excitation
     from paper_2111_11058_amd import cbfm
@@ -42,8 +43,8 @@ def _check(h, Zr, CJM, CMJ, inc, **how):
     jt = torch.zeros((len(inc), 2 * m.ne), dtype=torch.complex128, device="cuda")
     Zt = torch.tensor(Zr, dtype=torch.complex128, device="cuda")
     print("solve", how, "n", h.n_cbf, "right-hand sides", len(inc), flush=True)
-    out = cbfm.solve(_MESH["mesh"], _MESH["med"], h, Zt, inc, tol=1e-12, max_iter=300, restart=h.n_cbf, use_cmp=False,
-                     j_out=jt, **how)
+    out = cbfm.solve(_MESH["mesh"], _MESH["med"], h, Zt, inc, tol=1e-12, max_iter=300,
+                     restart=restart or h.n_cbf, use_cmp=False, j_out=jt, **how)
     e = np.linalg.norm(jt.cpu().numpy().T - jref) / np.linalg.norm(jref)
     print(out["iters"], out["relres"].max(), e)
     assert out["status"] == "OK" and np.all(out["relres"] <= 1e-12)
@@ -66,3 +67,20 @@ def test_block_sizes(block, nrhs):
     from synth import configs
     h, n, Zr, CJM, CMJ = _system(5)
     _check(h, Zr, CJM, CMJ, configs.random_incidences(nrhs, 5), block=block)
+
+
+@pytest.mark.parametrize("L, nrhs, restart", [(1, 1, 1), (1, 2, 3), (1, 1, 4), (2, 5, 5), (1, 3, 8), (5, 65, 9),
+                                              (5, 1, 640), (1, 130, 128), (9, 2, 13)])
+def test_plain_cycles(L, nrhs, restart):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from paper_2111_11058_amd import cbfm
+    from synth import configs
+    h, n, Zr, CJM, CMJ = _system(L)
+    inc = configs.random_incidences(nrhs, 5)
+    _check(h, Zr, CJM, CMJ, inc, restart)
+    # an iteration limit inside a chunk stops there, unconverged
+    for lim in (1, 6):
+        o = cbfm.solve(_MESH["mesh"], _MESH["med"], h, torch.tensor(Zr, device="cuda"), inc, tol=1e-30, max_iter=lim,
+                       restart=restart, use_cmp=False)
+        assert o["status"] == "E_NOCONV" and np.all(o["iters"] == lim) and np.all(o["relres"] < 1)
