@@ -79,20 +79,12 @@ __device__ inline double dpp_double(double x) {
   return __hiloint2double(hi, lo);
 }
 
-// Sum over the 64 lanes of a wavefront as a butterfly: every lane ends with
-// the same bits.
 // Sum over each row of 16 lanes (a DPP butterfly: every lane has it).
-template <int CTRL>
-__device__ inline double dpp_move(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
 __device__ inline double row16_total(double x) {
-  x += dpp_move<0xB1>(x);   // quad_perm [1, 0, 3, 2]
-  x += dpp_move<0x4E>(x);   // quad_perm [2, 3, 0, 1]
-  x += dpp_move<0x141>(x);  // row_half_mirror
-  x += dpp_move<0x140>(x);  // row_mirror
+  x += dpp_double<0xB1>(x);   // quad_perm [1, 0, 3, 2]
+  x += dpp_double<0x4E>(x);   // quad_perm [2, 3, 0, 1]
+  x += dpp_double<0x141>(x);  // row_half_mirror
+  x += dpp_double<0x140>(x);  // row_mirror
   return x;
 }
 // x of a lane known at compile time, uniform
@@ -100,6 +92,8 @@ __device__ inline double lane_value(double x, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
                           __builtin_amdgcn_readlane(__double2loint(x), lane));
 }
+// Sum over the 64 lanes of a wavefront as a butterfly: every lane ends with
+// the same bits.
 __device__ inline double wave_sum(double x) {
   x += dpp_double<0xB1>(x);   // quad_perm [1, 0, 3, 2]
   x += dpp_double<0x4E>(x);   // quad_perm [2, 3, 0, 1]
@@ -287,12 +281,13 @@ __global__ void cycle_init_kernel(GmresState st, int64_t m, int64_t nrhs, double
 // threads take every 256th row, the loads of all VPB vectors of a row go
 // out together, and the wavefronts are summed through LDS in a fixed order.
 // (For a float basis, runs of 8 vectors measured slower: half the blocks at
-// 4 instead of 7 wavefronts per SIMD.)
+// 4 instead of 7 wavefronts per SIMD.)  One vector a block where runs of four
+// would leave CUs without one: 4,480 rows, 48 vectors, one right-hand side
+// 12.8 -> 8.3 us.
 template <typename TB, typename TW, bool UNR, int VPB = 4>
 __global__ void __launch_bounds__(256) dots2_kernel(const TB* __restrict__ V, int64_t vstride,
                                                     const TW* __restrict__ w, int64_t n, int64_t nrhs, int64_t j,
                                                     GmresState st, const int64_t* __restrict__ jp) {
-  static_assert(!UNR || VPB == 4, "the unrolled rows take four vectors");
   if (jp) j = *jp;  // iteration index from the device (graph replays)
   const int64_t id = blockIdx.x;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -313,18 +308,18 @@ __global__ void __launch_bounds__(256) dots2_kernel(const TB* __restrict__ V, in
   // sums still take the rows in order), for long vectors and few blocks;
   // it needs more registers, which would cost occupancy otherwise
   for (; UNR && k + 768 < n; k += 1024) {
-    double2 x[4], y[4], v[4][4];
+    double2 x[4], y[4], v[4][VPB];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       x[u] = ld2(qj + k + 256 * u);
       y[u] = ld2(wc + k + 256 * u);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[u][t] = ld2(qi + (t < cnt ? t : 0) * vstride + k + 256 * u);
+      for (int t = 0; t < VPB; ++t) v[u][t] = ld2(qi + (t < cnt ? t : 0) * vstride + k + 256 * u);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < VPB; ++t) {
         s1[t] = cadd(s1[t], cconjmul(v[u][t], x[u]));
         s2[t] = cadd(s2[t], cconjmul(v[u][t], y[u]));
       }
@@ -1127,7 +1122,10 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
     {
       // work: bytes of q_0..q_j and w for every right-hand side
       TimedLaunch tl(T_GMRES_DOTS, q, (vb * (double)(j + 1) + wb) * (double)nrhs * (double)n);
-      if (n >= 2048 && nrhs < 16)
+      if ((jg + 4) / 4 * nrhs < 256)
+        hipLaunchKernelGGL((dots2_kernel<TB, TW, true, 1>), dim3((unsigned)((jg + 1) * nrhs)), dim3(256), 0, q, V,
+                           vstride, w, n, nrhs, j, gs, jp);
+      else if (n >= 2048 && nrhs < 16)
         hipLaunchKernelGGL((dots2_kernel<TB, TW, true>), dim3((unsigned)((jg + 4) / 4 * nrhs)), dim3(256), 0, q, V,
                            vstride, w, n, nrhs, j, gs, jp);
       else

@@ -84,3 +84,14 @@ def test_plain_cycles(L, nrhs, restart):
         o = cbfm.solve(_MESH["mesh"], _MESH["med"], h, torch.tensor(Zr, device="cuda"), inc, tol=1e-30, max_iter=lim,
                        restart=restart, use_cmp=False)
         assert o["status"] == "E_NOCONV" and np.all(o["iters"] == lim) and np.all(o["relres"] < 1)
+
+
+@pytest.mark.parametrize("L, nrhs", [(1, 2), (1, 3), (2, 4), (2, 5), (5, 7), (9, 8), (1, 9)])
+def test_few_column_product(L, nrhs, monkeypatch):
+    """The vector-unit product of 2 to 8 columns, forced (9: not taken)."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from synth import configs
+    monkeypatch.setenv("CBFM_GEMM_SHAPE", "11")
+    h, n, Zr, CJM, CMJ = _system(L)
+    _check(h, Zr, CJM, CMJ, configs.random_incidences(nrhs, 5))
