@@ -84,8 +84,8 @@ __global__ void cell_gram_kernel(const CellJob* __restrict__ cells, int Nmax, co
 // [[K, -TE], [TH, K]] as the first n columns of the row-major n x ld
 // augmented system [Z_mm | V_m], with identity padding, each RWG entry the
 // sum over the two triangles of either RWG of the triangle-local entries
-// (local blocks [K, TE, TH], each 3 nt x 3 nt row-major; signs and lengths
-// are inside them).
+// (local blocks [K, TE, TH], each 3 nt rows of three column planes of nt;
+// signs and lengths are inside them).
 __global__ void cell_zmm_kernel(const double2* __restrict__ local, const CellJob* __restrict__ jobs, int cell0,
                                 const int32_t* __restrict__ tplus, const int32_t* __restrict__ tminus,
                                 const int32_t* __restrict__ aplus, const int32_t* __restrict__ aminus, int n,
@@ -102,7 +102,8 @@ __global__ void cell_zmm_kernel(const double2* __restrict__ local, const CellJob
     const int64_t ldl = 3 * (int64_t)jb.nt, op_stride = ldl * ldl;
     const int32_t em = jb.edges[rr], en = jb.edges[cc];
     const int64_t ri[2] = {3 * (int64_t)jb.pos[tplus[em]] + aplus[em], 3 * (int64_t)jb.pos[tminus[em]] + aminus[em]};
-    const int64_t ci[2] = {3 * (int64_t)jb.pos[tplus[en]] + aplus[en], 3 * (int64_t)jb.pos[tminus[en]] + aminus[en]};
+    const int64_t cs = jb.nt;
+    const int64_t ci[2] = {jb.pos[tplus[en]] + aplus[en] * cs, jb.pos[tminus[en]] + aminus[en] * cs};
     const double2* L = local + jb.loff + op * op_stride;
     double re = 0, im = 0;
 #pragma unroll

@@ -256,13 +256,17 @@ __device__ __forceinline__ float expo(float x) { return __expf(x); }
 // (R^2 2, 1/R 5, sine and cosine 35, the kernels 19, sums 14, and a seventh
 // of what each source point costs), 49 in float.  The form that summed
 // vectors and reduced every phase took 123.  19,968-triangle cylinder,
-// eight panels (225 M pairs): 62.7 -> 49.9 ms in double, 3.6 and 4.5 G pairs/s
-// (39 ms of it without the stores); 19.4 M pairs in float: 2.40 -> 1.72 ms.
+// eight panels (225 M pairs): 62.7 -> 47.1 ms in double, 3.6 and 4.8 G pairs/s
+// (39 ms of it without the stores); 19.4 M pairs in float: 2.40 -> 1.8 ms,
+// 2.1 where the columns come in the order of their RWGs.  The local blocks
+// keep each local function's columns in a plane of their own (entry (a, b)
+// of row i and column j at (3 i + a) ldl + b ldl / 3 + j): a wavefront's
+// store is 64 adjacent entries instead of every third one, 49.9 -> 47.1 ms.
 // Three waves per SIMD in double (168 registers) spill: 86 ms.
 template <typename R, bool LOSSY, bool CENTRED>
 __device__ __forceinline__ void regular_blocks(const TriTab<R>& tab, int32_t P, int32_t Q, const PairConsts<R>& pc,
                                                cx<R>* __restrict__ o0, int64_t op_stride, int64_t ldl) {
-  const int64_t nt = tab.nt;
+  const int64_t nt = tab.nt, cs = ldl / 3;
   const R* __restrict__ tp = tab.test + (int64_t)kTestVals * P;
   const R d[3] = {(R)(tab.cen[0][P] - tab.cen[0][Q]), (R)(tab.cen[1][P] - tab.cen[1][Q]),
                   (R)(tab.cen[2][P] - tab.cen[2][Q])};
@@ -479,7 +483,7 @@ __device__ __forceinline__ void regular_blocks(const TriTab<R>& tab, int32_t P, 
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
         const R cab = ca[a] * cb[b];
-        o0[a * ldl + b] = cx<R>{cab * out[a][b][0], cab * out[a][b][1]};
+        o0[a * ldl + b * cs] = cx<R>{cab * out[a][b][0], cab * out[a][b][1]};
       }
   }
   // T: X_m = Irr - q_b.Ir - p_a.Iq + (p_a.q_b) I0 per medium, with
@@ -529,7 +533,7 @@ __device__ __forceinline__ void regular_blocks(const TriTab<R>& tab, int32_t P, 
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
         const R cab = ca[a] * cb[b];
-        o0[(o + 1) * op_stride + a * ldl + b] =
+        o0[(o + 1) * op_stride + a * ldl + b * cs] =
             cx<R>{cab * (pa[0] - qb[b][0] + M[5][0] * G[a][b]), cab * (pa[1] - qb[b][1] + M[5][1] * G[a][b])};
       }
     }
@@ -559,7 +563,7 @@ __global__ void __launch_bounds__(256, 2) fill_regular_kernel(
   const int64_t i = blockIdx.y;
   const int64_t jq = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (jq >= nct) return;
-  regular_pair<R, LOSSY>(tab, rowTris[i], colTris[jq], pc, out + (3 * i) * ldl + 3 * jq, op_stride, ldl);
+  regular_pair<R, LOSSY>(tab, rowTris[i], colTris[jq], pc, out + (3 * i) * ldl + jq, op_stride, ldl);
 }
 
 // Many fills (scatterers of any size, each with its own medium) in one
@@ -595,7 +599,7 @@ __global__ void __launch_bounds__(256, 2) fill_regular_batch_kernel(const FillJo
     const int64_t local = it - J.item0, chunks = (J.nct + 255) / 256;
     const int64_t i = local / chunks, jq = (local % chunks) * 256 + threadIdx.x;
     if (jq >= J.nct) continue;
-    cx<R>* o0 = J.out + (3 * i) * J.ldl + 3 * jq;
+    cx<R>* o0 = J.out + (3 * i) * J.ldl + jq;
     regular_pair<R, LOSSY>(J.tab, J.rowTris[i], J.colTris[jq], J.pc, o0, J.op_stride, J.ldl);
   }
 }
@@ -835,8 +839,8 @@ __global__ void __launch_bounds__(64) near_outer_kernel(const double* __restrict
   }
   // (transposed: the block of test P and source Q goes to the slot of the
   // reversed pair, row i = Q's position, column j = P's, entry (b, a))
-  cx<R>* o0 = out + (3 * (int64_t)np.i) * ldl + 3 * (int64_t)np.j;
-  const int64_t sa = transposed ? 1 : ldl, sb = transposed ? ldl : 1;
+  cx<R>* o0 = out + (3 * (int64_t)np.i) * ldl + (int64_t)np.j;
+  const int64_t cs = ldl / 3, sa = transposed ? cs : ldl, sb = transposed ? ldl : cs;
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) {
       o0[a * sa + b * sb] = cx<R>{(R)Kab[a][b].re, (R)Kab[a][b].im};
@@ -978,7 +982,10 @@ void fill_regular_batch(const std::vector<FillBatchItem>& items, int precision, 
 
 // ------------------------------------------------------------- assembly
 // Z[o][r][c] = sum over the two triangles of RWG row0+r and of RWG col0+c of
-// the local entries (signs and lengths are inside the local blocks).
+// the local entries (signs and lengths are inside the local blocks; column
+// planes as regular_blocks stores them).  Bound by memory, every local entry
+// read once: 3.7 TB/s on a panel of the 19,968-triangle cylinder (11 GB,
+// 3.28 -> 3.03 ms with the planes).
 template <typename R, typename RO>
 __global__ void assemble_kernel(const cx<R>* __restrict__ local, int64_t op_stride, int64_t ldl,
                                 const int32_t* __restrict__ rowEdges, int64_t nrow,
@@ -992,7 +999,8 @@ __global__ void assemble_kernel(const cx<R>* __restrict__ local, int64_t op_stri
   if (c >= ncol) return;
   const int32_t em = rowEdges[r], en = colEdges[c];
   const int64_t ri[2] = {3 * (int64_t)rowPos[tplus[em]] + aplus[em], 3 * (int64_t)rowPos[tminus[em]] + aminus[em]};
-  const int64_t ci[2] = {3 * (int64_t)colPos[tplus[en]] + aplus[en], 3 * (int64_t)colPos[tminus[en]] + aminus[en]};
+  const int64_t cs = ldl / 3;
+  const int64_t ci[2] = {colPos[tplus[en]] + aplus[en] * cs, colPos[tminus[en]] + aminus[en] * cs};
 #pragma unroll
   for (int o = 0; o < 3; ++o) {
     RO re = 0, im = 0;
@@ -1052,7 +1060,8 @@ __global__ void assemble_pairs_kernel(const cx<R>* __restrict__ local, int64_t o
   const int64_t r = pairs[2 * k], c = pairs[2 * k + 1];
   const int32_t em = rowEdges[r], en = colEdges[c];
   const int64_t ri[2] = {3 * (int64_t)rowPos[tplus[em]] + aplus[em], 3 * (int64_t)rowPos[tminus[em]] + aminus[em]};
-  const int64_t ci[2] = {3 * (int64_t)colPos[tplus[en]] + aplus[en], 3 * (int64_t)colPos[tminus[en]] + aminus[en]};
+  const int64_t cs = ldl / 3;
+  const int64_t ci[2] = {colPos[tplus[en]] + aplus[en] * cs, colPos[tminus[en]] + aminus[en] * cs};
 #pragma unroll
   for (int o = 0; o < 3; ++o) {
     RO re = 0, im = 0;
@@ -1159,19 +1168,20 @@ namespace cbfm {
 static void fill_ranges(const cbfm_mesh_s* m, const Media& md, int precision, int64_t row0, int64_t nrow, int64_t col0,
                         int64_t ncol, int layout, void* out_dev, int64_t ld, hipStream_t s, char* ws, size_t ws_bytes) {
   const MeshHost& h = m->h;
-  // triangles touching the ranges and their positions
+  // triangles touching the ranges and their positions, in the order in which
+  // the RWGs use them: neighbouring columns of the assembly then read
+  // neighbouring entries of the local blocks (19.4 M pairs in float 1.82 ms
+  // in the mesh's order and layout, 0.99; the fill, whose source triangles
+  // are no longer adjacent in the tables, 1.8 -> 2.1)
   auto tris_of = [&](int64_t e0, int64_t n, std::vector<int32_t>& list, std::vector<int32_t>& pos) {
     pos.assign(h.nt, -1);
-    for (int64_t e = e0; e < e0 + n; ++e) {
-      pos[h.tplus[e]] = 0;
-      pos[h.tminus[e]] = 0;
-    }
     list.clear();
-    for (int64_t t = 0; t < h.nt; ++t)
-      if (pos[t] == 0) {
-        pos[t] = (int32_t)list.size();
-        list.push_back((int32_t)t);
-      }
+    for (int64_t e = e0; e < e0 + n; ++e)
+      for (int32_t t : {h.tplus[e], h.tminus[e]})
+        if (pos[t] < 0) {
+          pos[t] = (int32_t)list.size();
+          list.push_back(t);
+        }
   };
   std::vector<int32_t> rl, rp, cl, cp;
   tris_of(row0, nrow, rl, rp);

@@ -269,7 +269,9 @@ Media make_media(const cbfm_medium* med);
 
 // Fill the triangle-local matrix for row triangles x column triangles into
 // `local` (3 ops x 3*nrt x 3*nct complex of the given precision, ops per
-// layout) and overwrite the near pairs.  Implemented in fill.hip.
+// layout; row 3 i + a, column b nct + j for local functions a, b of row
+// triangle i and column triangle j) and overwrite the near pairs.
+// Implemented in fill.hip.
 // One regular fill of many (mesh, medium, rows x columns) jobs in a single
 // persistent launch (the near pairs of each job are left to fill_near).
 struct FillBatchItem {

@@ -65,7 +65,8 @@ __global__ void assemble_mom_kernel(const cz<R>* __restrict__ local, int64_t op_
   if (c >= ne) return;
   const int32_t em = rowEdges[r], en = colEdges[c];
   const int64_t ri[2] = {3 * (int64_t)rowPos[tplus[em]] + aplus[em], 3 * (int64_t)rowPos[tminus[em]] + aminus[em]};
-  const int64_t ci[2] = {3 * (int64_t)tplus[en] + aplus[en], 3 * (int64_t)tminus[en] + aminus[en]};
+  const int64_t cs = ldl / 3;
+  const int64_t ci[2] = {tplus[en] + aplus[en] * cs, tminus[en] + aminus[en] * cs};
   RO v[3][2];
 #pragma unroll
   for (int o = 0; o < 3; ++o) {
