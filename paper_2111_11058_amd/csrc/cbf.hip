@@ -178,6 +178,7 @@ __device__ inline double row16_sum(double x) {
 // Rows of a column that each of its 16 lanes holds in registers (columns of
 // up to 16 times as many entries; the 144 generating waves of Table I).
 constexpr int kLaneRows = 9;
+constexpr int kHeldRows = 6;  // the same for a pair of columns in LDS (orders to 100 fit there)
 
 // In-place Householder QR of the column-major m x ncol matrix A (lda), only R
 // kept: afterwards the first kmax = min(m, ncol) rows hold R and the entries
@@ -329,24 +330,41 @@ __global__ void __launch_bounds__(1024) cell_qr_kernel(double2* __restrict__ qa,
   }
 }
 
+// 1 / sqrt(x) and 1 / x of a normal x whose square is one: the hardware's
+// estimate and two Newton steps, the last a residual correction (a quarter of
+// the latency of the divisions and square roots).
+__device__ inline double rsqrt_newton(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+__device__ inline double rcp_newton(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(y, fma(-x, y, 1.0), y);
+  return fma(y, fma(-x, y, 1.0), y);
+}
+
 // One-sided (Hestenes) Jacobi on the columns of the column-major nc x nc
-// matrix B (ldb): pairs of columns are rotated, in the round-robin order that
+// matrix B (column p at col(p)): pairs of columns are rotated, in the round-robin order that
 // lets each row of 16 lanes of the block rotate a disjoint pair at once, until
 // in one sweep no pair has |b_p^H b_q| > tol ||b_p|| ||b_q||.  (A column
 // below 1e-14 of big, the rounding level of the matrix, is not turned against
 // another any more once |b_p^H b_q| <= 1e-17 big times the longer of the
-// two: no singular value moves by its rounding.)  The 2 x 2 step
+// two: no singular value moves by its rounding.  Columns from na on, below
+// 1e-17 of big, would never be turned and take no part.)  The 2 x 2 step
 // for alpha = ||b_p||^2, beta = ||b_q||^2, gamma = b_p^H b_q = |gamma| e:
 // zeta = (beta - alpha) / (2 |gamma|), t = sign(zeta) / (|zeta| +
 // sqrt(1 + zeta^2)), c = 1 / sqrt(1 + t^2), s = c t,
 // (b_p, b_q) <- (c b_p - s conj(e) b_q, s e b_p + c b_q).
-// HELD (nc <= 16 kLaneRows): a pair stays in registers between its sums and
-// its rotation (columns in global memory).
+// NR > 0 (nc <= 16 NR): a pair stays in registers between its sums and its
+// rotation.
 // Returns the number of sweeps, or -1 if max_sweeps ran out.
-template <bool HELD, typename P>
-__device__ __forceinline__ int hestenes_jacobi(P B, int ldb, int nc, double tol, double big2, int max_sweeps, int* flag) {
+template <int NR, typename Cols>
+__device__ __forceinline__ int hestenes_jacobi(Cols col, int nc, int na, double tol, double big2, int max_sweeps,
+                                               int* flag) {
+  constexpr bool HELD = NR > 0;
   const int gl = threadIdx.x & 15, grp = threadIdx.x >> 4, ngrp = blockDim.x >> 4;
-  const int ne = nc + (nc & 1);  // an odd count plays against an empty column
+  const int ne = na + (na & 1);  // an odd count plays against an empty column
   for (int sweep = 0; sweep < max_sweeps; ++sweep) {
     __syncthreads();
     if (threadIdx.x == 0) *flag = 0;
@@ -354,12 +372,13 @@ __device__ __forceinline__ int hestenes_jacobi(P B, int ldb, int nc, double tol,
     for (int step = 0; step < ne - 1; ++step) {
       for (int pr = grp; pr < ne / 2; pr += ngrp) {
         const int qr = ne - 1 - pr;
-        const int p = pr == 0 ? 0 : 1 + (pr - 1 + step) % (ne - 1);
-        const int q = 1 + (qr - 1 + step) % (ne - 1);
-        if (p >= nc || q >= nc) continue;
-        P x = B + (int64_t)p * ldb;
-        P y = B + (int64_t)q * ldb;
-        double2 hx[HELD ? kLaneRows : 1], hy[HELD ? kLaneRows : 1];
+        const int ps = pr - 1 + step, qs = qr - 1 + step;  // both below 2 (ne - 1)
+        const int p = pr == 0 ? 0 : 1 + (ps < ne - 1 ? ps : ps - (ne - 1));
+        const int q = 1 + (qs < ne - 1 ? qs : qs - (ne - 1));
+        if (p >= na || q >= na) continue;
+        double2* x = col(p);
+        double2* y = col(q);
+        double2 hx[HELD ? NR : 1], hy[HELD ? NR : 1];
         double al = 0, be = 0, gr = 0, gi = 0;
         auto sums = [&](double2 a, double2 c) {
           al += a.x * a.x + a.y * a.y;
@@ -369,13 +388,13 @@ __device__ __forceinline__ int hestenes_jacobi(P B, int ldb, int nc, double tol,
         };
         if (HELD) {
 #pragma unroll
-          for (int u = 0; u < kLaneRows; ++u) {
+          for (int u = 0; u < NR; ++u) {
             const int i = gl + 16 * u;
             hx[u] = i < nc ? x[i] : make_double2(0.0, 0.0);
             hy[u] = i < nc ? y[i] : make_double2(0.0, 0.0);
           }
 #pragma unroll
-          for (int u = 0; u < kLaneRows; ++u) sums(hx[u], hy[u]);
+          for (int u = 0; u < NR; ++u) sums(hx[u], hy[u]);
         } else {
           for (int i = gl; i < nc; i += 16) sums(x[i], y[i]);
         }
@@ -383,22 +402,31 @@ __device__ __forceinline__ int hestenes_jacobi(P B, int ldb, int nc, double tol,
         be = row16_sum(be);
         gr = row16_sum(gr);
         gi = row16_sum(gi);
-        const double g2 = gr * gr + gi * gi, ag = sqrt(g2);
-        if (!(al * be > 0 && ag > tol * sqrt(al * be)) ||
+        const double g2 = gr * gr + gi * gi;
+        if (!(al * be > 0 && g2 > (tol * al) * (tol * be)) ||
             (fmin(al, be) < 1e-28 * big2 && g2 <= 1e-34 * big2 * fmax(al, be)))
           continue;  // same on the 16 lanes
-        const double z = (be - al) / (2.0 * ag);
-        const double t = (z >= 0 ? 1.0 : -1.0) / (fabs(z) + sqrt(1.0 + z * z));
-        const double cs = 1.0 / sqrt(1.0 + t * t), sn = cs * t;
-        const double er = gr / ag, ei = gi / ag;
-        // a' = cs a - sn conj(e) c ;  c' = sn e a + cs c
+        // s e = c t e with t e = 2 gamma sign(h) / (|h| + sqrt(h^2 + 4 |gamma|^2))
+        const double h = be - al, w = fma(h, h, 4.0 * g2);
+        double T, cs;
+        if (w > 1e-280 && w < 1e280) {
+          const double d = fma(w, rsqrt_newton(w), fabs(h));
+          T = copysign(2.0, h) * rcp_newton(d);
+          cs = rsqrt_newton(fma(T * T, g2, 1.0));
+        } else {
+          const double ag = sqrt(g2), z = h / (2.0 * ag);
+          T = (z >= 0 ? 1.0 : -1.0) / (fabs(z) + sqrt(1.0 + z * z)) / ag;
+          cs = 1.0 / sqrt(1.0 + T * T * g2);
+        }
+        const double sr = cs * T * gr, si = cs * T * gi;
+        // a' = c a - conj(s e) c ;  c' = s e a + c c
         auto turn = [&](int i, double2 a, double2 c) {
-          x[i] = make_double2(cs * a.x - sn * (er * c.x + ei * c.y), cs * a.y - sn * (er * c.y - ei * c.x));
-          y[i] = make_double2(sn * (er * a.x - ei * a.y) + cs * c.x, sn * (er * a.y + ei * a.x) + cs * c.y);
+          x[i] = make_double2(cs * a.x - (sr * c.x + si * c.y), cs * a.y - (sr * c.y - si * c.x));
+          y[i] = make_double2((sr * a.x - si * a.y) + cs * c.x, (sr * a.y + si * a.x) + cs * c.y);
         };
         if (HELD) {
 #pragma unroll
-          for (int u = 0; u < kLaneRows; ++u)
+          for (int u = 0; u < NR; ++u)
             if (gl + 16 * u < nc) turn(gl + 16 * u, hx[u], hy[u]);
         } else {
           for (int i = gl; i < nc; i += 16) turn(i, x[i], y[i]);
@@ -422,20 +450,24 @@ __device__ __forceinline__ int hestenes_jacobi(P B, int ldb, int nc, double tol,
 // cell, zero beyond nc), Ut = U~ and Uts = U~ S^{-1} (column-major rk x rk,
 // first nc columns, zero rows beyond nc), info = 0, or 1 if the sweeps ran
 // out.  LDS = true keeps the nc x nc working matrix in LDS, else in work
-// (rk x rk per cell).  Bound by one CU's bandwidth to the matrix in each of
-// the nc - 1 steps of a sweep: 96 cells of order 144 in L2 17.1 -> 8.7 ms,
-// 27 of order 96 in LDS 2.78 -> 2.13 ms with the pivoting.
+// (rk x rk per cell) with as many of its columns in LDS as fit (generic
+// pointers).  Bound by one CU's bandwidth to the matrix and the latency of a
+// rotation in each of the nc - 1 steps of a sweep: 96 cells of order 144 17.1
+// -> 8.7 ms with the pivoting, 8.2 with rotations by reciprocal estimates,
+// 7.1 with 69 of the columns in LDS; 27 of order 96 in LDS 2.78 -> 2.12 ->
+// 1.66, 1.37 without the columns at the rounding level (20 of 96).
 template <bool LDS>
 __global__ void __launch_bounds__(1024) core_svd_kernel(const double2* __restrict__ X, int rk,
-                                                        const int32_t* __restrict__ ncell, double2* work, double tol,
+                                                        const int32_t* __restrict__ ncell, double2* work,
+                                                        int lds_entries, double tol,
                                                         int max_sweeps, double* __restrict__ sigma,
                                                         double2* __restrict__ Ut, double2* __restrict__ Uts,
                                                         int32_t* __restrict__ info) {
   extern __shared__ double2 lds[];
-  __shared__ int flag;
+  __shared__ int flag, last;
   const int b = blockIdx.x, nc = min((int)ncell[b], rk);
   double2* A = LDS ? lds : work + (int64_t)b * rk * rk;
-  double2* v = LDS ? lds + (int64_t)nc * nc : lds;            // nc entries
+  double2* v = LDS ? lds + (int64_t)nc * nc : lds + lds_entries;  // nc entries
   double* nrm = reinterpret_cast<double*>(v + nc);             // nc entries
   int* rank = reinterpret_cast<int*>(nrm + nc);                // nc entries
   const double2* Xb = X + (int64_t)b * rk * rk;
@@ -462,14 +494,30 @@ __global__ void __launch_bounds__(1024) core_svd_kernel(const double2* __restric
   double f2 = 0;  // (row 0 of R is the longest, within the square root of nc)
   for (int i = lane; i < nc; i += 64) f2 += A[i].x * A[i].x + A[i].y * A[i].y;
   f2 = wave_sum(f2);
-  const int sweeps = !LDS && nc <= 16 * kLaneRows ? hestenes_jacobi<!LDS>(A, nc, nc, tol, f2, max_sweeps, &flag)
-                                                  : hestenes_jacobi<false>(A, nc, nc, tol, f2, max_sweeps, &flag);
+  const int nl = LDS ? nc : min(nc, lds_entries / nc);
+  if (!LDS) {
+    for (int e = threadIdx.x; e < nl * nc; e += blockDim.x) lds[e] = A[e];
+    __syncthreads();
+  }
+  auto col = [&](int p) { return LDS || p < nl ? lds + p * nc : A + p * nc; };
+  constexpr int NR = LDS ? kHeldRows : kLaneRows;
+  if (threadIdx.x == 0) last = 0;
+  __syncthreads();
+  for (int j = wave; j < nc; j += nw) {  // the last column above the rounding level
+    const double2* cj = col(j);
+    double q = 0;
+    for (int i = lane; i < nc; i += 64) q += cj[i].x * cj[i].x + cj[i].y * cj[i].y;
+    q = wave_sum(q);
+    if (lane == 0 && q > 1e-35 * f2) atomicMax(&last, j);
+  }
+  __syncthreads();
+  const int na = last + 1;
+  const int sweeps = nc <= 16 * NR ? hestenes_jacobi<NR>(col, nc, na, tol, f2, max_sweeps, &flag)
+                                   : hestenes_jacobi<0>(col, nc, na, tol, f2, max_sweeps, &flag);
   for (int j = wave; j < nc; j += nw) {
     double q = 0;
-    for (int i = lane; i < nc; i += 64) {
-      const double2 a = A[(int64_t)j * nc + i];
-      q += a.x * a.x + a.y * a.y;
-    }
+    const double2* cj = col(j);
+    for (int i = lane; i < nc; i += 64) q += cj[i].x * cj[i].x + cj[i].y * cj[i].y;
     q = wave_sum(q);
     if (lane == 0) nrm[j] = sqrt(q);
   }
@@ -485,10 +533,11 @@ __global__ void __launch_bounds__(1024) core_svd_kernel(const double2* __restric
   for (int j = wave; j < nc; j += nw) {
     const double sg = nrm[j];
     const double s1 = sg > 0 ? 1.0 / sg : 0.0, s2 = s1 * s1;
+    const double2* cj = col(j);
     double2* u = Ut + (int64_t)b * rk * rk + (int64_t)rank[j] * rk;
     double2* us = Uts + (int64_t)b * rk * rk + (int64_t)rank[j] * rk;
     for (int i = lane; i < rk; i += 64) {
-      const double2 a = i < nc ? A[(int64_t)j * nc + i] : make_double2(0.0, 0.0);
+      const double2 a = i < nc ? cj[i] : make_double2(0.0, 0.0);
       u[i] = make_double2(a.x * s1, a.y * s1);
       us[i] = make_double2(a.x * s2, a.y * s2);
     }
@@ -837,8 +886,8 @@ void cmp_apply_dev(cbfm_cbf_s* c, int64_t nrhs, double2* x, hipStream_t s) {
   zgemm_batched(ds, s);
 }
 
-// Dynamic LDS that a core_svd_kernel<true> block may use on the current
-// device (the kernel's attribute is raised to it once per device).
+// Dynamic LDS that a core_svd_kernel block may use on the current device
+// (the kernels' attributes are raised to it once per device).
 static size_t core_svd_lds_limit() {
   static std::mutex mu;
   static std::map<int, size_t> limit;
@@ -850,11 +899,13 @@ static size_t core_svd_lds_limit() {
   int maxsh = 0;
   CBFM_HIP(hipDeviceGetAttribute(&maxsh, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
   size_t lim = maxsh > 256 ? (size_t)maxsh - 256 : 0;  // room for the kernel's static LDS
-  if (lim > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(&core_svd_kernel<true>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim) != hipSuccess) {
-    (void)hipGetLastError();
-    lim = 65536;
-  }
+  for (const void* k : {reinterpret_cast<const void*>(&core_svd_kernel<true>),
+                        reinterpret_cast<const void*>(&core_svd_kernel<false>)})
+    if (lim > 65536 &&
+        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim) != hipSuccess) {
+      (void)hipGetLastError();
+      lim = 65536;
+    }
   limit[dev] = lim;
   return lim;
 }
@@ -985,12 +1036,14 @@ static cbfm_cbf_s* orthogonalise(const cbfm_mesh_s* m, double2* QA_p, int S, int
     const int max_sweeps = 60;
     if (lds <= core_svd_lds_limit()) {
       hipLaunchKernelGGL(core_svd_kernel<true>, dim3(nb), dim3(1024), lds, s, core.as<double2>(), rk,
-                         dN_p, nullptr, tol, max_sweeps, sv.as<double>(), Ut.as<double2>(),
+                         dN_p, nullptr, 0, tol, max_sweeps, sv.as<double>(), Ut.as<double2>(),
                          Uts.as<double2>(), info.as<int32_t>());
     } else {
       Scratch work((size_t)nb * rk * rk * sizeof(double2), s);
-      hipLaunchKernelGGL(core_svd_kernel<false>, dim3(nb), dim3(1024), (size_t)ncmax * (sizeof(double2) + 12), s,
-                         core.as<double2>(), rk, dN_p, work.as<double2>(), tol, max_sweeps,
+      const size_t own = (size_t)ncmax * (sizeof(double2) + 12), lim = core_svd_lds_limit();
+      const int entries = lim > own ? (int)((lim - own) / sizeof(double2)) : 0;
+      hipLaunchKernelGGL(core_svd_kernel<false>, dim3(nb), dim3(1024), entries * sizeof(double2) + own, s,
+                         core.as<double2>(), rk, dN_p, work.as<double2>(), entries, tol, max_sweeps,
                          sv.as<double>(), Ut.as<double2>(), Uts.as<double2>(), info.as<int32_t>());
     }
     CBFM_HIP(hipGetLastError());
