@@ -119,6 +119,98 @@ __global__ void cell_zmm_kernel(const double2* __restrict__ local, const CellJob
   Aug[(int64_t)b * n * ld + (int64_t)r * ld + c] = v;
 }
 
+// The cells' supports, formed on the device (on the host 96 cells of a mesh
+// of 19,968 triangles took 5.5 ms of a 35 ms build, every cell walking every
+// triangle).  support_mark_kernel: pos[b][t] = 0 for the triangles t of cell
+// b's RWGs (blockIdx.y: cell; pos filled with -1).
+__global__ void support_mark_kernel(const int32_t* __restrict__ perm, const int64_t* __restrict__ cell_off,
+                                    const int32_t* __restrict__ tplus, const int32_t* __restrict__ tminus, int64_t nt,
+                                    int32_t* __restrict__ pos) {
+  const int64_t b = blockIdx.y, i = cell_off[b] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= cell_off[b + 1]) return;
+  const int32_t e = perm[i];
+  pos[b * nt + tplus[e]] = 0;
+  pos[b * nt + tminus[e]] = 0;
+}
+
+// One block of 1024 per cell: its marked triangles numbered in mesh order,
+// listed at tris[2 cell_off[b]] (at most two per RWG) and counted in ntri[b].
+__global__ void __launch_bounds__(1024) support_list_kernel(const int64_t* __restrict__ cell_off, int64_t nt,
+                                                            int32_t* __restrict__ pos, int32_t* __restrict__ tris,
+                                                            int32_t* __restrict__ ntri) {
+  __shared__ int wsum[2][16];
+  const int64_t b = blockIdx.x;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int32_t* pb = pos + b * nt;
+  int32_t* list = tris + 2 * cell_off[b];
+  int base = 0;
+  for (int64_t t0 = 0, it = 0; t0 < nt; t0 += 1024, ++it) {
+    const int64_t t = t0 + threadIdx.x;
+    const bool in = t < nt && pb[t] == 0;
+    const unsigned long long m = __ballot(in);
+    int* ws = wsum[it & 1];  // (two of them: one barrier a round)
+    if (lane == 0) ws[wv] = __popcll(m);
+    __syncthreads();
+    int before = base;
+    for (int w = 0; w < 16; ++w) {
+      before += w < wv ? ws[w] : 0;
+      base += ws[w];
+    }
+    if (in) {
+      const int k = before + __popcll(m & ((1ull << lane) - 1));
+      pb[t] = k;
+      list[k] = (int32_t)t;
+    }
+  }
+  if (threadIdx.x == 0) ntri[b] = base;
+}
+
+// The near pairs inside each cell's support, a thread per pair of the mesh's
+// list (x: p, y: q with the coplanar flag on top): a triangle lies in the
+// supports of at most the three cells of its RWGs.  Without out the pairs
+// are counted; with it cell b's are written from cursor[b] on, in any order
+// (every pair has its own slots).
+__global__ void support_near_kernel(const uint2* __restrict__ near, int64_t nnear, const int32_t* __restrict__ tri_edge,
+                                    const int32_t* __restrict__ iperm, const int64_t* __restrict__ cell_off, int nb,
+                                    int64_t nt, const int32_t* __restrict__ pos, int32_t* __restrict__ cursor,
+                                    NearPair* __restrict__ out) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const bool on = k < nnear;
+  const uint2 pq = near[on ? k : 0];
+  const int32_t p = (int32_t)pq.x, q = (int32_t)(pq.y & 0x7fffffffu);
+  int seen[3] = {-1, -1, -1};
+  for (int a = 0; a < 3; ++a) {
+    const int32_t e = tri_edge[3 * (int64_t)p + a];
+    const int64_t i = e < 0 ? cell_off[nb] : iperm[e];
+    int lo = 0, hi = nb - 1;  // the cell of position i
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (cell_off[mid] <= i)
+        lo = mid;
+      else
+        hi = mid - 1;
+    }
+    const bool in = on && i < cell_off[nb] && lo != seen[0] && lo != seen[1];
+    seen[a] = in ? lo : -1;
+    const int32_t jp = in ? pos[lo * nt + p] : -1, jq = in ? pos[lo * nt + q] : -1;
+    // one addition for the lanes of a wavefront that share a cell (most do:
+    // an addition per lane took 1.6 ms for the 96 cells)
+    bool wait = jq >= 0;
+    for (unsigned long long w = __ballot(wait); w != 0; w = __ballot(wait)) {
+      const int lead = __ffsll(w) - 1, cell = __shfl(lo, lead);
+      const bool mine = wait && lo == cell;
+      const unsigned long long m = __ballot(mine);
+      int first = 0;
+      if (lane == lead) first = atomicAdd(cursor + cell, __popcll(m));
+      first = __shfl(first, lead);
+      if (mine && out)
+        out[first + __popcll(m & ((1ull << lane) - 1))] = {p, q, jp, jq, (int32_t)(pq.y >> 31), cell};
+      if (mine) wait = false;
+    }
+  }
+}
+
 // The generating right-hand sides of every cell (blockIdx.z: cell): column
 // n + c of the cell's row-major n x (n + S) augmented system is
 // [v^E(edges); v^H(edges); 0] of wave c.
@@ -610,10 +702,6 @@ __global__ void gram_times_cj_cell_kernel(const int32_t* __restrict__ perm, cons
 }
 
 // ------------------------------------------------------------- host helpers
-static std::vector<int32_t> cell_edges(const MeshHost& h, int b) {
-  return std::vector<int32_t>(h.perm.begin() + h.cell_off[b], h.perm.begin() + h.cell_off[b + 1]);
-}
-
 void cbf_finish(cbfm_cbf_s* c) {
   const MeshHost& h = c->mesh->h;
   c->off.assign(h.nblocks + 1, 0);
@@ -910,45 +998,6 @@ static size_t core_svd_lds_limit() {
   return lim;
 }
 
-// Per-cell support triangles and the near pairs inside it.
-struct CellSupport {
-  std::vector<int32_t> tris, pos, edges;
-  std::vector<NearPair> near;
-};
-
-// The supports of all cells, with each cell's near pairs in the order of
-// the mesh's near list (one pass over the list: a triangle lies in the
-// supports of at most the three cells of its edges).
-static std::vector<CellSupport> supports(const MeshHost& h, int nb) {
-  std::vector<CellSupport> cs(nb);
-  std::vector<std::array<int32_t, 3>> tcell(h.nt, {-1, -1, -1});
-  for (int b = 0; b < nb; ++b) {
-    CellSupport& c = cs[b];
-    c.edges = cell_edges(h, b);
-    c.pos.assign(h.nt, -1);
-    for (int32_t e : c.edges) {
-      c.pos[h.tplus[e]] = 0;
-      c.pos[h.tminus[e]] = 0;
-    }
-    for (int64_t t = 0; t < h.nt; ++t)
-      if (c.pos[t] == 0) {
-        c.pos[t] = (int32_t)c.tris.size();
-        c.tris.push_back((int32_t)t);
-        for (int32_t& x : tcell[t])
-          if (x < 0) {
-            x = b;
-            break;
-          }
-      }
-  }
-  for (const NearPair& q : h.near)
-    for (int32_t b : tcell[q.p]) {
-      if (b < 0) break;
-      if (cs[b].pos[q.q] >= 0) cs[b].near.push_back({q.p, q.q, cs[b].pos[q.p], cs[b].pos[q.q], q.coplanar, 0});
-    }
-  return cs;
-}
-
 }  // namespace cbfm
 
 using namespace cbfm;
@@ -1188,11 +1237,41 @@ cbfm_status cbfm_build_cbf(cbfm_mesh m, const cbfm_medium* med, const cbfm_cbf_p
     // per cell the augmented system [Z_mm | V_m] (padded, row-major n x (n + S))
     const int ldz = n + S;
     Scratch Aug((size_t)nb * n * ldz * sizeof(double2), s);
-    std::vector<CellSupport> cs = supports(h, nb);
+    // the cells' supports and near pairs (the mesh's pairs: p, and q with the
+    // coplanar flag; of cell 0's triangles alone for translated copies)
+    std::vector<uint2> hnear;
+    hnear.reserve(m->translated ? h.near.size() / (size_t)h.nblocks + 1 : h.near.size());
+    for (const NearPair& q : h.near)
+      if (!m->translated || m->tcell[q.p] == 0)
+        hnear.push_back(make_uint2((uint32_t)q.p, (uint32_t)q.q | (q.coplanar ? 0x80000000u : 0u)));
+    const int64_t nnear = (int64_t)hnear.size();
+    Scratch dco((size_t)(nb + 1) * sizeof(int64_t), s), dpairs((size_t)nnear * sizeof(uint2), s),
+        dpos((size_t)nb * h.nt * sizeof(int32_t), s), dtri((size_t)2 * h.cell_off[nb] * sizeof(int32_t), s),
+        dcnt((size_t)2 * nb * sizeof(int32_t), s);
+    CBFM_HIP(hipMemcpyAsync(dco.p, h.cell_off.data(), (nb + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
+    CBFM_HIP(hipMemcpyAsync(dpairs.p, hnear.data(), nnear * sizeof(uint2), hipMemcpyHostToDevice, s));
+    CBFM_HIP(hipMemsetAsync(dpos.p, 0xff, (size_t)nb * h.nt * sizeof(int32_t), s));
+    CBFM_HIP(hipMemsetAsync(dcnt.p, 0, (size_t)2 * nb * sizeof(int32_t), s));
+    hipLaunchKernelGGL(support_mark_kernel, dim3((unsigned)((Nmax + 255) / 256), (unsigned)nb), dim3(256), 0, s,
+                       m->perm.as<int32_t>(), dco.as<int64_t>(), m->tplus.as<int32_t>(), m->tminus.as<int32_t>(), h.nt,
+                       dpos.as<int32_t>());
+    hipLaunchKernelGGL(support_list_kernel, dim3((unsigned)nb), dim3(1024), 0, s, dco.as<int64_t>(), h.nt,
+                       dpos.as<int32_t>(), dtri.as<int32_t>(), dcnt.as<int32_t>());
+    auto near_pass = [&](int32_t* cursor, NearPair* out) {
+      if (nnear == 0) return;
+      hipLaunchKernelGGL(support_near_kernel, dim3((unsigned)((nnear + 255) / 256)), dim3(256), 0, s,
+                         dpairs.as<uint2>(), nnear, m->tri_edge.as<int32_t>(), m->iperm.as<int32_t>(),
+                         dco.as<int64_t>(), nb, h.nt, dpos.as<int32_t>(), cursor, out);
+    };
+    near_pass(dcnt.as<int32_t>() + nb, nullptr);
+    CBFM_HIP(hipGetLastError());
+    std::vector<int32_t> cnt(2 * nb);
+    CBFM_HIP(hipMemcpyAsync(cnt.data(), dcnt.p, cnt.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    CBFM_HIP(hipStreamSynchronize(s));
     // groups of cells whose triangle-local blocks fit in at most 1 GiB (or
     // one cell), filled together; each cell's blocks at loff[b] elements
     size_t maxloc = 0;
-    for (int b = 0; b < nb; ++b) maxloc = std::max(maxloc, cs[b].tris.size());
+    for (int b = 0; b < nb; ++b) maxloc = std::max(maxloc, (size_t)cnt[b]);
     const size_t group_bytes = std::max<size_t>((size_t)1 << 30, (size_t)27 * maxloc * maxloc * sizeof(double2));
     std::vector<int> gstart{0};
     std::vector<size_t> gbytes;
@@ -1200,7 +1279,7 @@ cbfm_status cbfm_build_cbf(cbfm_mesh m, const cbfm_medium* med, const cbfm_cbf_p
     {
       size_t bytes = 0;
       for (int b = 0; b < nb; ++b) {
-        const size_t cb = (size_t)27 * cs[b].tris.size() * cs[b].tris.size() * sizeof(double2);
+        const size_t cb = (size_t)27 * cnt[b] * cnt[b] * sizeof(double2);
         if (b > gstart.back() && bytes + cb > group_bytes) {
           gbytes.push_back(bytes);
           gstart.push_back(b);
@@ -1212,47 +1291,32 @@ cbfm_status cbfm_build_cbf(cbfm_mesh m, const cbfm_medium* med, const cbfm_cbf_p
       gbytes.push_back(bytes);
       gstart.push_back(nb);
     }
-    // index staging for every cell, uploaded once: support lists, the near
-    // pairs of all cells in one array (each tagged with its cell), and the
-    // per-cell tables of the batched launches
+    // the per-cell tables of the batched launches, uploaded once: cell jobs,
+    // near-pair blocks and the first near pair of every cell
     std::vector<int64_t> noff(nb + 1, 0);
-    for (int b = 0; b < nb; ++b) noff[b + 1] = noff[b] + (int64_t)cs[b].near.size();
+    for (int b = 0; b < nb; ++b) noff[b + 1] = noff[b] + cnt[nb + b];
+    CBFM_REQUIRE(noff[nb] <= INT32_MAX, CBFM_E_ARG, "too many near pairs in the cells");
     auto al = [](size_t x) { return (x + 15) & ~(size_t)15; };
-    size_t ibytes = al(sizeof(NearPair) * noff[nb]) + al(sizeof(CellJob) * nb) + al(sizeof(NearOut) * nb);
-    for (int b = 0; b < nb; ++b) ibytes += al(4 * cs[b].tris.size()) + al(4 * cs[b].pos.size()) + al(4 * cs[b].edges.size());
-    std::vector<char> host(ibytes);
-    Scratch idx(ibytes, s);
-    size_t o = 0;
-    auto put = [&](const void* src, size_t bytes) {
-      if (bytes) std::memcpy(host.data() + o, src, bytes);
-      void* d = idx.as<char>() + o;
-      o += al(bytes);
-      return d;
-    };
-    std::vector<const int32_t*> dtris(nb);
-    std::vector<CellJob> jobs(nb);
-    std::vector<NearOut> nouts(nb);
+    const size_t ojob = 0, oout = al(sizeof(CellJob) * nb), ocur = oout + al(sizeof(NearOut) * nb);
+    std::vector<char> host(ocur + sizeof(int32_t) * nb);
+    Scratch idx(host.size(), s), near((size_t)noff[nb] * sizeof(NearPair), s);
+    auto* jobs = reinterpret_cast<CellJob*>(host.data() + ojob);
+    auto* nouts = reinterpret_cast<NearOut*>(host.data() + oout);
+    auto* cur = reinterpret_cast<int32_t*>(host.data() + ocur);
+    std::vector<int32_t> hN(nb);
     for (int b = 0; b < nb; ++b) {
-      const int64_t nt_b = (int64_t)cs[b].tris.size();
-      dtris[b] = (const int32_t*)put(cs[b].tris.data(), 4 * cs[b].tris.size());
-      jobs[b].pos = (const int32_t*)put(cs[b].pos.data(), 4 * cs[b].pos.size());
-      jobs[b].edges = (const int32_t*)put(cs[b].edges.data(), 4 * cs[b].edges.size());
-      jobs[b].loff = loff[b];
-      jobs[b].nt = (int32_t)nt_b;
-      jobs[b].N = (int32_t)cs[b].edges.size();
+      const int64_t nt_b = cnt[b];
+      hN[b] = (int32_t)(h.cell_off[b + 1] - h.cell_off[b]);
+      jobs[b] = {loff[b], cnt[b], hN[b], m->perm.as<int32_t>() + h.cell_off[b], dpos.as<int32_t>() + b * h.nt};
       nouts[b] = {loff[b], 9 * nt_b * nt_b, 3 * nt_b};
-      for (NearPair& q : cs[b].near) q.pad = b;
+      cur[b] = (int32_t)noff[b];
     }
-    NearPair* dnear = (NearPair*)(idx.as<char>() + o);
-    for (int b = 0; b < nb; ++b) {
-      std::memcpy(host.data() + o, cs[b].near.data(), sizeof(NearPair) * cs[b].near.size());
-      o += sizeof(NearPair) * cs[b].near.size();
-    }
-    o = al(o);
-    const CellJob* djobs = (const CellJob*)put(jobs.data(), sizeof(CellJob) * nb);
-    const NearOut* douts = (const NearOut*)put(nouts.data(), sizeof(NearOut) * nb);
-    CBFM_REQUIRE(o == ibytes, CBFM_E_HIP, "cell index staging size mismatch");
-    CBFM_HIP(hipMemcpyAsync(idx.p, host.data(), ibytes, hipMemcpyHostToDevice, s));
+    CBFM_HIP(hipMemcpyAsync(idx.p, host.data(), host.size(), hipMemcpyHostToDevice, s));
+    near_pass(reinterpret_cast<int32_t*>(idx.as<char>() + ocur), near.as<NearPair>());
+    CBFM_HIP(hipGetLastError());
+    const CellJob* djobs = reinterpret_cast<const CellJob*>(idx.as<char>() + ojob);
+    const NearOut* douts = reinterpret_cast<const NearOut*>(idx.as<char>() + oout);
+    const NearPair* dnear = near.as<NearPair>();
     // the cells' self blocks, a group at a time: regular pairs in one
     // persistent launch, the near pairs of all the group's cells in one
     // launch pair, then assembly and packing of every cell in one launch
@@ -1261,8 +1325,8 @@ cbfm_status cbfm_build_cbf(cbfm_mesh m, const cbfm_medium* med, const cbfm_cbf_p
       Scratch local(gbytes[g], s);
       std::vector<FillBatchItem> items;
       for (int b = g0; b < g1; ++b) {
-        const int64_t nt_b = cs[b].tris.size();
-        items.push_back({m, md, CBFM_LAYOUT_OPS3, dtris[b], nt_b, dtris[b], nt_b, local.as<double2>() + loff[b]});
+        const int32_t* tb = dtri.as<int32_t>() + 2 * h.cell_off[b];
+        items.push_back({m, md, CBFM_LAYOUT_OPS3, tb, cnt[b], tb, cnt[b], local.as<double2>() + loff[b]});
       }
       fill_regular_batch(items, CBFM_FP64, s);
       fill_near_batch(m, md, CBFM_LAYOUT_OPS3, dnear + noff[g0], noff[g1] - noff[g0], douts + g0, g0, local.p, s);
@@ -1277,8 +1341,6 @@ cbfm_status cbfm_build_cbf(cbfm_mesh m, const cbfm_medium* med, const cbfm_cbf_p
     // Z_mm J_m = V_m for every cell (Gauss-Jordan on the augmented systems)
     gj_solve_batched(Aug.as<double2>(), (int64_t)n * ldz, ldz, n, ldz, nb, "Z_mm of cell", s);
     // QR of (J^M)^H and (J^J)^H (column-major S x Nmax, zero-padded)
-    std::vector<int32_t> hN(nb);
-    for (int b = 0; b < nb; ++b) hN[b] = (int32_t)cs[b].edges.size();
     Scratch dN((size_t)nb * sizeof(int32_t), s);
     CBFM_HIP(hipMemcpyAsync(dN.p, hN.data(), nb * sizeof(int32_t), hipMemcpyHostToDevice, s));
     Scratch QA((size_t)nb * 2 * S * Nmax * sizeof(double2), s);

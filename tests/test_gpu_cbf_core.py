@@ -42,3 +42,35 @@ def test_core_forms(cells, S):
         # the rounding of sigma_1 over sigma_i >= 1e-6 sigma_1
         D = CM[c].conj().T @ G[np.ix_(ix, ix)] @ CJ[c]
         assert np.abs(D - np.diag(s)).max() < 1e-8 * s[0]
+
+
+@pytest.mark.parametrize("cells, seed", [(2, 1), (7, 2), (30, 3), (1, 0)])
+def test_scattered_cells(cells, seed):
+    """Cells of RWGs drawn at random, so that a triangle lies in the supports
+    of up to three cells and near pairs in several: sigma against the oracle."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from oracle import cbf
+    from paper_2111_11058_amd import cbfm
+    from synth import configs
+    P = oracle_problem("c1")
+    w, m = P["w"], P["m"]
+    eb = np.random.default_rng(seed).integers(0, cells, m.ne).astype(np.int32)
+    gen = configs.random_incidences(9, 31)
+    ref = cbf.build(m, P["Kc"], P["TE"], P["TH"], eb, gen, w.k0, w.eta0, 1e-6)
+    mesh = cbfm.Mesh(w.V, w.T, eb, cells)
+    med = cbfm.Medium.make(w.k0, w.eta0, w.eps_r, w.mu_r)
+    print(f"build_cbf {cells} scattered cells", flush=True)
+    # a cell without adjacent RWGs has G'_m = 0 (to rounding in the oracle)
+    top = max(s[0] for s in ref.sigma)
+    if any(s[0] < 1e-12 * top for s in ref.sigma):
+        with pytest.raises(cbfm.CBFMError, match="E_RANK"):
+            cbfm.build_cbf(mesh, med, gen, 1e-6)
+        return
+    cb = cbfm.build_cbf(mesh, med, gen, 1e-6)
+    assert np.array_equal(cb.L, ref.L)
+    o = 0
+    for c in range(cells):
+        s = ref.sigma[c]
+        assert np.abs(cb.sigma[o:o + len(s)] - s).max() < 1e-9 * s[0]
+        o += len(s)
