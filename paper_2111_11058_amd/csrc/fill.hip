@@ -256,7 +256,7 @@ __device__ __forceinline__ float expo(float x) { return __expf(x); }
 // (R^2 2, 1/R 5, sine and cosine 35, the kernels 19, sums 14, and a seventh
 // of what each source point costs), 49 in float.  The form that summed
 // vectors and reduced every phase took 123.  19,968-triangle cylinder,
-// eight panels (225 M pairs): 62.7 -> 47.1 ms in double, 3.6 and 4.8 G pairs/s
+// eight panels (225 M pairs): 62.7 -> 45.8 ms in double, 3.6 and 4.9 G pairs/s
 // (39 ms of it without the stores); 19.4 M pairs in float: 2.40 -> 1.8 ms,
 // 2.1 where the columns come in the order of their RWGs.  The local blocks
 // keep each local function's columns in a plane of their own (entry (a, b)
@@ -556,12 +556,19 @@ __device__ __forceinline__ void regular_pair(const TriTab<R>& tab, int32_t P, in
   regular_blocks<R, LOSSY, false>(tab, P, Q, pc, o0, op_stride, ldl);
 }
 
+// A block is one row triangle against 256 columns.  In double the rows vary
+// fastest over the blocks, so that the blocks in flight share their source
+// triangles' tables (the stores sweep those out of L2): 47.1 -> 45.8 ms on
+// the cylinder.  In float, with half the stores, the columns: 2.07 against
+// 2.18 ms.
+template <typename R>
+constexpr bool kRowsFastest = std::is_same<R, double>::value;
 template <typename R, bool LOSSY>
 __global__ void __launch_bounds__(256, 2) fill_regular_kernel(
     TriTab<R> tab, const int32_t* __restrict__ rowTris, const int32_t* __restrict__ colTris,
     int64_t nct, PairConsts<R> pc, cx<R>* __restrict__ out, int64_t op_stride, int64_t ldl) {
-  const int64_t i = blockIdx.y;
-  const int64_t jq = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = kRowsFastest<R> ? blockIdx.x : blockIdx.y;
+  const int64_t jq = (int64_t)(kRowsFastest<R> ? blockIdx.y : blockIdx.x) * blockDim.x + threadIdx.x;
   if (jq >= nct) return;
   regular_pair<R, LOSSY>(tab, rowTris[i], colTris[jq], pc, out + (3 * i) * ldl + jq, op_stride, ldl);
 }
@@ -882,6 +889,8 @@ void fill_local(const cbfm_mesh_s* m, const Media& md, int precision, int layout
   const bool lossy = md.k2i != 0.0;
   CBFM_REQUIRE(nrt <= 65535, CBFM_E_ARG, "too many row triangles for one launch");
   dim3 grid((unsigned)((nct + 255) / 256), (unsigned)nrt);
+  if (precision == CBFM_FP64) std::swap(grid.x, grid.y);  // kRowsFastest
+  CBFM_REQUIRE(grid.y <= 65535, CBFM_E_ARG, "too many column triangles for one launch");
   {
   TimedLaunch tl(precision == CBFM_FP64 ? T_FILL_REGULAR : T_FILL_REGULAR_F32, s,
                  (double)nrt * (double)nct);  // work: triangle pairs
