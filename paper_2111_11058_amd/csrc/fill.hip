@@ -556,19 +556,13 @@ __device__ __forceinline__ void regular_pair(const TriTab<R>& tab, int32_t P, in
   regular_blocks<R, LOSSY, false>(tab, P, Q, pc, o0, op_stride, ldl);
 }
 
-// A block is one row triangle against 256 columns.  In double the rows vary
-// fastest over the blocks, so that the blocks in flight share their source
-// triangles' tables (the stores sweep those out of L2): 47.1 -> 45.8 ms on
-// the cylinder.  In float, with half the stores, the columns: 2.07 against
-// 2.18 ms.
-template <typename R>
-constexpr bool kRowsFastest = std::is_same<R, double>::value;
+// A block is one row triangle against 256 columns.
 template <typename R, bool LOSSY>
 __global__ void __launch_bounds__(256, 2) fill_regular_kernel(
     TriTab<R> tab, const int32_t* __restrict__ rowTris, const int32_t* __restrict__ colTris,
-    int64_t nct, PairConsts<R> pc, cx<R>* __restrict__ out, int64_t op_stride, int64_t ldl) {
-  const int64_t i = kRowsFastest<R> ? blockIdx.x : blockIdx.y;
-  const int64_t jq = (int64_t)(kRowsFastest<R> ? blockIdx.y : blockIdx.x) * blockDim.x + threadIdx.x;
+    int64_t nct, PairConsts<R> pc, cx<R>* __restrict__ out, int64_t op_stride, int64_t ldl, bool rows_first) {
+  const int64_t i = rows_first ? blockIdx.x : blockIdx.y;
+  const int64_t jq = (int64_t)(rows_first ? blockIdx.y : blockIdx.x) * blockDim.x + threadIdx.x;
   if (jq >= nct) return;
   regular_pair<R, LOSSY>(tab, rowTris[i], colTris[jq], pc, out + (3 * i) * ldl + jq, op_stride, ldl);
 }
@@ -889,7 +883,16 @@ void fill_local(const cbfm_mesh_s* m, const Media& md, int precision, int layout
   const bool lossy = md.k2i != 0.0;
   CBFM_REQUIRE(nrt <= 65535, CBFM_E_ARG, "too many row triangles for one launch");
   dim3 grid((unsigned)((nct + 255) / 256), (unsigned)nrt);
-  if (precision == CBFM_FP64) std::swap(grid.x, grid.y);  // kRowsFastest
+  // Over the blocks the columns vary fastest; the rows do where the source
+  // triangles' tables (some 38 values each) outgrow one XCD's L2, since the
+  // stores sweep them out and the blocks in flight should share 256 columns
+  // (19,968 columns in double 47.1 -> 45.8 ms; in float, 3 MB of tables, 2.07
+  // against 2.18; 1,728 in double 0.554 against 0.566), and in double where a
+  // row is one or two blocks, so that the ragged ones come last (300 x 300:
+  // 46.6 -> 42.5 us).
+  const bool rows_first =
+      nct * 38 * (precision == CBFM_FP64 ? 8 : 4) > (4 << 20) || (precision == CBFM_FP64 && nct <= 512);
+  if (rows_first) std::swap(grid.x, grid.y);
   CBFM_REQUIRE(grid.y <= 65535, CBFM_E_ARG, "too many column triangles for one launch");
   {
   TimedLaunch tl(precision == CBFM_FP64 ? T_FILL_REGULAR : T_FILL_REGULAR_F32, s,
@@ -898,19 +901,19 @@ void fill_local(const cbfm_mesh_s* m, const Media& md, int precision, int layout
     auto* out = static_cast<cx<double>*>(local);
     if (lossy)
       hipLaunchKernelGGL((fill_regular_kernel<double, true>), grid, dim3(256), 0, s, m->tab64(), rowTris,
-                         colTris, nct, make_pair_consts<double>(md, layout), out, op_stride, ldl);
+                         colTris, nct, make_pair_consts<double>(md, layout), out, op_stride, ldl, rows_first);
     else
       hipLaunchKernelGGL((fill_regular_kernel<double, false>), grid, dim3(256), 0, s, m->tab64(), rowTris,
-                         colTris, nct, make_pair_consts<double>(md, layout), out, op_stride, ldl);
+                         colTris, nct, make_pair_consts<double>(md, layout), out, op_stride, ldl, rows_first);
     CBFM_HIP(hipGetLastError());
   } else {
     auto* out = static_cast<cx<float>*>(local);
     if (lossy)
       hipLaunchKernelGGL((fill_regular_kernel<float, true>), grid, dim3(256), 0, s, m->tab32(), rowTris,
-                         colTris, nct, make_pair_consts<float>(md, layout), out, op_stride, ldl);
+                         colTris, nct, make_pair_consts<float>(md, layout), out, op_stride, ldl, rows_first);
     else
       hipLaunchKernelGGL((fill_regular_kernel<float, false>), grid, dim3(256), 0, s, m->tab32(), rowTris,
-                         colTris, nct, make_pair_consts<float>(md, layout), out, op_stride, ldl);
+                         colTris, nct, make_pair_consts<float>(md, layout), out, op_stride, ldl, rows_first);
   }
   CBFM_HIP(hipGetLastError());
   }
