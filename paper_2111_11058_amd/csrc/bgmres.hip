@@ -686,90 +686,52 @@ __global__ void __launch_bounds__(256) bls_qr_kernel(const double2* __restrict__
   }
 }
 
-// ---- The inverses of the p x p diagonal blocks of R (upper triangular,
-// column-major with ldr), one block each: Di[b] row-major.  A zero diagonal
-// (a direction with no part in the least-squares solution) gives a zero row,
-// hence a zero entry of the solution.
-__global__ void __launch_bounds__(64) diag_inverse_kernel(const double2* __restrict__ Rb, int64_t ldr, int p,
-                                                          double2* __restrict__ Di) {
-  __shared__ double2 Rbb[PMAX][PMAX + 1];
-  const int64_t r0 = (int64_t)blockIdx.x * p;
-  for (int e = threadIdx.x; e < p * p; e += 64) {
-    const int r = e % p, k = e / p;  // column k of the block, row r
-    Rbb[r][k] = Rb[(r0 + k) * ldr + r0 + r];
-  }
-  __syncthreads();
-  const int c = threadIdx.x;
-  if (c >= p) return;
-  double2 y[PMAX];
-#pragma unroll
-  for (int r = PMAX - 1; r >= 0; --r) {
-    y[r] = make_double2(0.0, 0.0);
-    if (r >= p) continue;
-    double2 g = make_double2(r == c ? 1.0 : 0.0, 0.0);
-#pragma unroll
-    for (int k = r + 1; k < PMAX; ++k)
-      if (k < p) g = c_sub(g, c_mul(Rbb[r][k], y[k]));
-    const double2 d = Rbb[r][r];
-    const double dn = d.x * d.x + d.y * d.y;
-    if (dn > 0) y[r] = make_double2((g.x * d.x + g.y * d.y) / dn, (g.y * d.x - g.x * d.y) / dn);
-    Di[((int64_t)blockIdx.x * p + r) * p + c] = y[r];
-  }
+// x of a lane, the lane number uniform
+__device__ __forceinline__ double from_lane(double x, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                          __builtin_amdgcn_readlane(__double2loint(x), lane));
 }
 
 // ---- One step of the block back substitution Y = R^{-1} G (R upper
-// triangular, column-major with ldr, in p x p diagonal blocks with inverses
-// Di; G and Y row-major, p columns): every block forms the diagonal block's
-// solution Di[b] G_b in the eight columns of its blockIdx.y, blocks (0, .)
-// store Y_b, and each thread then removes R[k][block b] Y_b from its row
-// k < b p of G in those columns.  (Solving the triangle in every step took
-// 37 us a step, two thirds of it in 32 dependent divisions.)
+// triangular, column-major with ldr, in p x p diagonal blocks; G and Y
+// row-major, p columns): every block solves the diagonal block b in the eight
+// columns of its blockIdx.y (a zero diagonal, a direction with no part in the
+// least-squares solution, gives a zero entry), blocks (0, .) store Y_b, and
+// each thread then removes R[k][block b] Y_b from its row k < b p of G in
+// those columns.  The triangle is solved by a wavefront for two columns, a
+// lane per row, each solved entry read from its lane: 37 us a step with one
+// thread a column and a division an entry, 21 now.  (Products with the
+// blocks' inverses, refined once, took 18 us but lost accuracy where a block
+// is ill-conditioned: a MoM system of order 119,808 ended 2 % above its
+// residual estimate.)
 __global__ void __launch_bounds__(256) backsolve_step_kernel(const double2* __restrict__ Rb, int64_t ldr,
-                                                             const double2* __restrict__ Di,
                                                              double2* __restrict__ G, int p, int64_t b,
                                                              double2* __restrict__ Y) {
-  __shared__ double2 D[PMAX][PMAX + 1];
   __shared__ double2 Rbb[PMAX][PMAX + 1];
-  __shared__ double2 gb[PMAX][8];
   __shared__ double2 yb[PMAX][8];
   const int tid = threadIdx.x;
   const int64_t r0 = b * p;
   const int c0 = blockIdx.y * 8;
   const int64_t k = (int64_t)blockIdx.x * 256 + tid;
-  for (int e = tid; e < p * p; e += 256) {
-    D[e / p][e % p] = Di[b * p * p + e];
-    Rbb[e % p][e / p] = Rb[(r0 + e / p) * ldr + r0 + e % p];
-  }
-  for (int e = tid; e < p * 8; e += 256) {
-    const int c = c0 + e % 8;
-    gb[e / 8][e % 8] = c < p ? G[(r0 + e / 8) * p + c] : make_double2(0.0, 0.0);
-  }
+  const int yr = tid & 31, yc = tid >> 5;  // row and column of the triangular solve
+  const bool on = yr < p && c0 + yc < p;
+  double2 g = on ? G[(r0 + yr) * p + c0 + yc] : make_double2(0.0, 0.0);
+  for (int e = tid; e < p * p; e += 256) Rbb[e % p][e / p] = Rb[(r0 + e / p) * ldr + r0 + e % p];
   __syncthreads();
-  // y = D g, then once y += D (g - R y): the inverse alone would leave a
-  // residual of its condition times the rounding
-  const int yr = tid / 8, yc = tid % 8;
-  const bool on = tid < p * 8;
-  double2 y = make_double2(0.0, 0.0), res = y;
-  if (on) {
-#pragma unroll 8
-    for (int l = 0; l < p; ++l) y = c_add(y, c_mul(D[yr][l], gb[l][yc]));
-    yb[yr][yc] = y;
+  const double2 d = yr < p ? Rbb[yr][yr] : make_double2(0.0, 0.0);
+  const double dn = d.x * d.x + d.y * d.y;
+  const double2 inv = dn > 0 ? make_double2(d.x / dn, -d.y / dn) : make_double2(0.0, 0.0);
+#pragma unroll 4
+  for (int j = p - 1; j >= 0; --j) {
+    const double2 t = c_mul(g, inv);  // the solution on row j
+    const double2 t0 = make_double2(from_lane(t.x, j), from_lane(t.y, j));
+    const double2 t1 = make_double2(from_lane(t.x, 32 + j), from_lane(t.y, 32 + j));
+    const double2 y = (tid & 32) ? t1 : t0;
+    const double2 r = yr < j ? Rbb[yr][j] : make_double2(0.0, 0.0);
+    g = yr == j ? y : c_sub(g, c_mul(r, y));
   }
-  __syncthreads();
-  if (on) {
-    res = gb[yr][yc];
-#pragma unroll 8
-    for (int l = yr; l < p; ++l) res = c_sub(res, c_mul(Rbb[yr][l], yb[l][yc]));
-  }
-  __syncthreads();
-  if (on) gb[yr][yc] = res;
-  __syncthreads();
-  if (on) {
-#pragma unroll 8
-    for (int l = 0; l < p; ++l) y = c_add(y, c_mul(D[yr][l], gb[l][yc]));
-    yb[yr][yc] = y;
-    if (blockIdx.x == 0 && c0 + yc < p) Y[(r0 + yr) * p + c0 + yc] = y;
-  }
+  if (yr < p) yb[yr][yc] = g;
+  if (on && blockIdx.x == 0) Y[(r0 + yr) * p + c0 + yc] = g;
   __syncthreads();
   if (k >= r0) return;
   double2 acc[8];
@@ -952,14 +914,10 @@ class BlockGmres {
       CBFM_HIP(hipStreamSynchronize(s));
       const int64_t nb = ctl[CTL_DONE], K = nb * p;
       if (K > 0) {
-        Scratch di((size_t)nb * p * p * sizeof(double2), s);
-        hipLaunchKernelGGL(diag_inverse_kernel, dim3((unsigned)nb), dim3(64), 0, s, Rb_.as<double2>(), mb_ * p, p,
-                           di.as<double2>());
         for (int64_t bb = nb - 1; bb >= 0; --bb)
           hipLaunchKernelGGL(backsolve_step_kernel,
                              dim3((unsigned)std::max<int64_t>(1, (bb * p + 255) / 256), (unsigned)((p + 7) / 8)),
-                             dim3(256), 0, s, Rb_.as<double2>(), mb_ * p, di.as<double2>(), G_.as<double2>(), p, bb,
-                             Y_.as<double2>());
+                             dim3(256), 0, s, Rb_.as<double2>(), mb_ * p, G_.as<double2>(), p, bb, Y_.as<double2>());
         CBFM_HIP(hipGetLastError());
         // x += Y^T V_0..V_{nb-1}
         std::vector<std::vector<GemmDesc>> xg(1);
