@@ -893,7 +893,7 @@ __global__ void __launch_bounds__(512) x_update_kernel(GmresState st, const TV* 
 // the directions are common to all).  One block per (direction, group,
 // chunk of triangles), bound by the gathers of the currents, six complex
 // entries a triangle and right-hand side.  72 directions x 32 right-hand
-// sides x 18,432 triangles 2.69 -> 0.89 ms, 72 x 64 x 1,728 0.51 -> 0.13.
+// sides x 19,968 triangles 2.69 -> 0.89 ms, 72 x 64 x 1,728 0.51 -> 0.13.
 struct FarArgs {
   const double* xyz9;
   const int32_t* tri_edge;
