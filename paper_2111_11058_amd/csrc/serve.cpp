@@ -91,9 +91,10 @@ std::pair<size_t, size_t> estimate(int64_t nt, const std::vector<int32_t>& eb, i
   const double panel = std::max<double>(cell_panel, (double)panel_budget);
   const double m = restart > 0 ? std::min<double>(restart, n) : std::min<double>(n, 1000);
   // Krylov basis, H and R, the operator, vectors, and the per-column
-  // arrays (g, cs, sn and the two dot products)
+  // arrays (g, cs, sn, the newest column of H, the dot products of eight
+  // iterations in three copies and the sums of four)
   const double solve = (m + 1) * nrhs * n * z + 2 * nrhs * (m + 1) * m * z + n * n * z +
-                       8 * nrhs * std::max(n, 2 * ne) * z + 5 * nrhs * (m + 1) * z;
+                       8 * nrhs * std::max(n, 2 * ne) * z + 32 * nrhs * (m + 1) * z;
   const double resident = n * n * z + NL * NL * z + 2 * ne * S * z + 2048.0 * nt;
   return {(size_t)(std::max(build, panel) + solve), (size_t)resident};
 }
