@@ -20,8 +20,8 @@
 //     update;
 //  2. row block: over chunks of 64 columns, the permutation is applied and
 //     the pivot rows R become D^{-1} R;
-//  3. update: every other row i loses A[i, panel] D^{-1} R, one batched
-//     matrix-core GEMM with k = 32 (gemm.hip).
+//  3. update: every other row i loses A[i, panel] D^{-1} R on the matrix
+//     cores.
 // An inversion runs in place: the columns of the inverse take the places of
 // the eliminated columns.  The column of the inverse that belongs to row j
 // of the input ends up where the permutations took that row, so a last
@@ -32,7 +32,6 @@
 #include <string>
 #include <vector>
 
-#include "gemm.h"
 #include "gj.h"
 #include "internal.h"
 
@@ -384,6 +383,95 @@ __global__ void __launch_bounds__(256) gj_rows_kernel(RowsArgs p) {
     if (r0 + q < w) Ab[(int64_t)(k + r0 + q) * p.ld + j] = acc[q];
 }
 
+// The update of a step: rows r outside the panel, columns from col0 on, A[r][j]
+// -= P[r] R[., j] (P: the saved panel entries; R: the panel's rows of A), the
+// panel's own columns (an inversion) overwritten by the negative product.  A
+// block of four wavefronts takes 64 x 64 entries, 32 x 32 per wavefront, whose
+// old values are loaded first; both operands pass through LDS in two halves
+// of 16 k.  Bound by the entries read and written (32 bytes for 256 flops):
+// the general kernel, 16 x 16 per wavefront, read each operand entry four
+// times as often: 96 systems of 624 with 144 right-hand sides 440 -> 345 us
+// (first step, 1.3 GB).  3M complex products as in gemm.hip.
+struct UpdateArgs {
+  double2* A;
+  const double2* P;
+  int64_t strideA, ld;
+  int n, ncols, k, w, col0;
+};
+typedef double gj_dbl4 __attribute__((ext_vector_type(4)));
+__global__ void __launch_bounds__(256, 2) gj_update_kernel(UpdateArgs p) {
+  __shared__ double2 sp[64][17];
+  __shared__ double2 sr[16][65];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, slot = lane >> 4, li = lane & 15;
+  const int b = blockIdx.z, k = p.k, w = p.w, nrow = p.n - w;
+  double2* Ab = p.A + (int64_t)b * p.strideA;
+  const double2* Pb = p.P + (int64_t)b * p.n * kW;
+  const int i0 = blockIdx.y * 64, j0 = p.col0 + blockIdx.x * 64;
+  auto row_of = [&](int i) { return i < k ? i : i + w; };  // the i-th row outside the panel
+  const int mi = i0 + 32 * (wave >> 1), mj = j0 + 32 * (wave & 1);
+  double2 c[2][2][4];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = mi + 16 * x + 4 * q + slot, j = mj + 16 * y + li;
+        c[x][y][q] = i < nrow && j < p.ncols && !(j >= k && j < k + w) ? Ab[(int64_t)row_of(i) * p.ld + j]
+                                                                      : make_double2(0.0, 0.0);
+      }
+  gj_dbl4 p1[2][2], p2[2][2], p3[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) p1[x][y] = p2[x][y] = p3[x][y] = gj_dbl4{0, 0, 0, 0};
+  for (int h = 0; h < w; h += 16) {  // uniform
+    double2 a[4], r[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + (tid >> 4) + 16 * u, ka = h + (tid & 15);
+      a[u] = i < nrow && ka < w ? Pb[(int64_t)row_of(i) * kW + ka] : make_double2(0.0, 0.0);
+      const int kr = h + (tid >> 6) + 4 * u, j = j0 + (tid & 63);
+      r[u] = kr < w && j < p.ncols ? Ab[(int64_t)(k + kr) * p.ld + j] : make_double2(0.0, 0.0);
+    }
+    if (h > 0) __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      sp[(tid >> 4) + 16 * u][tid & 15] = a[u];
+      sr[(tid >> 6) + 4 * u][tid & 63] = r[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {  // step s takes k = 4 s + slot
+      double2 av[2], bv[2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        av[x] = sp[32 * (wave >> 1) + 16 * x + li][4 * s + slot];
+        bv[x] = sr[4 * s + slot][32 * (wave & 1) + 16 * x + li];
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          p1[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[x].x, bv[y].x, p1[x][y], 0, 0, 0);
+          p2[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[x].y, bv[y].y, p2[x][y], 0, 0, 0);
+          p3[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[x].x + av[x].y, bv[y].x + bv[y].y, p3[x][y], 0, 0, 0);
+        }
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = mi + 16 * x + 4 * q + slot, j = mj + 16 * y + li;
+        if (i >= nrow || j >= p.ncols) continue;
+        const double re = p1[x][y][q] - p2[x][y][q], im = p3[x][y][q] - p1[x][y][q] - p2[x][y][q];
+        Ab[(int64_t)row_of(i) * p.ld + j] = make_double2(c[x][y][q].x - re, c[x][y][q].y - im);
+      }
+}
+
 __global__ void gj_iota_kernel(int32_t* __restrict__ x, int n, int64_t total) {
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (e < total) x[e] = (int32_t)(e % n);
@@ -431,33 +519,6 @@ void eliminate(double2* A, int64_t strideA, int64_t ld, int n, int ncols, int nm
                        total);
     CBFM_HIP(hipGetLastError());
   }
-  // the update of every step: rows outside the panel, columns right of it
-  // (an inversion: every column; the panel's own columns are overwritten)
-  std::vector<std::vector<GemmDesc>> groups(steps);
-  for (int st = 0; st < steps; ++st) {
-    const int k = st * kW, w = std::min(kW, n - k);
-    for (int b = 0; b < nmat; ++b) {
-      double2* Ab = A + (int64_t)b * strideA;
-      const double2* P = pcol.as<double2>() + (int64_t)b * n * kW;
-      const int rr[2][2] = {{0, k}, {k + w, n}};
-      for (const auto& r : rr) {
-        if (r[1] <= r[0]) continue;
-        auto add = [&](int c0, int c1, int acc) {
-          if (c1 <= c0) return;
-          groups[st].push_back(gemm(P + (int64_t)r[0] * kW, kW, OP_N, Ab + (int64_t)k * ld + c0, ld, OP_N,
-                                    Ab + (int64_t)r[0] * ld + c0, ld, r[1] - r[0], c1 - c0, w, -1.0, acc));
-        };
-        if (inverse) {
-          add(0, k, 1);
-          add(k + w, n, 1);
-          add(k, k + w, 0);
-        } else {
-          add(k + w, ncols, 1);
-        }
-      }
-    }
-  }
-  GemmPlan plan(groups, s, false);
   Scratch* cand[2] = {&cand0, &cand1};
   for (int st = 0; st < steps; ++st) {
     const int k = st * kW, w = std::min(kW, n - k);
@@ -510,7 +571,16 @@ void eliminate(double2* A, int64_t strideA, int64_t ld, int n, int ncols, int nm
       hipLaunchKernelGGL(gj_rows_kernel, dim3((unsigned)nchunks, (unsigned)nmat), dim3(256), 0, s, r);
       CBFM_HIP(hipGetLastError());
     }
-    plan.launch((size_t)st, s);
+    // rows outside the panel, columns right of it (an inversion: every
+    // column; the panel's own columns are overwritten)
+    if (n > w && nchunks > 0) {
+      TimedLaunch tl(T_GEMM, s, 8.0 * w * (double)(n - w) * (double)(ncols - r.col0) * nmat);
+      const UpdateArgs u{A, pcol.as<double2>(), strideA, ld, n, ncols, k, w, r.col0};
+      hipLaunchKernelGGL(gj_update_kernel,
+                         dim3((unsigned)((ncols - r.col0 + 63) / 64), (unsigned)((n - w + 63) / 64), (unsigned)nmat),
+                         dim3(256), 0, s, u);
+      CBFM_HIP(hipGetLastError());
+    }
   }
   if (!inverse) return;
   // column j of the inverse sits at the position that holds input row j

@@ -74,3 +74,37 @@ def test_scattered_cells(cells, seed):
         s = ref.sigma[c]
         assert np.abs(cb.sigma[o:o + len(s)] - s).max() < 1e-9 * s[0]
         o += len(s)
+
+
+@pytest.mark.parametrize("order", [1, 9, 31, 32, 33, 64, 65, 95, 97, 129, 191])
+def test_inverse_orders(order):
+    """The CMP inverse at orders around the panel (32 columns) and the tile of
+    the update (64 entries): random CBFs of cells of uneven numbers of
+    functions, against numpy, by the backward error."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from oracle import cbf, reduced
+    from paper_2111_11058_amd import cbfm
+    from synth import configs
+    P = oracle_problem("c1")
+    w, m = P["w"], P["m"]
+    cells = min(8, order)
+    eb = np.asarray(w.edge_block if cells == 8 else np.zeros(m.ne), np.int32)
+    cells = 8 if cells == 8 else 1
+    ids = [np.flatnonzero(eb == a) for a in range(cells)]
+    L = [order // cells + (1 if a < order % cells else 0) for a in range(cells)]
+    CM = [configs.random_complex((len(ix), k), 40 + a) for a, (ix, k) in enumerate(zip(ids, L))]
+    CJ = [configs.random_complex((len(ix), k), 80 + a) for a, (ix, k) in enumerate(zip(ids, L))]
+    sigma = [np.ones(k) for k in L]
+    B = reduced.gram_b(cbf.rwg_gram(m), cbf.CBFSet(cells=ids, CM=CM, CJ=CJ, sigma=sigma, sigma_all=sigma))
+    h = cbfm.cbf_import(cbfm.Mesh(w.V, w.T, eb, cells), CM, CJ, sigma)
+    y = configs.random_complex((2, 2 * order), 22)
+    yt = torch.tensor(y, dtype=torch.complex128, device="cuda")
+    xt = torch.empty_like(yt)
+    print("cmp apply order", order, flush=True)
+    cbfm.cmp_apply(h, yt, xt)
+    x = xt.cpu().numpy()
+    back = max(np.linalg.norm(-B.conj().T @ x[:, :order].T - y[:, :order].T),
+               np.linalg.norm(B @ x[:, order:].T - y[:, order:].T)) / (np.linalg.norm(B, 2) * np.linalg.norm(x))
+    # an inverse by Gauss-Jordan: order times rounding times the growth of partial pivoting, at most some tens
+    assert back < 1e-16 * 40 * max(order, 8)
