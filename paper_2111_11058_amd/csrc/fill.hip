@@ -52,7 +52,7 @@ constexpr double kW0 = 9.0 / 40.0, kWA = 0.12593918054482717, kWB = 0.1323941527
 template <typename R>
 struct PairConsts {
   R k1, k2r, k2i;
-  R rev1, rev2;               // k / (2 pi): phase in revolutions
+  R rev1, rev2, drev;         // k / (2 pi): phase in revolutions; (k2r - k1) / (2 pi)
   R wl[7], al[7][2];          // w_l / (4 pi) and w_l / (4 pi) times r~'_l's coordinates along w_0, w_1
   // output op o in {1, 2}: op_o = c_a c_b sum_i (A[o][i] X_i + B[o][i] I0_i)
   R A[2][2][2], B[2][2][2];   // [op][medium][re/im]
@@ -148,6 +148,7 @@ static PairConsts<R> make_pair_consts(const Media& md, int layout) {
   const double rev[2] = {md.k1 / (2 * M_PI), md.k2r / (2 * M_PI)};
   pc.rev1 = (R)rev[0];
   pc.rev2 = (R)rev[1];
+  pc.drev = (R)((md.k2r - md.k1) / (2 * M_PI));
   for (int l = 0; l < 7; ++l) {
     const double w = fc.w[l] * (0.25 / M_PI), tau = l == 0 ? 0.0 : (l < 4 ? kTauA : kTauB);
     const int j = (l + 2) % 3;  // the vertex of point l > 0
@@ -191,9 +192,11 @@ static PairConsts<R> make_pair_consts(const Media& md, int layout) {
 // both signs, applied to the sign bits.  The phases here are small
 // multiples of 2 pi (k R over a scatterer), where this reduction is exact
 // enough.  17 FMAs, 3 products and a rint for the pair of values.
-__device__ __forceinline__ void sincos_rev(double x, double& s, double& c) {
+// (LOW: of x + lo, lo within the rounding of x.)
+template <bool LOW = false>
+__device__ __forceinline__ void sincos_rev(double x, double& s, double& c, double lo = 0.0) {
   const double q = rint(2.0 * x);
-  const double f = fma(-0.5, q, x);
+  const double f = LOW ? fma(-0.5, q, x) + lo : fma(-0.5, q, x);
   const int flip = ((int)q & 1) << 31;
   const double u = f * f;
   double ps = 0.10089695501646812;
@@ -226,18 +229,49 @@ __device__ __forceinline__ void phase(float /*x_rad*/, float x_rev, float& s, fl
   c = __builtin_amdgcn_cosf(f);
 }
 // 1 / sqrt(x): the hardware estimate (relative error about 5e-8 on gfx950)
-// refined by one Newton step y <- y + y (1 - x y^2) / 2, which squares the
-// error (a few 1e-15; the residual is formed with an FMA).
+// refined by one third-order step y <- y + y r (1/2 + 3 r / 8), r = 1 - x y^2
+// (the residual is formed with an FMA), to a rounding.  Newton's step, one
+// instruction less, leaves 1.5 x 5e-8 squared, 4e-15, the largest error of
+// the T entries.
 __device__ __forceinline__ double rsq(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   const double r = fma(-(x * y), y, 1.0);
-  return fma(0.5 * y, r, y);
+  return fma(y * r, fma(0.375, r, 0.5), y);
 }
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double expo(double x) { return exp(x); }
 __device__ __forceinline__ float expo(float x) { return __expf(x); }
 
+// sin and cos of 2 pi rev x, the product in twice the precision
+__device__ __forceinline__ void turns(double rev, double x, double& s, double& c) {
+  const double p = rev * x;
+  sincos_rev<true>(p, s, c, fma(rev, x, -p));
+}
+
 // ------------------------------------------------------------- regular kernel
+// d = c_P - c_Q from both parts of either centroid, and |d|^2 = d2h + d2l.
+// Roundings here would be common to the 49 point pairs of an entry and not
+// average out in its sums.
+__device__ __forceinline__ double sum_with_error(double a, double b, double& lo) {
+  const double s = a + b, z = s - a;
+  lo += (a - (s - z)) + (b - z);
+  return s;
+}
+template <typename R>
+__device__ __forceinline__ void centroid_offset(const TriTab<R>& tab, int32_t P, int32_t Q, R (&d)[3], R& d2h, R& d2l) {
+  double h = 0, lo = 0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    double l = tab.cenlo[c][P] - tab.cenlo[c][Q], e = 0;
+    const double y = sum_with_error(tab.cen[c][P], -tab.cen[c][Q], l), x = sum_with_error(y, l, e), q = x * x;
+    lo += fma(2.0 * x, e, fma(x, x, -q));
+    h = c == 0 ? q : sum_with_error(h, q, lo);
+    d[c] = (R)x;
+  }
+  d2h = (R)h;
+  d2l = (R)((h - (double)d2h) + lo);
+}
+
 // The 3 x 3 local blocks of the three output operators for test triangle P
 // and source triangle Q, written at o0 (row stride ldl, operator stride
 // op_stride).  P is the same on every lane of the wavefront (one row
@@ -268,16 +302,15 @@ __device__ __forceinline__ void regular_blocks(const TriTab<R>& tab, int32_t P, 
                                                cx<R>* __restrict__ o0, int64_t op_stride, int64_t ldl) {
   const int64_t nt = tab.nt, cs = ldl / 3;
   const R* __restrict__ tp = tab.test + (int64_t)kTestVals * P;
-  const R d[3] = {(R)(tab.cen[0][P] - tab.cen[0][Q]), (R)(tab.cen[1][P] - tab.cen[1][Q]),
-                  (R)(tab.cen[2][P] - tab.cen[2][Q])};
+  R d[3], d2h, d2l;
+  centroid_offset(tab, P, Q, d, d2h, d2l);
   R dv[2];  // d.v_i
 #pragma unroll
   for (int i = 0; i < 2; ++i) dv[i] = d[0] * tp[3 * i] + d[1] * tp[3 * i + 1] + d[2] * tp[3 * i + 2];
   R Rc = 0, pr = 1, pi = 0;  // |d|, and medium 2's turn pr - j pi
   if constexpr (CENTRED) {
-    const R d2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-    Rc = d2 > (R)0 ? d2 * rsq(d2) : (R)0;
-    phase((R)0, (pc.rev2 - pc.rev1) * Rc, pi, pr);
+    Rc = d2h > (R)0 ? d2h * rsq(d2h) : (R)0;  // (any value near |d| will do)
+    turns(pc.drev, Rc, pi, pr);
     if (LOSSY) {
       const R x = expo(pc.k2i * Rc);
       pr *= x;
@@ -302,20 +335,26 @@ __device__ __forceinline__ void regular_blocks(const TriTab<R>& tab, int32_t P, 
       rq[c] = AHEAD ? nx[c] : v;
       nx[c] = v;
     }
-    const R e[3] = {d[0] - rq[0], d[1] - rq[1], d[2] - rq[2]};
-    const R s0 = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
-    R D[3];  // e.v_i
+    // |d - r~'|^2 = d2h + s0: the small parts are added first, and d2h once
+    // per point pair, so that no rounding of the whole is common to the 49
+    R s0 = d2l;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) D[i] = e[0] * tp[3 * i] + e[1] * tp[3 * i + 1] + e[2] * tp[3 * i + 2];
+    for (int c = 0; c < 3; ++c) s0 = fma(rq[c], fma((R)-2, d[c], rq[c]), s0);
+    R D[3], rv[2];  // (d - r~').v_i, r~'.v_i
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      rv[i] = rq[0] * tp[3 * i] + rq[1] * tp[3 * i + 1] + rq[2] * tp[3 * i + 2];
+      D[i] = dv[i] - rv[i];
+    }
     D[2] = -D[0] - D[1];
     const R wl = pc.wl[l], a0 = pc.al[l][0], a1 = pc.al[l][1];
-    const R rv0 = wl * (dv[0] - D[0]), rv1 = wl * (dv[1] - D[1]);  // r~'.v_i
+    const R rv0 = wl * rv[0], rv1 = wl * rv[1];
     R A0[2][2] = {}, h[2][2][2] = {}, B0[2] = {}, hg[2][2] = {};
 #pragma unroll
     for (int k = 0; k < 7; ++k) {
       const int i = (k + 2) % 3;  // the vertex of point k > 0
       const R tau = (R)(k < 4 ? kTauA : kTauB), wk = (R)(k == 0 ? kW0 : k < 4 ? kWA : kWB);
-      const R R2 = k == 0 ? s0 : fma((R)2 * tau, D[i], s0 + tp[9 + (k - 1)]);
+      const R R2 = d2h + (k == 0 ? s0 : fma((R)2 * tau, D[i], s0 + tp[9 + (k - 1)]));
       const R iR = rsq(R2);
       const R Rl = R2 * iR;
       const R t = iR * iR;
@@ -420,7 +459,7 @@ __device__ __forceinline__ void regular_blocks(const TriTab<R>& tab, int32_t P, 
     for (int c = 0; c < 3; ++c) w[b][c] = tab.v[c][b * nt + Q];
   const R* ca = tp + 15;
   R ec = 1, es = 0;  // the turn e^{-j k1 R_c} = ec - j es of every sum
-  if constexpr (CENTRED) phase((R)0, pc.rev1 * Rc, es, ec);
+  if constexpr (CENTRED) turns(pc.rev1, Rc, es, ec);
   {
     // K = -(c_a c_b / 4) [S0 + U_a + W_b - b0 D_ab + ch_a n_b - m_a cq_b]:
     //   S0 = -sum_ij H_ij D_ij,

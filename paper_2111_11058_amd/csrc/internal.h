@@ -169,14 +169,16 @@ struct Scratch {
 };
 
 // Per-triangle geometry, structure of arrays, in one precision.  Points are
-// stored relative to the triangle's centroid; the centroid itself is kept
-// in double for both precisions (pair offsets are formed in double).
+// stored relative to the triangle's centroid, formed from its edges (good to
+// the rounding of its size, not of its place); the centroid itself is kept
+// as the sum of two doubles for both precisions.
 template <typename R>
 struct TriTab {
   const R* q[3];    // quadrature points, [k * nt + t], k < 7
   const R* v[3];    // vertices (free vertices of the local functions), [a * nt + t]
   const R* c;       // s_a * l_a, [a * nt + t]
-  const double* cen[3];  // centroid
+  const double* cen[3];    // centroid
+  const double* cenlo[3];  // what the rounding of cen leaves out
   const R* test;         // a test triangle's constants, kTestVals per triangle (upload in mesh.cpp)
   const double* rad;     // largest distance of a quadrature point from the centroid
   int64_t nt;

@@ -280,6 +280,7 @@ cbfm::TriTab<double> cbfm_mesh_s::tab64() const {
     t.q[i] = q64.as<double>() + i * 7 * nt;
     t.v[i] = v64.as<double>() + i * 3 * nt;
     t.cen[i] = cen.as<double>() + i * nt;
+    t.cenlo[i] = cen.as<double>() + (3 + i) * nt;
   }
   t.c = c64.as<double>();
   t.test = test64.as<double>();
@@ -295,6 +296,7 @@ cbfm::TriTab<float> cbfm_mesh_s::tab32() const {
     t.q[i] = q32.as<float>() + i * 7 * nt;
     t.v[i] = v32.as<float>() + i * 3 * nt;
     t.cen[i] = cen.as<double>() + i * nt;
+    t.cenlo[i] = cen.as<double>() + (3 + i) * nt;
   }
   t.c = c32.as<float>();
   t.test = test32.as<float>();
@@ -351,22 +353,26 @@ static void upload(cbfm_mesh_s* m) {
   const int64_t nt = h.nt;
   double bary[7][3];
   quad_rule(bary);
-  std::vector<double> q64(3 * 7 * nt), v64(3 * 3 * nt), c64(3 * nt), cen(3 * nt), xyz9(9 * nt), rad(nt),
+  std::vector<double> q64(3 * 7 * nt), v64(3 * 3 * nt), c64(3 * nt), cen(6 * nt), xyz9(9 * nt), rad(nt),
       test64(kTestVals * nt);
   std::vector<float> q32(q64.size()), v32(v64.size()), c32(c64.size()), test32(test64.size());
   for (int64_t t = 0; t < nt; ++t) {
     const double* P[3] = {&h.V[3 * h.T[t * 3]], &h.V[3 * h.T[t * 3 + 1]], &h.V[3 * h.T[t * 3 + 2]]};
     const double* c = &h.centroid[3 * t];
     for (int i = 0; i < 3; ++i) {
+      // the points about the centroid come from the edges, so that v_0 + v_1 +
+      // v_2 = 0 to the rounding of the triangle's size, as the moments along
+      // the medians take it; the centroid's own rounding is kept
       cen[i * nt + t] = c[i];
-      for (int k = 0; k < 7; ++k) {
-        const double x = bary[k][0] * P[0][i] + bary[k][1] * P[1][i] + bary[k][2] * P[2][i];
-        q64[(i * 7 + k) * nt + t] = x - c[i];
-      }
+      cen[(3 + i) * nt + t] = (((P[0][i] - c[i]) + (P[1][i] - c[i])) + (P[2][i] - c[i])) / 3.0;
+      double v[3];
       for (int a = 0; a < 3; ++a) {
-        v64[(i * 3 + a) * nt + t] = P[a][i] - c[i];
+        v[a] = ((P[a][i] - P[(a + 1) % 3][i]) + (P[a][i] - P[(a + 2) % 3][i])) / 3.0;
+        v64[(i * 3 + a) * nt + t] = v[a];
         xyz9[t * 9 + a * 3 + i] = P[a][i];
       }
+      for (int k = 0; k < 7; ++k)
+        q64[(i * 7 + k) * nt + t] = bary[k][0] * v[0] + bary[k][1] * v[1] + bary[k][2] * v[2];
     }
     for (int a = 0; a < 3; ++a)
       c64[a * nt + t] = h.tri_sign[t * 3 + a] * h.length[h.tri_edge[t * 3 + a]];
