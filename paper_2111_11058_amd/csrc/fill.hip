@@ -128,15 +128,20 @@ static FillConsts make_consts(const Media& md, int layout) {
 }
 
 // Fits of sin(2 pi x) / x and (cos(2 pi x) - 1) / x^2 in u = x^2 for
-// |x| <= 2/9 (Chebyshev interpolation at 8 nodes in 50-digit arithmetic; the
-// rounded coefficients give sine and cosine to 8e-17).
-constexpr double kCentredRev = 2.0 / 9.0;
-static const double kSinC[8] = {6.283185307179586,   -41.34170224039948,  81.60524927595382, -76.70585973341251,
-                                42.05869238059981,   -15.094574916251993, 3.818329843398246, -0.6978101945091162};
-static const double kCosC[8] = {-19.739208802178716, 64.9393940226682,   -85.45681720665131,  60.24464136500272,
-                                -26.426256236163066, 7.903512705704424,  -1.7138232485388523, 0.27490612566708106};
-// |k2i x| up to which exp(k2i x) is its degree-8 Taylor polynomial (4e-17)
-constexpr double kCentredExp = 1.0 / 16.0;
+// |x| <= 1/6 (Chebyshev interpolation at 8 nodes in 60-digit arithmetic): sine
+// and cosine to 2e-19 and 1.1e-20, within the fit errors of sincos_rev's nine
+// terms.  (Over 2/9 of a turn the sine's was 2.4e-17.)
+constexpr double kCentredRev = 1.0 / 6.0;
+static const long double kSinC[8] = {
+    6.28318530717958647581L, -41.3417022403997551045L, 81.6052492760711758391L,
+    -76.7058597519441391115L, 42.0586937868212439689L, -15.0946304281942693970L,
+    3.81943508867774844198L, -0.706629055507627513134L};
+static const long double kCosC[8] = {
+    -19.7392088021787172373L, 64.9393940226682896981L, -85.4568172066923722132L,
+    60.2446413714861824344L, -26.4262567281289714753L, 7.90353212584098589754L,
+    -1.71420988811353577400L, 0.277991016899364898739L};
+// |k2i x| up to which exp(k2i x) is its degree-8 Taylor polynomial (1e-18)
+constexpr double kCentredExp = 1.0 / 24.0;
 
 template <typename R>
 static PairConsts<R> make_pair_consts(const Media& md, int layout) {
@@ -167,11 +172,12 @@ static PairConsts<R> make_pair_consts(const Media& md, int layout) {
       pc.B[o][i][0] = (R)B.real();
       pc.B[o][i][1] = (R)B.imag();
     }
-  for (int i = 0; i < 2; ++i) {
-    double p = rev[i];
-    for (int t = 0; t < 8; ++t, p *= rev[i]) {
+  for (int i = 0; i < 2; ++i) {  // (in long double: one rounding a coefficient)
+    const long double r = (long double)(i == 0 ? md.k1 : md.k2r) / 6.28318530717958647692528676655900577L;
+    long double p = r;
+    for (int t = 0; t < 8; ++t, p *= r) {
       pc.sn[i][t] = (R)(kSinC[t] * p);
-      p *= rev[i];
+      p *= r;
       pc.cs[i][t] = (R)(kCosC[t] * p);
     }
   }

@@ -1,7 +1,8 @@
 """Rounding of the regular fill: entries do not depend on where the body lies
 (the points about a centroid and the centroids' offsets carry the rounding of
-the triangle and of the pair, not of the coordinates), and the float fill's
-error over long distances averages over the quadrature points."""
+the triangle and of the pair, not of the coordinates), the float fill's error
+over long distances averages over the quadrature points, and both precisions
+agree with the oracle on either side of the centred phases' bounds."""
 import dataclasses
 
 import numpy as np
@@ -78,3 +79,26 @@ def test_float_over_long_distances():
         e = np.linalg.norm(x - r) / np.linalg.norm(four) / (k * R)
         print(o, e)
         assert e < 1.1e-8
+
+
+@pytest.mark.parametrize("prec, tol", [("FP64", 1e-12), ("FP32", 2e-5)])
+@pytest.mark.parametrize("scale, loss", [(0.98, 0.0), (1.02, 0.0), (0.9, 0.98), (0.9, 1.02), (2.0, 3.0)])
+def test_centred_bounds(scale, loss, prec, tol):
+    """The largest pair's phase span just below and above a sixth of a turn,
+    its loss just below and above 1/24."""
+    from oracle import fill, mesh as om
+    from paper_2111_11058_amd import cbfm
+    from synth import configs
+    w = configs.small_cylinder()
+    m = om.build(w.V, w.T)
+    v = m.xyz - m.xyz.mean(axis=1, keepdims=True)
+    most = 2 * 0.69614047802963365 * np.linalg.norm(v, axis=2).max()
+    k0 = 2 * np.pi * scale / 6.0 / most / 3.0
+    eps = (3.0 - 1j * loss / 24.0 / most / k0) ** 2
+    k, _ = fill.media(k0, w.eta0, eps, 1.0)
+    print("centred bounds", scale, loss, prec, flush=True)
+    got = _fill(dataclasses.replace(w, k0=k0, eps_r=eps), getattr(cbfm, prec))
+    for o, (x, r) in enumerate(zip(got, fill.fill_ops(m, k))):
+        e = np.linalg.norm(x - r) / np.linalg.norm(r)
+        print(o, e)
+        assert e < tol
