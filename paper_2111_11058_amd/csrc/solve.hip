@@ -1221,9 +1221,12 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
     CBFM_HIP(hipEventRecord(side->ev_ready[par], s));
     CBFM_HIP(hipStreamWaitEvent(side->ls, side->ev_ready[par], 0));
     columns(j0, (int)(j - j0), nullptr, gm.active, side->ls);
-    CBFM_HIP(hipEventRecord(side->ev_done[par], side->ls));
     CBFM_HIP(hipGetLastError());
-    if (j - j0 == check_every && check(side->ls)) break;
+    const bool stop = j - j0 == check_every && check(side->ls);
+    // after the copy of the flags: the main stream, which waits for this
+    // event, changes them and copies them to the same host words next
+    CBFM_HIP(hipEventRecord(side->ev_done[par], side->ls));
+    if (stop) break;
   }
   if (side)
     for (hipEvent_t e : side->ev_done) CBFM_HIP(hipStreamWaitEvent(s, e, 0));
@@ -2189,12 +2192,14 @@ static bool run_sstep_cycle(SStep& ss, const GemmPlan& matvec, double2* V, doubl
                          bad, ss.broken.as<int32_t>(), j, m, nrhs);
     }
     CBFM_HIP(hipMemcpyAsync(gm.active, gs.active, nrhs * sizeof(int32_t), hipMemcpyDeviceToDevice, q));
-    CBFM_HIP(hipEventRecord(ss.ev_read[par], q));
     CBFM_HIP(hipGetLastError());
     total += S;
-    if (pending > 0 && all_done(flags.wait())) break;
-    flags.post(gs.active, q);
+    const bool stop = pending > 0 && all_done(flags.wait());
+    if (!stop) flags.post(gs.active, q);
     ++pending;
+    // after the copy of the flags (see run_cycle)
+    CBFM_HIP(hipEventRecord(ss.ev_read[par], q));
+    if (stop) break;
   }
   for (hipEvent_t e : ss.ev_read)  // recorded by this cycle or an earlier one (or never: no wait)
     CBFM_HIP(hipStreamWaitEvent(s, e, 0));
