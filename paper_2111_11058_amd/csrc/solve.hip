@@ -1092,9 +1092,12 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
                       const TB* xb = nullptr, double2* qd = nullptr) {
   const double vb = (double)sizeof(TB), wb = (double)sizeof(TW);
   constexpr int check_every = kChunk;
-  // w is kept as the next basis vector unless that rounds it to another
-  // type (its range), or the iterate is built from another basis
-  gs.raw = std::is_same<TB, TW>::value && xb == nullptr;
+  // w is kept as the next basis vector in double, unless the iterate is built
+  // from another basis.  Not in float: the next product has the square of
+  // the operator's norm, out of float's range for norms beyond 1e19 or
+  // below 1e-19 (a reduced matrix of a body of some nanometres, in metres,
+  // has 1e-18; in double the norm may be 1e-100 to 1e100)
+  gs.raw = std::is_same<TB, double2>::value && std::is_same<TW, double2>::value && xb == nullptr;
   const int64_t ng = (nrhs + 63) / 64;
   auto all_done = [&](const int32_t* a) { return std::none_of(a, a + nrhs, [](int32_t v) { return v != 0; }); };
   // 64-row update blocks where 128-row ones would not give every CU one
