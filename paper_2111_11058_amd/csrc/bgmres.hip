@@ -265,7 +265,7 @@ __global__ void __launch_bounds__(256) chol_pivot_kernel(const double* __restric
     if (tid < PMAX) {
       const double d = tid < p ? S[tid][tid].re.hi + S[tid][tid].re.lo : 1.0;
       dsc[tid] = d > 0 ? sqrt(d) : 0.0;
-      if (tid < p && !(d >= 1e-20 * dmax0)) redo_s = 1;
+      if (tid < p && !(d > 0 && d >= 1e-20 * dmax0)) redo_s = 1;  // (one zero column: dmax0 is zero too)
     }
     __syncthreads();
     if (!redo_s) {  // uniform
