@@ -834,21 +834,6 @@ class BlockGmres {
     else
       mvx_.reset(new XGemmPlan(mvx, XG_FP32, s));
     upd_.reset(new GemmPlan(upd, s, false));
-    CBFM_HIP(hipStreamCreateWithFlags(&ls_, hipStreamNonBlocking));
-    for (int k = 0; k < 2; ++k) {
-      CBFM_HIP(hipEventCreateWithFlags(&ev_ready_[k], hipEventDisableTiming));
-      CBFM_HIP(hipEventCreateWithFlags(&ev_read_[k], hipEventDisableTiming));
-    }
-  }
-  ~BlockGmres() {
-    if (ls_) {
-      (void)hipStreamSynchronize(ls_);
-      (void)hipStreamDestroy(ls_);
-    }
-    for (int k = 0; k < 2; ++k) {
-      if (ev_ready_[k]) (void)hipEventDestroy(ev_ready_[k]);
-      if (ev_read_[k]) (void)hipEventDestroy(ev_read_[k]);
-    }
   }
   BlockGmres(const BlockGmres&) = delete;
   BlockGmres& operator=(const BlockGmres&) = delete;
@@ -1032,8 +1017,9 @@ class BlockGmres {
   std::unique_ptr<Scratch> dots_dev_, dots_ws_;
   std::unique_ptr<GemmPlan> mv_, upd_;
   std::unique_ptr<XGemmPlan> mvx_;
-  hipStream_t ls_ = nullptr;  // the least-squares stream (default priority)
-  hipEvent_t ev_ready_[2] = {nullptr, nullptr}, ev_read_[2] = {nullptr, nullptr};
+  SideLease lease_;
+  const hipStream_t ls_ = lease_.stream;  // the least-squares stream
+  const hipEvent_t ev_ready_[2] = {lease_.ev[0], lease_.ev[1]}, ev_read_[2] = {lease_.ev[2], lease_.ev[3]};
 };
 
 }  // namespace

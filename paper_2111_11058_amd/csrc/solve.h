@@ -56,6 +56,30 @@ struct GmresSpec {
                            // max_iter then count block iterations
 };
 
+// A second stream for the least-squares steps of a solve (non-blocking,
+// default priority) from a pool, and four events.  The stream is given back
+// idle and outlives the solve: this runtime has aborted over events of
+// destroyed streams, and a nested solve (the inexact CMP's) would create and
+// destroy one in every outer iteration.  The events, two of them recorded on
+// the caller's stream, end with the lease, which the caller's stream
+// outlives.  Every lease has a stream of its own, so threads and nested
+// solves share none; at most kSpareSides streams are kept unused.  Declare
+// what records further events on the stream after the lease, so that it
+// ends first.
+class SideLease {
+ public:
+  SideLease();
+  ~SideLease();
+  SideLease(const SideLease&) = delete;
+  SideLease& operator=(const SideLease&) = delete;
+  hipStream_t stream = nullptr;
+  hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+
+ private:
+  void give_back();
+  int dev_ = 0;
+};
+
 // Device flags read back through pinned host memory: post() queues a copy
 // and an event, wait() blocks on the last posted copy; sync_read() copies and
 // waits at once.

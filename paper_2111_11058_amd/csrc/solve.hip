@@ -1039,39 +1039,72 @@ static void apply_op(const double2* A, int64_t lda, int64_t n, int64_t nrhs, con
   zgemm_batched(d, s);
 }
 
-// The second stream of plain cycles (default priority), its events and the
-// copies of the active flags that the main stream's kernels read, two of each
-// by the parity of the chunk.
+// ---- the pool of SideLease
+namespace {
+constexpr size_t kSpareSides = 16;
+struct SidePool {
+  std::mutex mu;
+  std::vector<std::pair<int, hipStream_t>> spare;  // device, idle stream
+};
+// never destroyed: the runtime may be torn down before static destructors run
+SidePool& side_pool() {
+  static SidePool* p = new SidePool;
+  return *p;
+}
+}  // namespace
+
+SideLease::SideLease() {
+  CBFM_HIP(hipGetDevice(&dev_));
+  {
+    std::lock_guard<std::mutex> lk(side_pool().mu);
+    auto& sp = side_pool().spare;
+    for (size_t i = sp.size(); i-- > 0 && !stream;)
+      if (sp[i].first == dev_) {
+        stream = sp[i].second;
+        sp.erase(sp.begin() + (ptrdiff_t)i);
+      }
+  }
+  try {
+    if (!stream) CBFM_HIP(hipStreamCreateWithFlags(&stream, hipStreamNonBlocking));
+    for (hipEvent_t& e : ev) CBFM_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  } catch (...) {
+    give_back();
+    throw;
+  }
+}
+
+SideLease::~SideLease() { give_back(); }
+
+void SideLease::give_back() {
+  if (!stream) return;
+  (void)hipStreamSynchronize(stream);
+  for (hipEvent_t e : ev)  // the events first, while both their streams are there
+    if (e) (void)hipEventDestroy(e);
+  {
+    std::lock_guard<std::mutex> lk(side_pool().mu);
+    auto& sp = side_pool().spare;
+    if (sp.size() < kSpareSides) {
+      sp.push_back({dev_, stream});
+      return;
+    }
+  }
+  (void)hipStreamDestroy(stream);
+}
+
+// The second stream of plain cycles, its events and the copies of the active
+// flags that the main stream's kernels read, two of each by the parity of the
+// chunk.
 struct ColumnSide {
-  hipStream_t ls = nullptr;
-  hipEvent_t ev_ready[2] = {nullptr, nullptr}, ev_done[2] = {nullptr, nullptr};
   int64_t nrhs;
   Scratch flags;
-  ColumnSide(int64_t nrhs_, hipStream_t s) : nrhs(nrhs_), flags(2 * nrhs_ * sizeof(int32_t), s) {
-    try {
-      CBFM_HIP(hipStreamCreateWithFlags(&ls, hipStreamNonBlocking));
-      for (int k = 0; k < 2; ++k) {
-        CBFM_HIP(hipEventCreateWithFlags(&ev_ready[k], hipEventDisableTiming));
-        CBFM_HIP(hipEventCreateWithFlags(&ev_done[k], hipEventDisableTiming));
-      }
-    } catch (...) {
-      close();
-      throw;
-    }
-  }
-  ~ColumnSide() { close(); }
+  SideLease lease;
+  hipStream_t ls;
+  hipEvent_t ev_ready[2], ev_done[2];
+  ColumnSide(int64_t nrhs_, hipStream_t s)
+      : nrhs(nrhs_), flags(2 * nrhs_ * sizeof(int32_t), s), ls(lease.stream), ev_ready{lease.ev[0], lease.ev[1]},
+        ev_done{lease.ev[2], lease.ev[3]} {}
   ColumnSide(const ColumnSide&) = delete;
   ColumnSide& operator=(const ColumnSide&) = delete;
-  void close() {
-    if (ls) {
-      (void)hipStreamSynchronize(ls);
-      (void)hipStreamDestroy(ls);
-    }
-    for (int k = 0; k < 2; ++k) {
-      if (ev_ready[k]) (void)hipEventDestroy(ev_ready[k]);
-      if (ev_done[k]) (void)hipEventDestroy(ev_done[k]);
-    }
-  }
   int32_t* seen(int k) const { return flags.as<int32_t>() + k * nrhs; }
 };
 
@@ -2003,8 +2036,9 @@ struct SStep {
   // the device) and the workspace of their K-split parts
   std::vector<GemmDesc> dots;
   std::unique_ptr<Scratch> dots_dev, dots_ws;
-  hipStream_t ls = nullptr;  // the least-squares stream (default priority)
-  hipEvent_t ev_ready[2] = {nullptr, nullptr}, ev_read[2] = {nullptr, nullptr};
+  SideLease lease;
+  hipStream_t ls;  // the least-squares stream
+  hipEvent_t ev_ready[2], ev_read[2];
   SStep(int S_, int64_t n_, int64_t nrhs_, int64_t m_, hipStream_t s)
       : S(S_), n(n_), nrhs(nrhs_), m(m_), M1(m_ + S_ + 1), HS((m_ + S_) * (m_ + S_ + 1)), cst(m_ + 1),
         C1(2 * nrhs_ * (m_ + 1) * S_ * sizeof(double2), s), C2(2 * nrhs_ * (m_ + 1) * S_ * sizeof(double2), s),
@@ -2012,31 +2046,10 @@ struct SStep {
         Rt(2 * nrhs_ * S_ * S_ * sizeof(double2), s), sig(2 * nrhs_ * S_ * sizeof(double), s),
         theta(nrhs_ * S_ * sizeof(double2), s), broken(nrhs_ * sizeof(int32_t), s),
         bad(2 * nrhs_ * sizeof(int32_t), s), seen(2 * nrhs_ * sizeof(int32_t), s),
-        part(S_ * nrhs_ * ((n_ + 255) / 256) * sizeof(double), s) {
-    try {
-      CBFM_HIP(hipStreamCreateWithFlags(&ls, hipStreamNonBlocking));
-      for (int k = 0; k < 2; ++k) {
-        CBFM_HIP(hipEventCreateWithFlags(&ev_ready[k], hipEventDisableTiming));
-        CBFM_HIP(hipEventCreateWithFlags(&ev_read[k], hipEventDisableTiming));
-      }
-    } catch (...) {
-      close();
-      throw;
-    }
-  }
-  ~SStep() { close(); }
+        part(S_ * nrhs_ * ((n_ + 255) / 256) * sizeof(double), s), ls(lease.stream),
+        ev_ready{lease.ev[0], lease.ev[1]}, ev_read{lease.ev[2], lease.ev[3]} {}
   SStep(const SStep&) = delete;
   SStep& operator=(const SStep&) = delete;
-  void close() {
-    if (ls) {
-      (void)hipStreamSynchronize(ls);
-      (void)hipStreamDestroy(ls);
-    }
-    for (int k = 0; k < 2; ++k) {
-      if (ev_ready[k]) (void)hipEventDestroy(ev_ready[k]);
-      if (ev_read[k]) (void)hipEventDestroy(ev_read[k]);
-    }
-  }
   double2* c1(int par) const { return C1.as<double2>() + par * nrhs * cst * S; }
   double2* c2(int par) const { return C2.as<double2>() + par * nrhs * cst * S; }
   double2* rt(int par) const { return Rt.as<double2>() + par * nrhs * S * S; }
@@ -2312,8 +2325,9 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
   // read one check later, so the host never waits for the device inside a
   // cycle; iterations queued after the last right-hand side converged do
   // nothing (every kernel skips inactive right-hand sides).
-  PinnedFlags flags(nrhs);
-  std::unique_ptr<ColumnSide> side(new ColumnSide(nrhs, s));
+  ColumnSide side(nrhs, s);
+  std::unique_ptr<SStep> sst;
+  PinnedFlags flags(nrhs);  // (after side and sst, on whose streams its event is recorded)
   auto all_done = [&](const int32_t* a) {
     return std::none_of(a, a + nrhs, [](int32_t v) { return v != 0; });
   };
@@ -2368,7 +2382,6 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
   // s-step: a first plain cycle of S + 1 iterations gives the shifts; then
   // s-step cycles, and plain ones for good after a breakdown
   bool sstep_on = S > 0 && ms >= S, shifts_ready = false;
-  std::unique_ptr<SStep> sst;
   for (;;) {
     // r = b - A x  (x = 0 on the first cycle)
     double2* r = f32 ? r64.as<double2>() : u.as<double2>();
@@ -2390,10 +2403,10 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
     if (sstep_on && shifts_ready && total + S > p.max_iter) sstep_on = false;
     if (f32)
       run_cycle(matvec32, dyn32.get(), dyn32 ? dyn32->desc(0) : nullptr, jdev.as<int64_t>(), V.as<float2>(),
-                u.as<float2>(), vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, side.get());
+                u.as<float2>(), vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, &side);
     else if (b32)
       run_cycle(matvec, dyn.get(), dyn ? dyn->desc(0) : nullptr, jdev.as<int64_t>(), V.as<float2>(), u.as<double2>(),
-                vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, side.get(), (const float2*)nullptr,
+                vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, &side, (const float2*)nullptr,
                 qd.as<double2>());
     else if (sstep_on && !shifts_ready) {
       const int64_t m1 = std::min<int64_t>(S + 1, mres);
@@ -2401,7 +2414,7 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
       g1.ms = m1 + 1;
       CBFM_HIP(hipMemsetAsync(gs.H, 0, (size_t)nrhs * (m1 + 1) * m1 * sizeof(double2), s));
       run_cycle(matvec, (const GemmPlan*)nullptr, nullptr, jdev.as<int64_t>(), V.as<double2>(), u.as<double2>(),
-                vstride, n, nrhs, m1, p.max_iter, total, g1, part.as<double>(), np, flags, x, s, side.get());
+                vstride, n, nrhs, m1, p.max_iter, total, g1, part.as<double>(), np, flags, x, s, &side);
       std::vector<int32_t> its1(nrhs);
       CBFM_HIP(hipMemcpyAsync(its1.data(), gs.its, nrhs * sizeof(int32_t), hipMemcpyDeviceToHost, s));
       CBFM_HIP(hipStreamSynchronize(s));
@@ -2415,10 +2428,10 @@ GmresResult gmres_run(KrylovOp& op, int64_t n, int64_t nrhs, const double2* b, d
         sstep_on = false;
     } else if (dense)
       run_cycle(matvec, dyn.get(), dyn ? dyn->desc(0) : nullptr, jdev.as<int64_t>(), V.as<double2>(),
-                u.as<double2>(), vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, side.get());
+                u.as<double2>(), vstride, n, nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, &side);
     else
       run_cycle(opmv, (const OpMV*)nullptr, nullptr, jdev.as<int64_t>(), V.as<double2>(), u.as<double2>(), vstride, n,
-                nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, side.get(), op.xbasis());
+                nrhs, mres, p.max_iter, total, gs, part.as<double>(), np, flags, x, s, &side, op.xbasis());
     if (total >= p.max_iter) break;
   }
   CBFM_HIP(hipMemcpyAsync(out.its.data(), gs.its, nrhs * sizeof(int32_t), hipMemcpyDeviceToHost, s));
