@@ -1236,9 +1236,11 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
         }
       }
     } catch (...) {
+      (void)hipStreamSynchronize(s);
       (void)hipGraphExecDestroy(exec);
       throw;
     }
+    (void)hipStreamSynchronize(s);  // (the last chunks may still run)
     CBFM_HIP(hipGraphExecDestroy(exec));
   }
   // chunks of iterations on s; the column steps of chunk k run on the second
