@@ -265,7 +265,9 @@ __global__ void __launch_bounds__(256) chol_pivot_kernel(const double* __restric
     if (tid < PMAX) {
       const double d = tid < p ? S[tid][tid].re.hi + S[tid][tid].re.lo : 1.0;
       dsc[tid] = d > 0 ? sqrt(d) : 0.0;
-      if (tid < p && !(d > 0 && d >= 1e-20 * dmax0)) redo_s = 1;  // (one zero column: dmax0 is zero too)
+      // (p = 1, a zero column: rank 0 in the first pass; in the second the
+      // first took rounding for a direction, and a zero vector takes its place)
+      if (tid < p && !(d >= 1e-20 * dmax0 && (d > 0 || must_full))) redo_s = 1;
     }
     __syncthreads();
     if (!redo_s) {  // uniform
@@ -320,7 +322,7 @@ __global__ void __launch_bounds__(256) chol_pivot_kernel(const double* __restric
           const double fr = b >= a ? g * dsc[b] : 0.0;
           M[a * p + b] = make_double2(x[u].x * fr, x[u].y * fr);
           // T = R^{-1}: T[b][a] = conj((R^{-H})[a][b]), zero below the diagonal
-          const double ft = b <= a ? g / dsc[b] : 0.0;
+          const double ft = b <= a && dsc[b] > 0 ? g / dsc[b] : 0.0;
           T[b * p + a] = make_double2(y[u].x * ft, -y[u].y * ft);
         }
         if (tid == 0) rank[0] = p;

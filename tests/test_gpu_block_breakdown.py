@@ -33,3 +33,26 @@ def test_zero_block(diag):
         o = cbfm.solve(mesh, med, h, Zr, inc, tol=1e-10, max_iter=8, restart=4, use_cmp=False, block=1)
         print("zero block", diag, e, o, flush=True)
         assert o["status"] == "OK" and o["relres"][0] <= 1e-15
+
+
+@pytest.mark.parametrize("diag", [(1.0, 1.0), (2.0, 3.0)])
+def test_rounding_block(diag):
+    """The same with tested fields of any phase: the block is rounding, which
+    the first pass may take for a direction and the second projects to zero."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from oracle import excitation, mesh as om
+    from paper_2111_11058_amd import cbfm
+    from synth import configs
+    w = configs.sphere_c1()
+    m = om.build(w.V, w.T)
+    mesh = cbfm.Mesh(w.V, w.T)
+    med = cbfm.Medium.make(w.k0, w.eta0, w.eps_r, w.mu_r)
+    inc = configs.random_incidences(24, 5)
+    CJ = excitation.rhs(m, inc, w.k0, w.eta0)[:m.ne, :1].copy()
+    h = cbfm.cbf_import(mesh, [np.zeros((m.ne, 1), complex)], [CJ], [np.ones(1)])
+    Zr = torch.tensor(np.diag(diag).astype(complex), device="cuda")
+    print("rounding block", diag, flush=True)
+    for q in range(len(inc)):
+        o = cbfm.solve(mesh, med, h, Zr, inc[q:q + 1], tol=1e-10, max_iter=8, restart=4, use_cmp=False, block=1)
+        assert o["status"] == "OK" and o["relres"][0] <= 1e-14, (q, o)
