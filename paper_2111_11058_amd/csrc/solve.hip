@@ -524,9 +524,7 @@ __device__ __forceinline__ void column_step(const GmresState& st, int64_t m, int
 // on small systems (118 iterations of order 156: 4.8 ms with a launch per
 // step, 2.6).  correct == 0: the end of a cycle, column j0 - 1 alone.
 __global__ void __launch_bounds__(256) columns_kernel(GmresState st, int64_t m, int64_t j0, int cnt, int64_t nrhs,
-                                                      int correct, int32_t* __restrict__ seen,
-                                                      const int64_t* __restrict__ jp) {
-  if (jp) j0 = *jp;
+                                                      int correct, int32_t* __restrict__ seen) {
   const int64_t c = (int64_t)blockIdx.x;
   const int tid = threadIdx.x;
   bool act = st.active[c] != 0;
@@ -670,9 +668,7 @@ __global__ void __launch_bounds__(1024 / RPL) dcgs_update_kernel(TB* __restrict_
 // fewer, several column offsets each (added by a butterfly); the eight
 // wavefronts take interleaved columns of the row (contiguous in H, read once
 // for the chunk), two columns in flight each, summed in a fixed order.
-__global__ void __launch_bounds__(512) hbulk_kernel(int64_t nrhs, int64_t m, int64_t j0, int cnt, GmresState st,
-                                                    const int64_t* __restrict__ jp) {
-  if (jp) j0 = *jp;
+__global__ void __launch_bounds__(512) hbulk_kernel(int64_t nrhs, int64_t m, int64_t j0, int cnt, GmresState st) {
   const int64_t f = j0 - 1;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   __shared__ double2 shp[7][kChunk][64];
@@ -684,7 +680,7 @@ __global__ void __launch_bounds__(512) hbulk_kernel(int64_t nrhs, int64_t m, int
   while (cw > 1 && cw / 2 >= nrhs) cw >>= 1;
   const int sub = 64 / cw, lc = lane & (cw - 1), li = lane / cw;
   const int64_t l = blockIdx.x / ng, c = (blockIdx.x % ng) * 64 + lc;
-  if (l > f || f <= 0) return;  // graph replays launch the rows of the longest column
+  if (l > f || f <= 0) return;
   const bool on = c < nrhs && st.active[c];
   const int64_t cc = on ? c : 0;  // idle lanes read valid entries and discard them
   const int64_t lo = l > 0 ? l - 1 : 0;
@@ -756,14 +752,19 @@ __global__ void normalize_kernel(const TW* __restrict__ w, TB* __restrict__ V, i
   if (qd) qd[c * n + k] = stored2(out, v);
 }
 
-// Device-side iteration counter of graph replays, and the matrix-vector
-// product's operand q_j taken from it.
+// Device-side iteration counter of graph replays: set, or moved on at the
+// start of an iteration, together with the matrix-vector product's operand
+// q_j taken from it (a launch less than with a counter kernel at the end).
 __global__ void counter_kernel(int64_t* __restrict__ jp, int64_t value, int add) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *jp = add ? *jp + value : value;
 }
 template <typename D, typename TV>
-__global__ void point_matvec_kernel(D* __restrict__ desc, const TV* V, int64_t vstride, const int64_t* __restrict__ jp) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) desc->B = V + (*jp) * vstride;
+__global__ void point_matvec_kernel(D* __restrict__ desc, const TV* V, int64_t vstride, int64_t* __restrict__ jp) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) {
+    const int64_t j = *jp + 1;
+    *jp = j;
+    desc->B = V + j * vstride;
+  }
 }
 
 // y = R^{-1} g over the first kc[c] rows (R upper triangular), in place in
@@ -1093,7 +1094,7 @@ void SideLease::give_back() {
 
 // The second stream of plain cycles, its events and the copies of the active
 // flags that the main stream's kernels read, two of each by the parity of the
-// chunk.
+// chunk (a third copy for captured chunks, whose kernels read one place).
 struct ColumnSide {
   int64_t nrhs;
   Scratch flags;
@@ -1101,20 +1102,62 @@ struct ColumnSide {
   hipStream_t ls;
   hipEvent_t ev_ready[2], ev_done[2];
   ColumnSide(int64_t nrhs_, hipStream_t s)
-      : nrhs(nrhs_), flags(2 * nrhs_ * sizeof(int32_t), s), ls(lease.stream), ev_ready{lease.ev[0], lease.ev[1]},
+      : nrhs(nrhs_), flags(3 * nrhs_ * sizeof(int32_t), s), ls(lease.stream), ev_ready{lease.ev[0], lease.ev[1]},
         ev_done{lease.ev[2], lease.ev[3]} {}
   ColumnSide(const ColumnSide&) = delete;
   ColumnSide& operator=(const ColumnSide&) = delete;
   int32_t* seen(int k) const { return flags.as<int32_t>() + k * nrhs; }
 };
 
+// The captured iterations of a chunk; the graph is destroyed after its last
+// launch on s has run.
+struct ChunkGraph {
+  hipStream_t s;
+  hipGraphExec_t exec = nullptr;
+  explicit ChunkGraph(hipStream_t s_) : s(s_) {}
+  ~ChunkGraph() {
+    if (!exec) return;
+    (void)hipStreamSynchronize(s);
+    (void)hipGraphExecDestroy(exec);
+  }
+  ChunkGraph(const ChunkGraph&) = delete;
+  ChunkGraph& operator=(const ChunkGraph&) = delete;
+  template <typename F>
+  void capture(const F& enqueue) {
+    hipStream_t cs;
+    CBFM_HIP(hipStreamCreate(&cs));
+    hipGraph_t graph = nullptr;
+    auto drop = [&] {
+      if (graph) (void)hipGraphDestroy(graph);
+      (void)hipStreamSynchronize(cs);
+      scratch_forget_stream(cs);
+      (void)hipStreamDestroy(cs);
+    };
+    hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+      try {
+        enqueue(cs);
+      } catch (...) {
+        (void)hipStreamEndCapture(cs, &graph);
+        drop();
+        throw;
+      }
+      e = hipStreamEndCapture(cs, &graph);
+    }
+    if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+    drop();
+    CBFM_HIP(e);
+  }
+};
+
 // One GMRES cycle from the normalised residual in V[0]: up to mres Arnoldi
 // iterations (the matrix-vector products by mv.launch(j)), the last column,
 // the triangular solve and x += Q y.  total counts the iterations of all
 // cycles against max_iter.  With a graph plan (dyn, its descriptor dyn_desc
-// and the device counter jdev), chunks of four iterations are captured once
-// into a HIP graph whose kernels read the iteration index from jdev, and
-// the graph is replayed; the remaining iterations run as plain launches.
+// and the device counter jdev), chunks of four iterations (all but their
+// column steps) are captured once into a HIP graph whose kernels read the
+// iteration index from jdev, and the graph is replayed; the remaining
+// iterations run as plain launches.
 // The basis is stored as TB and the work vector w as TW.  With qd (a float
 // basis beside a double w), every matrix-vector product reads its operand
 // from qd, where the newest basis vector's stored value is kept in double.
@@ -1136,11 +1179,10 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
   // 64-row update blocks where 128-row ones would not give every CU one
   const int np64 = (int64_t)np * nrhs < 256 ? (int)((n + 63) / 64) : 0;
   // the least-squares steps of iterations j..j+cnt-1
-  auto columns = [&](int64_t j, int cnt, const int64_t* jp, int32_t* seen, hipStream_t q) {
-    const int64_t rows = jp ? mres : j;
-    if (rows > 1)
-      hipLaunchKernelGGL(hbulk_kernel, dim3((unsigned)(rows * ng)), dim3(512), 0, q, nrhs, mres, j, cnt, gs, jp);
-    hipLaunchKernelGGL(columns_kernel, dim3((unsigned)nrhs), dim3(256), 0, q, gs, mres, j, cnt, nrhs, 1, seen, jp);
+  auto columns = [&](int64_t j, int cnt, int32_t* seen, hipStream_t q) {
+    if (j > 1)
+      hipLaunchKernelGGL(hbulk_kernel, dim3((unsigned)(j * ng)), dim3(512), 0, q, nrhs, mres, j, cnt, gs);
+    hipLaunchKernelGGL(columns_kernel, dim3((unsigned)nrhs), dim3(256), 0, q, gs, mres, j, cnt, nrhs, 1, seen);
   };
   // enqueue iteration j (jp == nullptr) or the iteration *jp (graph capture)
   auto iteration = [&](int64_t j, const int64_t* jp, const GmresState& gs, hipStream_t q) {
@@ -1149,7 +1191,9 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
       if constexpr (std::is_same<TB, TW>::value) {
         using D = typename std::conditional<std::is_same<TB, double2>::value, GemmDesc, GemmDescX>::type;
         hipLaunchKernelGGL((point_matvec_kernel<D, TB>), dim3(1), dim3(64), 0, q, static_cast<D*>(dyn_desc), V,
-                           vstride, jp);
+                           vstride, jdev);
+      } else {
+        hipLaunchKernelGGL(counter_kernel, dim3(1), dim3(64), 0, q, jdev, (int64_t)1, 1);
       }
       dyn->launch(0, q);
     } else {
@@ -1182,83 +1226,53 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
     if (!gs.raw)
       hipLaunchKernelGGL((normalize_kernel<TB, TW>), grid2(n, nrhs), dim3(256), 0, q, w, V, vstride, n, part,
                          np64 ? np64 : np, gs, mres, j, nrhs, jp, qd);
-    if (!jp) {  // the column steps follow on the second stream
-      CBFM_HIP(hipGetLastError());
-      return;
-    }
-    columns(j, 1, jp, nullptr, q);
-    hipLaunchKernelGGL(counter_kernel, dim3(1), dim3(64), 0, q, jdev, (int64_t)1, 1);
     CBFM_HIP(hipGetLastError());
   };
   int pending = 0;  // flag copies queued in this cycle
   int64_t j = 0;
-  bool done = false;
   auto check = [&](hipStream_t q) {
     if (pending > 0 && all_done(flags.wait())) return true;
     flags.post(gs.active, q);
     ++pending;
     return false;
   };
+  ChunkGraph chunk(s);
   if (dyn && mres >= check_every && max_iter - total >= check_every) {
-    hipStream_t cs;
-    CBFM_HIP(hipStreamCreate(&cs));
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-      try {
-        for (int q = 0; q < check_every; ++q) iteration(0, jdev, gs, cs);
-      } catch (...) {
-        (void)hipStreamEndCapture(cs, &graph);
-        if (graph) (void)hipGraphDestroy(graph);
-        (void)hipStreamSynchronize(cs);
-        scratch_forget_stream(cs);
-        (void)hipStreamDestroy(cs);
-        throw;
-      }
-      e = hipStreamEndCapture(cs, &graph);
-    }
-    if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    if (graph) (void)hipGraphDestroy(graph);
-    (void)hipStreamSynchronize(cs);
-    scratch_forget_stream(cs);
-    (void)hipStreamDestroy(cs);
-    CBFM_HIP(e);
-    hipLaunchKernelGGL(counter_kernel, dim3(1), dim3(64), 0, s, jdev, (int64_t)0, 0);
-    try {
-      while (j + check_every <= mres && total + check_every <= max_iter) {
-        CBFM_HIP(hipGraphLaunch(exec, s));
-        j += check_every;
-        total += check_every;
-        if (check(s)) {
-          done = true;
-          break;
-        }
-      }
-    } catch (...) {
-      (void)hipStreamSynchronize(s);
-      (void)hipGraphExecDestroy(exec);
-      throw;
-    }
-    (void)hipStreamSynchronize(s);  // (the last chunks may still run)
-    CBFM_HIP(hipGraphExecDestroy(exec));
+    GmresState gm = gs;
+    gm.active = side->seen(2);
+    chunk.capture([&](hipStream_t q) {
+      for (int t = 0; t < check_every; ++t) iteration(0, jdev, gm, q);
+    });
+    hipLaunchKernelGGL(counter_kernel, dim3(1), dim3(64), 0, s, jdev, (int64_t)-1, 0);
   }
-  // chunks of iterations on s; the column steps of chunk k run on the second
-  // stream beside chunk k + 1, whose kernels take a right-hand side as long
-  // as it was active after chunk k - 2
-  if (!done && j < mres && total < max_iter)
-    for (int k = 0; k < 2; ++k)
-      CBFM_HIP(hipMemcpyAsync(side->seen(k), gs.active, nrhs * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-  for (int64_t k = 0; !done && j < mres && total < max_iter; ++k) {
+  // chunks of iterations on s, replayed or launched; the column steps of
+  // chunk k run on the second stream beside chunk k + 1, whose kernels take a
+  // right-hand side as long as it was active after chunk k - 2.  (Captured
+  // too, the column steps lie between the iterations: 826 iterations, 32
+  // right-hand sides, mixed form, 57.1 ms with one after each, 51.2 with one
+  // launch after four, 49.0 beside the next chunk)
+  auto copy_flags = [&](int32_t* to, const int32_t* from) {
+    CBFM_HIP(hipMemcpyAsync(to, from, nrhs * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
+  };
+  if (j < mres && total < max_iter)
+    for (int k = 0; k < 2; ++k) copy_flags(side->seen(k), gs.active);
+  for (int64_t k = 0; j < mres && total < max_iter; ++k) {
     const int par = (int)(k & 1);
     GmresState gm = gs;
     gm.active = side->seen(par);
     if (k >= 2) CBFM_HIP(hipStreamWaitEvent(s, side->ev_done[par], 0));
     const int64_t j0 = j;
-    for (; j < j0 + check_every && j < mres && total < max_iter; ++j, ++total) iteration(j, nullptr, gm, s);
+    if (chunk.exec && j + check_every <= mres && total + check_every <= max_iter) {
+      copy_flags(side->seen(2), gm.active);
+      CBFM_HIP(hipGraphLaunch(chunk.exec, s));
+      j += check_every;
+      total += check_every;
+    } else {
+      for (; j < j0 + check_every && j < mres && total < max_iter; ++j, ++total) iteration(j, nullptr, gm, s);
+    }
     CBFM_HIP(hipEventRecord(side->ev_ready[par], s));
     CBFM_HIP(hipStreamWaitEvent(side->ls, side->ev_ready[par], 0));
-    columns(j0, (int)(j - j0), nullptr, gm.active, side->ls);
+    columns(j0, (int)(j - j0), gm.active, side->ls);
     CBFM_HIP(hipGetLastError());
     const bool stop = j - j0 == check_every && check(side->ls);
     // after the copy of the flags: the main stream, which waits for this
@@ -1266,13 +1280,12 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
     CBFM_HIP(hipEventRecord(side->ev_done[par], side->ls));
     if (stop) break;
   }
-  if (side)
-    for (hipEvent_t e : side->ev_done) CBFM_HIP(hipStreamWaitEvent(s, e, 0));
+  for (hipEvent_t e : side->ev_done) CBFM_HIP(hipStreamWaitEvent(s, e, 0));
   // the last column of the cycle, taken without the delayed correction
   if (j > 0 && gs.raw)
     hipLaunchKernelGGL(norm_kernel<TB>, dim3((unsigned)nrhs), dim3(256), 0, s, V + j * vstride, n, gs.nrm, gs.active);
   if (j > 0)
-    hipLaunchKernelGGL(columns_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, gs, mres, j, 1, nrhs, 0, nullptr, nullptr);
+    hipLaunchKernelGGL(columns_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, gs, mres, j, 1, nrhs, 0, nullptr);
   hipLaunchKernelGGL(backsolve_kernel, dim3((unsigned)nrhs), dim3(256), 0, s, gs, mres, nrhs);
   // x += Q y, or Z y for flexible GMRES (the preconditioned vectors z_j)
   hipLaunchKernelGGL(x_update_kernel<TB>, dim3((unsigned)((int64_t)np * nrhs)), dim3(512), 0, s, gs, xb ? xb : V,
