@@ -566,8 +566,8 @@ __global__ void __launch_bounds__(256) columns_kernel(GmresState st, int64_t m, 
 // side, wavefront v summing over the basis vectors i = v mod W, and |a|^2 and
 // a^H b beside them; wavefront 0 combines the partial sums in a fixed order
 // and completes the update, storing the row block's sum of |w|^2 in part.
-// Sixteen wavefronts of one row per lane where eight of two would leave CUs
-// without a block: 594 rows x 8 right-hand sides 12.3 -> 8.5 us; 4,480 x 1
+// Sixteen wavefronts of one row per lane where eight of two would leave half
+// of the CUs without a block: 594 rows x 8 right-hand sides 12.3 -> 8.5 us; 4,480 x 1
 // 5.3 and 9.3 (the basis range split over eight blocks, and a pass adding
 // their sums) -> 5.8.
 template <typename TB, typename TW, int RPL>
@@ -1176,8 +1176,11 @@ static void run_cycle(const MV& mv, const MV* dyn, void* dyn_desc, int64_t* jdev
   gs.raw = std::is_same<TB, double2>::value && std::is_same<TW, double2>::value && xb == nullptr;
   const int64_t ng = (nrhs + 63) / 64;
   auto all_done = [&](const int32_t* a) { return std::none_of(a, a + nrhs, [](int32_t v) { return v != 0; }); };
-  // 64-row update blocks where 128-row ones would not give every CU one
-  const int np64 = (int64_t)np * nrhs < 256 ? (int)((n + 63) / 64) : 0;
+  // 64-row update blocks where 128-row ones would leave half of the CUs
+  // without one.  120 iterations with 64 against 128 rows: 896 x 8 (56 blocks
+  // of 128) 3.26 and 3.53 ms, 2,048 x 8 (128) 5.15 and 5.31; 4,480 x 4 (140)
+  // 13.1 and 11.4, 640 x 32 (160) 4.52 and 4.43, 4,480 x 8 (280) 14.0 and 12.4
+  const int np64 = (int64_t)np * nrhs <= 128 ? (int)((n + 63) / 64) : 0;
   // the least-squares steps of iterations j..j+cnt-1
   auto columns = [&](int64_t j, int cnt, int32_t* seen, hipStream_t q) {
     if (j > 1)
