@@ -439,11 +439,14 @@ __device__ inline double rcp_newton(double x) {
 // One-sided (Hestenes) Jacobi on the columns of the column-major nc x nc
 // matrix B (column p at col(p)): pairs of columns are rotated, in the round-robin order that
 // lets each row of 16 lanes of the block rotate a disjoint pair at once, until
-// in one sweep no pair has |b_p^H b_q| > tol ||b_p|| ||b_q||.  (A column
-// below 1e-14 of big, the rounding level of the matrix, is not turned against
-// another any more once |b_p^H b_q| <= 1e-17 big times the longer of the
-// two: no singular value moves by its rounding.  Columns from na on, below
-// 1e-17 of big, would never be turned and take no part.)  The 2 x 2 step
+// in one sweep no pair has |b_p^H b_q| > tol ||b_p|| ||b_q||.  (With big2 >
+// 0, a column below 1e-14 of big, the rounding level of the matrix, is not
+// turned against another any more once |b_p^H b_q| <= 1e-17 big times the
+// longer of the two, and columns from na on, below 1e-17 of big, take no part.
+// Columns above 1e-8 of big lose nothing: the turn left out would move one
+// by at most 1e-31 big^2 / ||b_p||^2 of its length, 1e-15.  The columns at
+// the rounding level are not turned out of the others, so they must not be
+// kept: orthogonalise.)  The 2 x 2 step
 // for alpha = ||b_p||^2, beta = ||b_q||^2, gamma = b_p^H b_q = |gamma| e:
 // zeta = (beta - alpha) / (2 |gamma|), t = sign(zeta) / (|zeta| +
 // sqrt(1 + zeta^2)), c = 1 / sqrt(1 + t^2), s = c t,
@@ -541,7 +544,8 @@ __device__ __forceinline__ int hestenes_jacobi(Cols col, int nc, int na, double 
 // graded triangle 7 to 9.  Written sorted by decreasing sigma: sigma (rk per
 // cell, zero beyond nc), Ut = U~ and Uts = U~ S^{-1} (column-major rk x rk,
 // first nc columns, zero rows beyond nc), info = 0, or 1 if the sweeps ran
-// out.  LDS = true keeps the nc x nc working matrix in LDS, else in work
+// out; cut leaves columns at the rounding level unturned.  LDS = true keeps
+// the nc x nc working matrix in LDS, else in work
 // (rk x rk per cell) with as many of its columns in LDS as fit (generic
 // pointers).  Bound by one CU's bandwidth to the matrix and the latency of a
 // rotation in each of the nc - 1 steps of a sweep: 96 cells of order 144 17.1
@@ -551,8 +555,8 @@ __device__ __forceinline__ int hestenes_jacobi(Cols col, int nc, int na, double 
 template <bool LDS>
 __global__ void __launch_bounds__(1024) core_svd_kernel(const double2* __restrict__ X, int rk,
                                                         const int32_t* __restrict__ ncell, double2* work,
-                                                        int lds_entries, double tol,
-                                                        int max_sweeps, double* __restrict__ sigma,
+                                                        int lds_entries, double tol, int max_sweeps, bool cut,
+                                                        double* __restrict__ sigma,
                                                         double2* __restrict__ Ut, double2* __restrict__ Uts,
                                                         int32_t* __restrict__ info) {
   extern __shared__ double2 lds[];
@@ -593,9 +597,9 @@ __global__ void __launch_bounds__(1024) core_svd_kernel(const double2* __restric
   }
   auto col = [&](int p) { return LDS || p < nl ? lds + p * nc : A + p * nc; };
   constexpr int NR = LDS ? kHeldRows : kLaneRows;
-  if (threadIdx.x == 0) last = 0;
+  if (threadIdx.x == 0) last = cut ? 0 : nc - 1;
   __syncthreads();
-  for (int j = wave; j < nc; j += nw) {  // the last column above the rounding level
+  for (int j = wave; j < nc && cut; j += nw) {  // the last column above the rounding level
     const double2* cj = col(j);
     double q = 0;
     for (int i = lane; i < nc; i += 64) q += cj[i].x * cj[i].x + cj[i].y * cj[i].y;
@@ -604,8 +608,9 @@ __global__ void __launch_bounds__(1024) core_svd_kernel(const double2* __restric
   }
   __syncthreads();
   const int na = last + 1;
-  const int sweeps = nc <= 16 * NR ? hestenes_jacobi<NR>(col, nc, na, tol, f2, max_sweeps, &flag)
-                                   : hestenes_jacobi<0>(col, nc, na, tol, f2, max_sweeps, &flag);
+  const double big2 = cut ? f2 : 0.0;
+  const int sweeps = nc <= 16 * NR ? hestenes_jacobi<NR>(col, nc, na, tol, big2, max_sweeps, &flag)
+                                   : hestenes_jacobi<0>(col, nc, na, tol, big2, max_sweeps, &flag);
   for (int j = wave; j < nc; j += nw) {
     double q = 0;
     const double2* cj = col(j);
@@ -1036,83 +1041,109 @@ static cbfm_cbf_s* orthogonalise(const cbfm_mesh_s* m, double2* QA_p, int S, int
   const MeshHost& h = m->h;
   const int nall = h.nblocks, nb = share ? 1 : nall;  // cells of the mesh, cells built
   const int rk = std::min(S, Nmax);
+  Scratch info((size_t)nb * sizeof(int32_t), s);  // per cell: the Jacobi SVD ran out of sweeps
+  std::vector<int32_t> hinfo(nb);
   // with N >= S in every cell the QR of the S x N matrices gives an S x N
   // R again: the matrices themselves serve (Sec. III-B's G'_m is the core).
   // 96 cells of 312 RWGs, S = 144: 3.8 ms saved
-  const bool qr = *std::min_element(hN.begin(), hN.begin() + nb) < S;
-  Scratch info((size_t)nb * sizeof(int32_t), s);  // per cell: the Jacobi SVD ran out of sweeps
-  std::vector<int32_t> hinfo(nb);
-  Scratch Rf(qr ? (size_t)nb * 2 * rk * Nmax * sizeof(double2) : 0, s);  // per cell R_M, then R_J
-  if (qr) {
-    hipLaunchKernelGGL(cell_qr_kernel, dim3(2 * nb), dim3(1024), (size_t)S * sizeof(double2), s, QA_p, S,
-                       Nmax, dN_p, rk, Rf.as<double2>());
-    CBFM_HIP(hipGetLastError());
-  }
+  bool qr = *std::min_element(hN.begin(), hN.begin() + nb) < S;
+  std::unique_ptr<Scratch> Rf;  // with the QR: per cell R_M, then R_J
   // factor w (0: M, 1: J) of cell b: row-major rk x Nmax, or without the QR
   // the transpose, row-major Nmax x S
   auto factor = [&](int b, int w) {
-    return qr ? Rf.as<double2>() + (size_t)(2 * b + w) * rk * Nmax : QA_p + (size_t)(2 * b + w) * S * Nmax;
+    return qr ? Rf->as<double2>() + (size_t)(2 * b + w) * rk * Nmax : QA_p + (size_t)(2 * b + w) * S * Nmax;
   };
-  const int64_t ldf = qr ? Nmax : S;
-  // core X = R_M G_m R_J^H (column-major rk x rk), computed as its row-major
-  // transpose conj(R_J) G_m^T R_M^T = -conj(R_J) G_m R_M^T (G_m antisymmetric)
   Scratch Gm((size_t)nb * Nmax * Nmax * sizeof(double2), s);
   Scratch T2((size_t)nb * Nmax * rk * sizeof(double2), s);
   Scratch core((size_t)nb * rk * rk * sizeof(double2), s);
   hipLaunchKernelGGL(cell_gram_kernel, dim3((Nmax + 255) / 256, Nmax, nb), dim3(256), 0, s, djobs, Nmax,
                      m->tplus.as<int32_t>(), m->tminus.as<int32_t>(), m->aplus.as<int32_t>(), m->aminus.as<int32_t>(),
                      m->tri_edge.as<int32_t>(), m->tri_sign.as<int32_t>(), m->length.as<double>(), Gm.as<double2>());
-  std::vector<GemmDesc> d1, d2;
-  for (int b = 0; b < nb; ++b) {
-    const int Nb = hN[b];
-    double2* G = Gm.as<double2>() + (size_t)b * Nmax * Nmax;
-    double2* t2 = T2.as<double2>() + (size_t)b * Nmax * rk;
-    d1.push_back(gemm(G, Nb, OP_N, factor(b, 0), ldf, qr ? OP_T : OP_N, t2, rk, Nb, rk, Nb));
-    d2.push_back(gemm(factor(b, 1), ldf, qr ? OP_R : OP_C, t2, rk, OP_N, core.as<double2>() + (size_t)b * rk * rk, rk,
-                      rk, rk, Nb, -1.0));
-  }
   CBFM_HIP(hipGetLastError());
-  zgemm_batched(d1, s);
-  zgemm_batched(d2, s);
+  // core X = R_M G_m R_J^H (column-major rk x rk), computed as its row-major
+  // transpose conj(R_J) G_m^T R_M^T = -conj(R_J) G_m R_M^T (G_m antisymmetric)
+  auto form_core = [&] {
+    if (qr) {
+      Rf.reset(new Scratch((size_t)nb * 2 * rk * Nmax * sizeof(double2), s));
+      hipLaunchKernelGGL(cell_qr_kernel, dim3(2 * nb), dim3(1024), (size_t)S * sizeof(double2), s, QA_p, S,
+                         Nmax, dN_p, rk, Rf->as<double2>());
+      CBFM_HIP(hipGetLastError());
+    }
+    const int64_t ldf = qr ? Nmax : S;
+    std::vector<GemmDesc> d1, d2;
+    for (int b = 0; b < nb; ++b) {
+      const int Nb = hN[b];
+      double2* G = Gm.as<double2>() + (size_t)b * Nmax * Nmax;
+      double2* t2 = T2.as<double2>() + (size_t)b * Nmax * rk;
+      d1.push_back(gemm(G, Nb, OP_N, factor(b, 0), ldf, qr ? OP_T : OP_N, t2, rk, Nb, rk, Nb));
+      d2.push_back(gemm(factor(b, 1), ldf, qr ? OP_R : OP_C, t2, rk, OP_N, core.as<double2>() + (size_t)b * rk * rk, rk,
+                        rk, rk, Nb, -1.0));
+    }
+    zgemm_batched(d1, s);
+    zgemm_batched(d2, s);
+  };
   // SVD of the cores: right singular vectors U~ and U~ S^{-1}
   Scratch sv((size_t)nb * rk * sizeof(double), s);
   Scratch Ut((size_t)nb * rk * rk * sizeof(double2), s);
   Scratch Uts((size_t)nb * rk * rk * sizeof(double2), s);
-  {
+  std::vector<double> hs((size_t)nb * rk);
+  auto core_svd = [&](bool cut) {
     const int ncmax = std::min(Nmax, rk);
     const size_t lds = (size_t)ncmax * ncmax * sizeof(double2) + (size_t)ncmax * (sizeof(double2) + 12);
     const double tol = std::sqrt((double)ncmax) * 2.220446049250313e-16;
     const int max_sweeps = 60;
     if (lds <= core_svd_lds_limit()) {
       hipLaunchKernelGGL(core_svd_kernel<true>, dim3(nb), dim3(1024), lds, s, core.as<double2>(), rk,
-                         dN_p, nullptr, 0, tol, max_sweeps, sv.as<double>(), Ut.as<double2>(),
+                         dN_p, nullptr, 0, tol, max_sweeps, cut, sv.as<double>(), Ut.as<double2>(),
                          Uts.as<double2>(), info.as<int32_t>());
     } else {
       Scratch work((size_t)nb * rk * rk * sizeof(double2), s);
       const size_t own = (size_t)ncmax * (sizeof(double2) + 12), lim = core_svd_lds_limit();
       const int entries = lim > own ? (int)((lim - own) / sizeof(double2)) : 0;
       hipLaunchKernelGGL(core_svd_kernel<false>, dim3(nb), dim3(1024), entries * sizeof(double2) + own, s,
-                         core.as<double2>(), rk, dN_p, work.as<double2>(), entries, tol, max_sweeps,
+                         core.as<double2>(), rk, dN_p, work.as<double2>(), entries, tol, max_sweeps, cut,
                          sv.as<double>(), Ut.as<double2>(), Uts.as<double2>(), info.as<int32_t>());
     }
     CBFM_HIP(hipGetLastError());
+    CBFM_HIP(hipMemcpyAsync(hs.data(), sv.p, hs.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+    CBFM_HIP(hipMemcpyAsync(hinfo.data(), info.p, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    CBFM_HIP(hipStreamSynchronize(s));
+    for (int b = 0; b < nb; ++b)
+      CBFM_REQUIRE(hinfo[b] == 0, CBFM_E_HIP, "cell " + std::to_string(b) + ": Jacobi SVD did not converge");
+  };
+  auto kept = [&](int b) {  // L_b
+    const double* sb = &hs[(size_t)b * rk];
+    int L = 0;
+    while (L < rk && L < hN[b] && sb[L] > 0 && sb[L] >= delta_svd * sb[0]) ++L;
+    return max_L > 0 ? std::min(L, max_L) : L;
+  };
+  form_core();
+  core_svd(true);
+  // A caller who keeps functions down to the rounding level (delta_svd below
+  // 1e-8, no lower cap): every column turned, on factors that the QR has
+  // graded, where singular values and vectors of dependent waves are good
+  // to their own size.  (Above 1e-8 neither changes what is kept; the cube's
+  // 27 cores of order 96 take 1.4 ms, 1.7 with every column turned.)
+  bool deep = false;
+  for (int b = 0; b < nb; ++b) {
+    const int L = kept(b);
+    deep = deep || (L > 0 && hs[(size_t)b * rk + L - 1] < 1e-8 * hs[(size_t)b * rk]);
   }
-  std::vector<double> hs((size_t)nb * rk);
-  CBFM_HIP(hipMemcpyAsync(hs.data(), sv.p, hs.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-  CBFM_HIP(hipMemcpyAsync(hinfo.data(), info.p, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  CBFM_HIP(hipStreamSynchronize(s));
-  for (int b = 0; b < nb; ++b)
-    CBFM_REQUIRE(hinfo[b] == 0, CBFM_E_HIP, "cell " + std::to_string(b) + ": Jacobi SVD did not converge");
+  if (deep) {
+    if (!qr) {
+      qr = true;
+      form_core();
+    }
+    core_svd(false);
+  }
+  const int64_t ldf = qr ? Nmax : S;
   auto* c = new cbfm_cbf_s();
   try {
     c->mesh = m;
     c->L.resize(nall);
     for (int b = 0; b < nb; ++b) {
       const double* sb = &hs[(size_t)b * rk];
-      int L = 0;
-      const int Nb = hN[b];
-      while (L < rk && L < Nb && sb[L] > 0 && sb[L] >= delta_svd * sb[0]) ++L;
-      if (max_L > 0) L = std::min(L, max_L);
+      const int L = kept(b);
       CBFM_REQUIRE(L > 0, CBFM_E_RANK, "cell " + std::to_string(b) + " keeps no CBF");
       c->L[b] = L;
       c->sigma.insert(c->sigma.end(), sb, sb + L);
