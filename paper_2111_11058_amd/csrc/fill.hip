@@ -920,6 +920,21 @@ static void near_stage(const cbfm_mesh_s* m, const FillConsts& fc, const NearPai
   CBFM_HIP(hipGetLastError());
 }
 
+// Over the blocks the columns vary fastest; the rows do where the source
+// triangles' tables (some 38 values each) outgrow one XCD's L2, since the
+// stores sweep them out and the blocks in flight should share 256 columns
+// (19,968 columns in double 47.1 -> 45.8 ms; in float, 3 MB of tables, 2.07
+// against 2.18; 1,728 in double 0.554 against 0.566), and in double where a
+// row is one or two blocks, so that the ragged ones come last (300 x 300:
+// 46.6 -> 42.5 us).  The line at two blocks is a flat one: whole fills of 300
+// and 432 columns 1.0 to 1.5 % faster, of 588 to 1,200 columns 0.2 slower to
+// 1.5 % faster, of 1,728 square the 2 % slower above.  Never where the
+// columns' blocks exceed a grid's second dimension.
+static bool fill_rows_first(int64_t nct, bool fp64) {
+  if ((nct + 255) / 256 > 65535) return false;
+  return nct * 38 * (fp64 ? 8 : 4) > (4 << 20) || (fp64 && nct <= 512);
+}
+
 void fill_local(const cbfm_mesh_s* m, const Media& md, int precision, int layout,
                 const int32_t* rowTris, int64_t nrt, const int32_t* colTris, int64_t nct,
                 const NearPair* near, int64_t nnear, void* local, hipStream_t s, void* near_buf) {
@@ -928,17 +943,8 @@ void fill_local(const cbfm_mesh_s* m, const Media& md, int precision, int layout
   const bool lossy = md.k2i != 0.0;
   CBFM_REQUIRE(nrt <= 65535, CBFM_E_ARG, "too many row triangles for one launch");
   dim3 grid((unsigned)((nct + 255) / 256), (unsigned)nrt);
-  // Over the blocks the columns vary fastest; the rows do where the source
-  // triangles' tables (some 38 values each) outgrow one XCD's L2, since the
-  // stores sweep them out and the blocks in flight should share 256 columns
-  // (19,968 columns in double 47.1 -> 45.8 ms; in float, 3 MB of tables, 2.07
-  // against 2.18; 1,728 in double 0.554 against 0.566), and in double where a
-  // row is one or two blocks, so that the ragged ones come last (300 x 300:
-  // 46.6 -> 42.5 us).
-  const bool rows_first =
-      nct * 38 * (precision == CBFM_FP64 ? 8 : 4) > (4 << 20) || (precision == CBFM_FP64 && nct <= 512);
+  const bool rows_first = fill_rows_first(nct, precision == CBFM_FP64);
   if (rows_first) std::swap(grid.x, grid.y);
-  CBFM_REQUIRE(grid.y <= 65535, CBFM_E_ARG, "too many column triangles for one launch");
   {
   TimedLaunch tl(precision == CBFM_FP64 ? T_FILL_REGULAR : T_FILL_REGULAR_F32, s,
                  (double)nrt * (double)nct);  // work: triangle pairs
