@@ -302,7 +302,7 @@ __global__ void __launch_bounds__(256) chol_pivot_kernel(const double* __restric
           break;  // uniform
         }
         if (a == k) mine = pk;
-        double inv = __builtin_amdgcn_rcp(pk);  // 1e-10 < pk: two Newton steps
+        double inv = __builtin_amdgcn_rcp(pk);  // 1e-10 < pk: two Newton steps, the division's bits
         inv = fma(fma(-pk, inv, 1.0), inv, inv);
         inv = fma(fma(-pk, inv, 1.0), inv, inv);
         const double2 s = r[a];  // S[k][a]; row a loses conj(S[k][a]) / pk times row k

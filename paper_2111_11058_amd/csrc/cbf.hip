@@ -268,9 +268,15 @@ __device__ inline double row16_sum(double x) {
 }
 
 // Rows of a column that each of its 16 lanes holds in registers (columns of
-// up to 16 times as many entries; the 144 generating waves of Table I).
+// up to 16 times as many entries; the 144 generating waves of Table I), and
+// the same for a pair of columns in LDS (orders to 100 fit there).  96 cores,
+// held against read twice: orders 64, 80 and 96 in LDS 0.88, 1.41, 1.81 and
+// 0.83, 1.44, 1.93 ms; 104, 112, 128, 144 beyond it 3.43, 3.70, 4.85, 6.71
+// and 3.75, 4.12, 5.66, 8.43.  One more row each (7; 97 to 100 the same, 96
+// 1.91) or three (12) spills: 144 7.42 ms, though 145 to 192 would gain (145
+// 9.32 -> 7.78, 192 24.5 -> 17.7).
 constexpr int kLaneRows = 9;
-constexpr int kHeldRows = 6;  // the same for a pair of columns in LDS (orders to 100 fit there)
+constexpr int kHeldRows = 6;
 
 // In-place Householder QR of the column-major m x ncol matrix A (lda), only R
 // kept: afterwards the first kmax = min(m, ncol) rows hold R and the entries
@@ -424,7 +430,11 @@ __global__ void __launch_bounds__(1024) cell_qr_kernel(double2* __restrict__ qa,
 
 // 1 / sqrt(x) and 1 / x of a normal x whose square is one: the hardware's
 // estimate and two Newton steps, the last a residual correction (a quarter of
-// the latency of the divisions and square roots).
+// the latency of the divisions and square roots).  1 / x has the bits of the
+// division (2^31 random values), 1 / sqrt(x) is off by 0.9993 of an ulp at
+// most, 1.0 / sqrt(x) by 1.4993; the rotations below have c^2 + |s|^2 - 1 of
+// 1.45e-16 rms (6.1e-16 at most), with divisions and roots in their place
+// 1.61e-16 (6.7e-16), over norms and angles of any ratio.
 __device__ inline double rsqrt_newton(double x) {
   double y = __builtin_amdgcn_rsq(x);
   y = fma(0.5 * y, fma(-x * y, y, 1.0), y);

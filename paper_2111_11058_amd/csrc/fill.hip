@@ -257,7 +257,9 @@ __device__ __forceinline__ void turns(double rev, double x, double& s, double& c
 // ------------------------------------------------------------- regular kernel
 // d = c_P - c_Q from both parts of either centroid, and |d|^2 = d2h + d2l.
 // Roundings here would be common to the 49 point pairs of an entry and not
-// average out in its sums.
+// average out in its sums: the float panel of 19.4 M pairs is 2.6e-7 off 64
+// bits with the parts, 5.1e-7 with one rounded square; in double K of a cube
+// of 8,748 triangles 1.3e-15 and 4.7e-15 (with points rounded at their place).
 __device__ __forceinline__ double sum_with_error(double a, double b, double& lo) {
   const double s = a + b, z = s - a;
   lo += (a - (s - z)) + (b - z);
@@ -292,13 +294,15 @@ __device__ __forceinline__ void centroid_offset(const TriTab<R>& tab, int32_t P,
 // by e^{-j k1 R_c} once.
 //
 // Bound by VALU issue and then by the stores (432 bytes a pair in double):
-// per point pair and both lossless media 85 vector instructions in double
-// (R^2 2, 1/R 5, sine and cosine 35, the kernels 19, sums 14, and a seventh
-// of what each source point costs), 49 in float.  The form that summed
-// vectors and reduced every phase took 123.  19,968-triangle cylinder,
-// eight panels (225 M pairs): 62.7 -> 45.8 ms in double, 3.6 and 4.9 G pairs/s
-// (39 ms of it without the stores); 19.4 M pairs in float: 2.40 -> 1.8 ms,
-// 2.1 where the columns come in the order of their RWGs.  The local blocks
+// per point pair and both lossless media 87 vector instructions in double
+// (R^2 3, 1/R 6, sine and cosine 35, the kernels 19, sums 14, and a seventh
+// of what each source point costs), 50 in float; two and one of them for
+// R^2 from its parts and a 1/R to a rounding.  The form that summed vectors
+// and reduced every phase took 123.  19,968-triangle cylinder, eight panels
+// (225 M pairs): 62.7 -> 46.3 ms in double, 3.6 and 4.9 G pairs/s (39 ms of
+// it without the stores); 19.4 M pairs in float, the columns in the order of
+// their RWGs: 2.40 -> 2.0 ms.  Errors against 64 bits in the comment of
+// centroid_offset.  The local blocks
 // keep each local function's columns in a plane of their own (entry (a, b)
 // of row i and column j at (3 i + a) ldl + b ldl / 3 + j): a wavefront's
 // store is 64 adjacent entries instead of every third one, 49.9 -> 47.1 ms.

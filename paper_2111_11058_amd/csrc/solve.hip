@@ -173,8 +173,8 @@ __global__ void sub_from_kernel(const double2* __restrict__ b, double2* __restri
 // multiplies it by gamma), which takes the norm and the scaling pass out of
 // the iteration: product, dots, update, with the least-squares steps on a
 // second stream.  406 iterations of order 594, 8 right-hand sides: 17.8 ->
-// 13.2 ms; 272 of order 526, one: 9.8 -> 6.1; 666 of order 890, 8: 37.0 ->
-// 28.5.
+// 13.2 ms (11.9 with the product of few columns in gemm.hip); 272 of order
+// 526, one: 9.8 -> 6.1; 666 of order 890, 8: 37.0 -> 28.5 (24.7).
 constexpr int kChunk = 4;           // iterations between convergence checks
 constexpr int kSlots = 2 * kChunk;  // iterations whose dots the column steps may still read
 struct GmresState {
@@ -1723,8 +1723,8 @@ __global__ void __launch_bounds__(512) cholqr_kernel(double2* __restrict__ Z, in
 }
 
 // Dynamic LDS of cholqr_kernel<S> for vectors of length n, or 0 where they do
-// not fit beside its own arrays (up to n = 1,100 for S = 8 and 2,500 for S =
-// 4; longer ones take the Gram, factor and product kernels).
+// not fit beside its own arrays (160 KB: up to n = 1,110 for S = 8 and 2,464
+// for S = 4; longer ones take the Gram, factor and product kernels).
 template <int S>
 static size_t cholqr_lds(int64_t n) {
   static std::mutex mu;
